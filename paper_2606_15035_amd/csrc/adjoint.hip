@@ -55,7 +55,7 @@ struct GlobalAdjSink {
 
 // The block's LDS tile over its chunk's node box (nine doubles per node);
 // o[] takes the particle's frame to the tile's.  A node outside the box
-// (not expected: the box has a node of margin per side) goes to global
+// (not expected: the box holds every orbit) goes to global
 // memory.  The tile pointer carries the LDS address space, so the additions
 // are LDS atomics (through a plain pointer they compiled to flat atomics,
 // the slower path that serves either memory).
@@ -359,8 +359,7 @@ __global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P) {
 // The push terms over cell-sorted particles, one block per chunk of kAdjChunk
 // particles whose wavefronts' lanes sit kAdjChunk / 64 particles apart (one
 // cell apart at 64 particles per cell), as in the current scatter: the block
-// finds the node box of its chunk's orbits and end points (one node of
-// margin per side), sums the nine mesh adjoints of its particles in an LDS
+// finds the node box of its chunk's orbits and end points, sums the nine mesh adjoints of its particles in an LDS
 // tile over that box, and adds the tile to global memory once.  A chunk
 // whose box exceeds the tile adds straight to global memory.  The kernel
 // runs at one wavefront per SIMD (its registers), so one block per CU loses
@@ -393,15 +392,11 @@ __global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P
     if (i >= P.np) continue;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double x0 = P.x[a * P.np + i], d = P.dt * P.vb[a * P.np + i];
-      const double u0 = x0 * G.invH[a], u1 = (x0 + d) * G.invH[a];
-      const int lo = to_int_clamped(floor(fmin(u0, u1) + Spline<2>::base_off)) +
-                     Spline<2>::first_off - 1;
-      const int hi = to_int_clamped(floor(fmax(u0, u1) + Spline<2>::base_off)) +
-                     Spline<2>::first_off + 3;
+      int lo, n, b0;
+      orbit_nodes<2>(P.x[a * P.np + i], P.dt * P.vb[a * P.np + i], G.invH[a], lo, n, b0);
       const int rel = min_image(lo - s_ref[a], G.n[a]);
       rmin[a] = min(rmin[a], rel);
-      rmax[a] = max(rmax[a], rel + (hi - lo));
+      rmax[a] = max(rmax[a], rel + n);
     }
   }
   int tlo[3], dim[3];
@@ -428,10 +423,8 @@ __global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P
                      use_tile};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double x0 = P.x[a * P.np + i], d = P.dt * P.vb[a * P.np + i];
-      const double u0 = x0 * G.invH[a], u1 = (x0 + d) * G.invH[a];
-      const int lo = to_int_clamped(floor(fmin(u0, u1) + Spline<2>::base_off)) +
-                     Spline<2>::first_off - 1;
+      int lo, n, b0;
+      orbit_nodes<2>(P.x[a * P.np + i], P.dt * P.vb[a * P.np + i], G.invH[a], lo, n, b0);
       const int raw = lo - s_ref[a];
       // particle frame -> chunk frame -> tile
       sink.o[a] = min_image(raw, G.n[a]) - raw - s_ref[a] - tlo[a];

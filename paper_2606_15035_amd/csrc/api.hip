@@ -229,13 +229,14 @@ struct ecpic_sim {
   double* Jb[2];     // orbit current, double-buffered across Picard passes
   int jlast = 0;     // index of the current of the last accepted pass
   bool jclean = true;  // Jb[1 - jlast] is zero (each pass's transform clears the other buffer)
-  int chunk = 4096;    // scatter chunk; 2048 once chunks stop fitting the LDS tile
+  int chunk = 256, span = 256;  // automatic scatter chunk, span of its lanes
+  bool scatter_mm = false;  // see use_scatter_mm
   // workspace
   double2* Jh;
   double2* batch;
   double* realbuf;
   double* Uhalf;
-  int* gwork;  // gather work list: [count, indices of blocks whose box missed the LDS tile]
+  int* gwork;  // gather work list: [count, particles whose orbits left their block's LDS tile]
   int* sboxes;  // node boxes of the scatter's chunks, found in a step's first pass
   int* gboxes;  // node boxes of the gather's blocks, likewise
   double2* tw[3];
@@ -272,11 +273,9 @@ struct ecpic_sim {
     P.np = np;
     P.split = cfg.split_orbit_at_knots;
     P.rule = rule;
-    // long chunks pay off for the LDS atomics (32^3 two-stream: FP64
-    // 0.287 -> 0.245 ms per pass, mixed 0.247 -> 0.239 ms); the wider cubic
-    // stencil takes the short ones
-    P.chunk = cfg.scatter_chunk > 0 ? cfg.scatter_chunk
-                                    : (cfg.spline_degree >= 3 ? 2048 : chunk);
+    P.chunk = cfg.scatter_chunk > 0 ? cfg.scatter_chunk : chunk;
+    P.span = scatter_mm ? P.chunk : std::max(P.chunk, span);
+    P.scatter_mm = scatter_mm ? 1 : 0;
     P.nsp = nsp;
     for (int k = 0; k < kMaxSpecies; ++k) {
       P.qs[k] = qs[k];
@@ -300,6 +299,53 @@ struct ecpic_sim {
 };
 
 namespace {
+
+constexpr int kMaxSpan = 16384;
+
+// Span of the scatter's lanes: the power of two nearest to the particles of 64
+// cells, so that the 64 lanes of a wavefront sit in about as many cells and
+// their LDS additions do not meet (fewer cells: lanes of one cell wait for each
+// other; more: the node box outgrows the LDS tile).  Measured per pass with
+// spans of 1, 2, 4 and 8 times the particles per block: mixed, 33,554,432 at 128
+// per cell, 2048 per block 4202 / 3607 / 3417 / 3440 us (the third is this rule);
+// linear unsplit, 131,072 at 32 per cell, 256 per block 110 / 51 / 33 / 25 us
+// (the fourth); quadratic, 100,002 at 12 per cell, 256 per block 33 / 28 / 27 /
+// 120 us (the third); 300,007 at 9 per cell and orbits of several cells, 256 per
+// block 90 / 90 / 323 / 1205 us (the second).
+int auto_span(int64_t np, int64_t ncell) {
+  int64_t span = 256;
+  while (span < kMaxSpan && span * span * 2 < 64 * np / ncell * (64 * np / ncell)) span *= 2;
+  return (int)span;
+}
+
+// Particles per scatter block where the configuration leaves it open: the span,
+// at most 2048, halved down to 256 while there are fewer than three blocks per
+// compute unit.  Measured per pass at the span above: linear, 131,072
+// particles, 256 / 512 / 1024 per block 13.5 / 12.8 / 15.2 us; cubic, 524,288 at
+// 16 per cell 90 / 82 / 85 us; quadratic, 300,007 90 / 106 us; mixed quadratic,
+// 2,097,152 at 64 per cell, 1024 / 2048 / 4096 152 / 150 / 148 us.
+int auto_chunk(int64_t np, int span) {
+  int chunk = std::min(span, 2048);
+  while (chunk > 256 && np < (int64_t)chunk * 768) chunk /= 2;
+  return chunk;
+}
+
+// most scatter blocks of any chunk and span (blocks of 256 particles, and those
+// of the last span that may be empty)
+int64_t scatter_blocks_max(int64_t np) { return scatter_blocks(np > 0 ? np : 1, 256, kMaxSpan); }
+
+// The FP64 current by matrix instructions (k_scatter_mm): quadratic shape,
+// sorted in every step, and at least 48 particles per cell, so that the
+// particles of one stencil fill its products (K = 4).  Measured per pass
+// against the kernel with one LDS addition per lane, node and component: 64
+// particles per cell (2,097,152) 150 against 180 us, 12 per cell (100,002) 36
+// against 27 us.  The linear shape (8 nodes) has too few additions to gain, the
+// cubic one runs out of registers (524,288: 140 against 82 us).
+bool use_scatter_mm(const ecpic_config* c, int64_t np, int64_t ncell) {
+  return c->precision == ECPIC_FP64 && c->split_orbit_at_knots == 1 && c->spline_degree == 2 &&
+         c->sort_interval >= 0 && c->sort_interval <= 1 && np >= 48 * ncell;
+}
+constexpr int kMmChunk = 1024;  // its chunk at most: a 1024-node tile holds the box of 16 cells
 
 // fn(live store, sort alternate) for the store the configuration selects
 template <class Fn>
@@ -348,8 +394,8 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->realbuf = w.take<double>(9 * nc);
   S->Uhalf = w.take<double>(3 * nc);
   for (int a = 0; a < 3; ++a) S->tw[a] = w.take<double2>(S->G.n[a] / 2);
-  S->gwork = w.take<int>(particle_blocks(np) + 1);
-  S->sboxes = w.take<int>((size_t)kBoxInts * std::max<int64_t>(scatter_blocks(np, 2048), 1));
+  S->gwork = w.take<int>((np > 0 ? np : 1) + 1);
+  S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
   S->gboxes = w.take<int>((size_t)kBoxInts * std::max<int64_t>(particle_blocks(np), 1));
   // the plain iteration's next iterate is the gather's output, so the gather
   // (and the step's set-up) can hand the scatter vbar^p directly
@@ -358,7 +404,7 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->sc.red = w.take<double>(S_NSLOTS);
   S->sc.spread = w.take<double>((size_t)S_NSLOTS * kSpread * kSpreadStride);
   const int64_t maxblk = std::max<int64_t>(
-      std::max<int64_t>(particle_blocks(np), scatter_blocks(np, 2048)),
+      scatter_blocks_max(np),  // at least particle_blocks(np)
       std::max<int64_t>(mesh_blocks(nc), cn_pencil_blocks(S->G)));
   S->sc.part_stride = std::max<int64_t>((int64_t)kMaxSumValues * (maxblk > 0 ? maxblk : 1),
                                         (int64_t)kAndersonSums * anderson_dot_blocks(3 * np));
@@ -433,7 +479,7 @@ ecpic_status sort_by_graph(ecpic_sim* S, PS& cur, PS& alt) {
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-      launch_sort(cs, S->G, S->np, c, a, i1, i2, S->sb, S->vit, S->vbar);
+      launch_sort(cs, S->G, S->cfg.spline_degree, S->np, c, a, i1, i2, S->sb, S->vit, S->vbar);
       e = hipStreamEndCapture(cs, &graph);
     }
     (void)hipStreamDestroy(cs);
@@ -601,6 +647,10 @@ ecpic_status ecpic_create(const ecpic_config* cfg, int64_t n_particles, void* st
   S->static_scratch = static_ws;
   S->fix_scale = cfg->fixed_point_scale > 0.0 ? cfg->fixed_point_scale : 0x1p40;
   S->rule = gauss_rule01(quad_rule_points(cfg));
+  S->scatter_mm = use_scatter_mm(cfg, n_particles, S->G.ncell);
+  S->span = auto_span(n_particles, S->G.ncell);
+  S->chunk = auto_chunk(n_particles, S->span);
+  if (S->scatter_mm) S->chunk = std::min(S->chunk, kMmChunk);
   carve(S, static_cast<char*>(state_dev), static_cast<char*>(workspace_dev), nullptr, nullptr);
   S->state_base = static_cast<char*>(state_dev);
   S->state_size = need_s;
@@ -628,8 +678,7 @@ ecpic_status ecpic_create(const ecpic_config* cfg, int64_t n_particles, void* st
   if (hipMemsetAsync(S->sc.red, 0, sizeof(double) * S_NSLOTS, S->stream) != hipSuccess ||
       hipMemsetAsync(S->sc.spread, 0, sizeof(double) * S_NSLOTS * kSpread * kSpreadStride,
                      S->stream) != hipSuccess ||
-      hipMemsetAsync(S->gwork, 0, sizeof(int) * (particle_blocks(n_particles) + 1), S->stream) !=
-          hipSuccess ||
+      hipMemsetAsync(S->gwork, 0, sizeof(int), S->stream) != hipSuccess ||
       (S->Jfix && hipMemsetAsync(S->Jfix, 0, sizeof(unsigned long long) * 3 * S->G.ncell,
                                  S->stream) != hipSuccess) ||
       hipStreamSynchronize(S->stream) != hipSuccess) {
@@ -801,7 +850,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   const CurrentOut cout{nullptr, S->Jfix, S->fix_scale};
   const double fix_unit = S->q / S->G.dV / S->fix_scale;
   const bool fused = fused_field_solve_fits(S->G);
-  launch_reset_slots(s, S->sc, S_PIECES, 2);  // pieces, scatter tile misses
+  launch_reset_slots(s, S->sc, S_PIECES, 1);
   int p = 0, jcur = 1 - S->jlast;
   if (!S->jclean && !S->mixed()) launch_fill(s, 3 * nc, S->Jb[jcur], 0.0);  // after a failed step
   S->jclean = false;
@@ -824,6 +873,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   // expected to run are queued so: pass 1, which every step runs, and the
   // passes every one of the last eight steps ran.  If the step stops before
   // such a pass, its current stays in the buffer that the next step clears.
+  const GatherGrid gg = gather_grid(S->np, nc);
   const int sure = sure_passes(S);
   bool ahead = false;  // this pass's current was queued by the previous pass
   for (p = 0; p <= S->cfg.picard_max; ++p) {
@@ -877,12 +927,12 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
       const FinishJob jobs[7] = {{P_CN, fused ? cn_pencil_blocks(S->G) : (int)mesh_blocks(nc), 3,
                                   S_JE},
                                  {0, 0, 1, S_DJMAX, F_SPREAD_MAX},
-                                 {P_JS, (int)scatter_blocks(S->np, P.chunk), 1, S_JS},
+                                 {P_JS, (int)scatter_blocks(S->np, P.chunk, P.span), 1, S_JS},
                                  {0, 0, 2, S_DVMAX, F_SPREAD_MAX},
                                  {0, 0, 1, S_BAD, F_SPREAD_MAX},
-                                 {0, 0, 2, S_PIECES, F_SPREAD_SUM},
+                                 {0, 0, 1, S_PIECES, F_SPREAD_SUM},
                                  {P_AA,
-                                  mk == 1 ? (int)particle_blocks(S->np) : anderson_dot_blocks(n3),
+                                  mk == 1 ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
                                   anderson_sums(mk), S_AA}};
       launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gwork);
     }
@@ -980,10 +1030,6 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   ecpic_status st = sync_read(S, 0, S_NSLOTS);
   if (st != ECPIC_OK) return st;
   const double* h = S->host;
-  // long chunks whose node boxes overflow the LDS tile fall back to global
-  // atomics; past 1% of the chunks of a step, use the short ones from now on
-  if (P.chunk == 4096 && h[S_SMISS] > 0.01 * (p + 1) * (double)scatter_blocks(S->np, 4096))
-    S->chunk = 2048;
   if (prof) {
     float ta = 0.f, tb = 0.f;
     HIPCHK(hipEventElapsedTime(&ta, S->ev[0], S->ev[1]));
@@ -1300,7 +1346,9 @@ ecpic_status ecpic_checkpoint_restore(ecpic_sim* S, const void* src) {
   CheckpointHeader h;
   std::memcpy(&h, src, sizeof(h));
   if (h.magic != kCheckpointMagic) return fail(ECPIC_EINVAL, "not an ecpic checkpoint");
-  if (std::strncmp(h.version, ecpic_version(), sizeof(h.version)) != 0)
+  // version 0.24 wrote the same layout
+  if (std::strncmp(h.version, ecpic_version(), sizeof(h.version)) != 0 &&
+      std::strncmp(h.version, "ecpic-gfx950 0.24", sizeof(h.version)) != 0)
     return fail(ECPIC_EINVAL, "checkpoint of library %.32s, this is %s", h.version, ecpic_version());
   if (std::memcmp(&h.cfg, &S->cfg, sizeof(ecpic_config)) != 0 || h.np != S->np ||
       h.state_size != S->state_size)
@@ -1326,7 +1374,6 @@ ecpic_status ecpic_checkpoint_restore(ecpic_sim* S, const void* src) {
   S->cur = h.cur;
   S->jlast = h.jlast;
   S->jclean = h.jclean != 0;
-  S->chunk = h.chunk;
   S->nsp = h.nsp;
   S->q = h.q;
   S->m = h.m;
@@ -1387,7 +1434,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
     int* id2 = A.id2;
     Fp64Store cur{const_cast<double*>(x), const_cast<double*>(v), const_cast<double*>(w)};
     Fp64Store alt{A.xs, A.vs, A.ws};
-    launch_sort(s, G, np, cur, alt, id, id2, A.sb);
+    launch_sort(s, G, 2, np, cur, alt, id, id2, A.sb);
     A.id = id;  // the ids of the sorted copies (cur now views A.xs, A.vs, A.ws)
     x = cur.x;
     v = cur.v;
@@ -1562,7 +1609,7 @@ ecpic_status ecpic_field_energy_grad(ecpic_sim* S, double* lF) {
   return ECPIC_OK;
 }
 
-const char* ecpic_version(void) { return "ecpic-gfx950 0.24"; }
+const char* ecpic_version(void) { return "ecpic-gfx950 0.25"; }
 
 }  // extern "C"
 

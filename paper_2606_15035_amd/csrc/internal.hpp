@@ -40,7 +40,6 @@ enum Slot : int {
   S_RL2,        // sum R_h^2                            (sum)
   S_WCUR,       // W of the current field level         (sum)
   S_PIECES,     // orbit pieces summed over particles    (sum of integers)
-  S_SMISS,      // scatter chunks whose node box missed the LDS tile (sum of integers)
   S_NSLOTS
 };
 // Producer sites of block partial sums (each has its own region).
@@ -65,7 +64,10 @@ struct StepParams {
   // particle species (each particle carries its own charge and mass, Sec. 2):
   // a particle of species s has qs[s], ms[s]; one species: the store holds no
   // species array and every particle has (q, m) = (qs[0], ms[0])
-  int chunk;  // particles per scatter block: 4096 or 2048 (always 2048 for degree 3)
+  int chunk;  // particles per scatter block: a power of two in [256, 4096]
+  int span;   // particles over which the lanes of a scatter block are spread: a power of two >= chunk
+  int gper;   // batches of 256 particles per gather block (set by its launcher)
+  int scatter_mm;  // FP64, split, degree 2: the current by matrix instructions
   int nsp;
   double qs[kMaxSpecies];
   double ms[kMaxSpecies];
@@ -136,7 +138,7 @@ void launch_anderson_update(hipStream_t s, int mk, int64_t n, const AndersonVecs
 // host: gamma (mk values) from the anderson_sums(mk) sums of k_aa_dots
 void anderson_gamma(int mk, const double* sums, double* gamma);
 // grid sizes of the producing kernels
-int64_t scatter_blocks(int64_t np, int chunk);
+int64_t scatter_blocks(int64_t np, int chunk, int span);
 int64_t particle_blocks(int64_t np);
 int64_t mesh_blocks(int64_t ncell);
 
@@ -179,18 +181,24 @@ struct AndersonPrev {
   const double* w = nullptr;
   const double* g = nullptr;
 };
-// work: 1 + (blocks of 256 particles) ints, work[0] = 0 on entry; the tiled
-// kernel lists the blocks whose node box missed the LDS tile, the second
-// kernel runs them from global memory; the per-pass finishing kernel resets
-// work[0].  vbar_out (nullable): (vnew + v^n) / 2, the vbar of a next pass
-// whose iterate is vnew.  bx: node boxes of the blocks of 256 particles, as
-// for the scatter's chunks; with reuse, a block one of whose orbits leaves
-// its stored box finds its box again and stores it.
+// Launch shape of the gather (particles.hip): batches of 256 particles per
+// block, blocks, whether the whole mesh sits in LDS, and the blocks of the
+// kernel that runs the listed particles; Anderson partial sums have
+// blocks + list_blocks rows
+struct GatherGrid {
+  int batches, blocks, list_blocks;
+  bool whole_mesh;
+};
+GatherGrid gather_grid(int64_t np, int64_t ncell);
+// work: 1 + np ints, work[0] = 0 on entry; the tiled kernel lists the particles
+// whose orbits leave their block's node box, the second kernel runs them from
+// global memory; the per-pass finishing kernel resets work[0].  vbar_out
+// (nullable): (vnew + v^n) / 2, the vbar of a next pass whose iterate is vnew.
+// bx: node boxes of the blocks, as for the scatter's chunks.
 template <class PS>
-void launch_gather_push(hipStream_t s, int r, const StepParams& P, const PS& st,
-                        const double* vit, double* vnew, double* vbar_out, const double* gbuf,
-                        int* work, Scratch sc, AndersonPrev prev = AndersonPrev{},
-                        ChunkBoxes bx = {});
+void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const double* vit,
+                        double* vnew, double* vbar_out, const double* gbuf, int* work, Scratch sc,
+                        AndersonPrev prev = AndersonPrev{}, ChunkBoxes bx = {});
 template <class PS>
 void launch_sweep(hipStream_t s, int r, const StepParams& P, const PS& st, const double* vit,
                   const double* gbuf, const double* Uhalf, Scratch sc);
@@ -232,14 +240,15 @@ struct SortScratch {
 };
 int64_t sort_scan_blocks(int64_t ncell);
 void launch_iota(hipStream_t s, int64_t n, int* p);
-// Sorts the particles of cur (with their ids) into alt, then swaps cur/alt
+// Sorts the particles of cur (with their ids) into alt by the base node of the
+// degree-r stencil at x^n, then swaps cur/alt
 // and id/id2, so that cur and id hold the sorted particles.  With vit, the
 // permutation also writes the first Picard guess 2 v^n - v^{n-1} of every
 // particle there, in the sorted order (3 x np FP64, component-major), and
 // with vbar its vbar^0.
 template <class PS>
-void launch_sort(hipStream_t s, const Grid& G, int64_t np, PS& cur, PS& alt, int*& id, int*& id2,
-                 const SortScratch& b, double* vit = nullptr, double* vbar = nullptr);
+void launch_sort(hipStream_t s, const Grid& G, int r, int64_t np, PS& cur, PS& alt, int*& id,
+                 int*& id2, const SortScratch& b, double* vit = nullptr, double* vbar = nullptr);
 void launch_to_caller(hipStream_t s, int64_t np, const int* id, const double* src, double* dst);
 void launch_from_caller(hipStream_t s, int64_t np, const int* id, const double* src, double* dst);
 

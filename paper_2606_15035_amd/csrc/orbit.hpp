@@ -304,6 +304,25 @@ __device__ __forceinline__ bool for_each_piece(const double* x0, const double* d
   return false;
 }
 
+// Nodes that one axis of an orbit's stencils can touch: lo .. lo + n (unwrapped),
+// b0 = the first node of the stencil at x0.  A piece's knot interval is decided
+// against the knot positions and crossing parameters, the intervals here by the
+// rounded u0 and u1; the two differ only within rounding of a knot (at most 64
+// spacings added in FP64 over at most 256 cells: below 1e-12 of a cell), which
+// kKnotEps covers.  A displacement that is not a number gives no bound (its
+// pieces' stencils are found by clamping): callers that index by the result
+// check d == d first.
+constexpr double kKnotEps = 1e-9;
+template <int R>
+__device__ __forceinline__ void orbit_nodes(double x0, double d, double invH, int& lo, int& n,
+                                            int& b0) {
+  const double u0 = x0 * invH, u1 = (x0 + d) * invH;
+  lo = to_int_clamped(floor(fmin(u0, u1) + (Spline<R>::base_off - kKnotEps)));
+  n = to_int_clamped(floor(fmax(u0, u1) + (Spline<R>::base_off + kKnotEps))) - lo + R;
+  b0 = to_int_clamped(floor(u0 + (Spline<R>::base_off - kKnotEps))) + Spline<R>::first_off;
+  lo += Spline<R>::first_off;
+}
+
 // Base node of the stencil of the point at s (the rule over the whole orbit
 // without splitting, where every point takes the stencil of its own cell).
 template <int R>

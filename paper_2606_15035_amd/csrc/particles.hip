@@ -474,32 +474,31 @@ __global__ __launch_bounds__(kBlock) void k_extrapolate(int64_t n3, const T* __r
   if (vbar) vbar[i] = 0.5 * (w + (double)v[i]);
 }
 
-// Orbit current of a chunk of kChunk particles per block.  Lanes take
-// particles with a stride of kChunk / 64 inside the chunk, so that for
-// cell-sorted particles the 64 lanes of a wavefront sit in up to
-// kChunk / (particles per cell) different cells and their LDS atomics rarely
-// hit the same address.
-// Pass 1 finds the box of nodes the chunk's orbits touch (unwrapped indices
-// relative to the chunk's first particle, one node of margin per side);
-// pass 2 accumulates the current in an LDS tile over that box; the tile is
-// then flushed with one global atomic per non-zero node value.  A chunk whose
-// box exceeds the tile adds straight to global memory.  A 4096-particle chunk
-// spans 64 cells at 64 particles per cell, so the 64 lanes of a wavefront sit
-// in 64 different cells and their atomics never meet on one address (2048
-// particles put two lanes in every cell: scatter 0.287 -> 0.245 ms at 32^3);
-// the 3072-node tile (72 KB) still leaves room for two blocks per CU.  Where
-// the box of such a chunk does not fit (more particles per cell, longer
-// orbits: the 64^3 thermal workload) blocks count the miss and the host
-// switches to 2048-particle chunks; cubic stencils use those from the start.
-// Quadratic and linear 2048-particle chunks fit a 2048-node tile (48 KB),
-// which lets three blocks share a CU (three waves per SIMD at 168 registers:
-// 64^3 mixed scatter 5.04 -> 4.79 ms per pass); the cubic ones need 3072.
-template <int R, int CH>
-struct ScatterChunk {
-  static constexpr int kChunk = CH;
-  static constexpr int kPerThread = kChunk / kBlock;  // particles per thread
-  static constexpr int kTileNodes = (CH == 2048 && R < 3) ? 2048 : 3072;
-  static constexpr int kWavesPerSimd = (CH == 2048 && R < 3) ? 3 : 1;  // minimum asked for
+// Orbit current of P.chunk particles per block.  The lanes are spread over a
+// span of P.span >= P.chunk consecutive sorted particles (chunk_particle), so
+// that the 64 lanes of a wavefront sit in different cells and their LDS
+// additions rarely hit the same address; P.span / P.chunk blocks interleave over
+// one span.  How long both are: auto_span and auto_chunk in api.hip.
+// Pass 1 finds the box of nodes the block's orbits touch (unwrapped indices
+// relative to its first particle); where that box exceeds the tile (thermal plasmas: the fastest particle of a block
+// sets it), the box of the block's start stencils, widened by as many nodes as
+// fit, takes its place.  Pass 2 accumulates the current in an LDS tile over
+// that box; the tile is then flushed with one global atomic per non-zero node
+// value.  Pieces outside the box go straight to global memory, as does every
+// piece of a block whose start stencils alone exceed the tile (unsorted
+// particles).
+// The LDS serves the 64-bit additions of 16 neighbouring lanes at a time, one
+// per bank pair.  64 lanes one cell apart sit in a 4x4x4 block of cells (the
+// sort's order); lane l takes segment 4 (l % 16) + l / 16 of the chunk, so that
+// 16 neighbouring lanes are four cells apart in the order, and the tile's rows
+// are padded (TileStrides) so that such lanes rarely share a bank pair.
+constexpr int kScatterNodes = 3072;  // 72 KB: two blocks share a CU
+
+struct TileStrides {
+  int sy, sx;  // slots between neighbours along y and x; along z 1
+  // sy = 0 mod 16 and sx = 4 mod 16, at least dz and dy sy
+  __device__ __forceinline__ TileStrides(int dy, int dz)
+      : sy((dz + 15) & ~15), sx(dy * sy + 4) {}
 };
 
 // t / d for 0 <= t < 2^22 and d >= 1, with inv_d = 1.0f / d: (t + 1/2) / d
@@ -509,10 +508,43 @@ __device__ __forceinline__ int div_small(int t, float inv_d) {
   return (int)(((float)t + 0.5f) * inv_d);
 }
 
-template <int CH>
-__device__ __forceinline__ int64_t chunk_particle(int64_t base, int k) {
-  return base + (int64_t)(threadIdx.x % kWave) * (CH / kWave) + threadIdx.x / kWave +
-         (int64_t)(kBlock / kWave) * k;
+// first particle of scatter block blk, and particle k of this thread in it: the
+// block's lanes sit span / 64 particles apart, chunk / 64 consecutive particles
+// each; span / chunk blocks share a span
+__device__ __forceinline__ int64_t chunk_base(int chunk, int span, int blk) {
+  const int per_span = span / chunk;
+  return (int64_t)(blk / per_span) * span + (blk % per_span) * (chunk / kWave);
+}
+__device__ __forceinline__ int64_t chunk_particle(int64_t base, int span, int k) {
+  const int lane = threadIdx.x % kWave, seg = 4 * (lane % 16) + lane / 16;
+  return base + seg * (span / kWave) + (int)(threadIdx.x / kWave) + (kBlock / kWave) * k;
+}
+
+// Extra nodes per side, at most 4, by which a box of extents dim can grow and
+// still fit `nodes` slots; -1 if it does not fit as it is.
+__device__ __forceinline__ int plain_slack(const int* dim, int nodes) {
+  // each extent is bounded first so that the products cannot overflow
+  if (!(dim[0] > 0 && dim[0] <= nodes && dim[1] <= nodes && dim[2] <= nodes)) return -1;
+  int e = -1;
+  while (e < 4 && (int64_t)(dim[0] + 2 * e + 2) * (dim[1] + 2 * e + 2) * (dim[2] + 2 * e + 2) <=
+                      nodes)
+    ++e;
+  return e;
+}
+
+// The same for the scatter tile with its padded rows.
+__device__ __forceinline__ int box_slack(const int* dim) {
+  if (!(dim[0] > 0 && dim[0] <= kScatterNodes && dim[1] <= kScatterNodes &&
+        dim[2] <= kScatterNodes))
+    return -1;
+  int e = -1;
+  while (e < 4) {
+    const int g = 2 * (e + 1);
+    const TileStrides s(dim[1] + g, dim[2] + g);
+    if ((int64_t)(dim[0] + g) * s.sx > kScatterNodes) break;
+    ++e;
+  }
+  return e;
 }
 
 // x^n, vbar^p = (v^{n+1,p} + v^n) / 2 and the unwrapped displacement
@@ -563,29 +595,21 @@ __device__ __forceinline__ unsigned long long quantize(double w, double scale) {
   return (unsigned long long)(long long)rint(w * scale);
 }
 
-// MULTI: the particles carry species (one byte each); otherwise every
-// particle has the coefficients of species 0, kept in scalar registers
-template <int R, class PS, bool SPLIT, bool MULTI, int CH>
-__global__ __launch_bounds__(kBlock) __attribute__((
-    amdgpu_waves_per_eu(ScatterChunk<R, CH>::kWavesPerSimd))) void k_scatter(StepParams P, PS st,
-                                                   const double* __restrict__ vit,
-                                                   const double* __restrict__ vbar,
-                                                   CurrentOut out, Scratch sc,
-                                                   ChunkBoxes bx) {
+// The node box of a scatter block's chunk (first particle `base`): reference
+// cell sref (that of the first particle), origin tlo relative to it and extents
+// dim, per axis, block-uniform; taken from bx when an earlier pass of the step
+// stored it.  index(k), k < per_thread, are the thread's particles; slack(dim)
+// is the number of nodes by which a box can grow on every side and still fit
+// the kernel's tile, negative if it does not fit.
+template <int R, class PS, class Index, class Slack>
+__device__ __forceinline__ void scatter_box(const StepParams& P, const PS& st,
+                                            const double* __restrict__ vit,
+                                            const double* __restrict__ vbar, const ChunkBoxes& bx,
+                                            int64_t base, int per_thread,
+                                            Index&& index, Slack&& slack, int (&sref)[3],
+                                            int (&tlo)[3], int (&dim)[3]) {
   constexpr int W = R + 1;
-  constexpr bool FIX = PS::kMixed;  // int64 fixed-point deposit
-  constexpr int kTileNodes = ScatterChunk<R, CH>::kTileNodes;
-  __shared__ double tile[3 * kTileNodes];  // FIX: int64 quanta in the same bytes
   __shared__ int s_ref[3];
-  unsigned long long* tile_q = reinterpret_cast<unsigned long long*>(tile);
-  constexpr int kChunk = ScatterChunk<R, CH>::kChunk, kPerThread = ScatterChunk<R, CH>::kPerThread;
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  double js[1] = {0.0};
-  double bad = 0.0;
-  late_reduce_init<2>();
-  // the chunk's node box: reference cell sref (that of the chunk's first
-  // particle), origin tlo relative to it and extents dim, per axis
-  int sref[3], tlo[3], dim[3];
   if (bx.reuse) {  // found by this chunk in the step's first pass
     const int* b = bx.box + (int64_t)blockIdx.x * kBoxInts;
 #pragma unroll
@@ -597,7 +621,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   } else {
     if (threadIdx.x == 0) {
       double x0[3];
-      st.x_of(P.G, P.np, base, x0);
+      st.x_of(P.G, P.np, min(base, P.np - 1), x0);  // a span's last blocks may be empty
 #pragma unroll
       for (int a = 0; a < 3; ++a)
         s_ref[a] = to_int_clamped(floor(x0[a] * P.G.invH[a] + Spline<R>::base_off));
@@ -605,30 +629,48 @@ __global__ __launch_bounds__(kBlock) __attribute__((
     __syncthreads();
 #pragma unroll
     for (int a = 0; a < 3; ++a) sref[a] = s_ref[a];
-    // pass 1: the box of the nodes the chunk's orbits touch
+    // pass 1: the boxes of the nodes the chunk's orbits touch and (cmin, cmax)
+    // of those its start stencils touch
     int rmin[3] = {0x3fffffff, 0x3fffffff, 0x3fffffff};
     int rmax[3] = {-0x3fffffff, -0x3fffffff, -0x3fffffff};
-    for (int k = 0; k < kPerThread; ++k) {
-      const int64_t i = chunk_particle<CH>(base, k);
+    int cmin[3] = {0x3fffffff, 0x3fffffff, 0x3fffffff};
+    int cmax[3] = {-0x3fffffff, -0x3fffffff, -0x3fffffff};
+    for (int k = 0; k < per_thread; ++k) {
+      const int64_t i = index(k);
       if (i >= P.np) continue;
       double x0[3], d[3], vb[3];
       orbit_of(P, st, vit, vbar, i, x0, d, vb);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        const double u0 = x0[a] * P.G.invH[a], u1 = (x0[a] + d[a]) * P.G.invH[a];
-        const int lo = to_int_clamped(floor(fmin(u0, u1) + Spline<R>::base_off)) + Spline<R>::first_off - 1;
-        const int hi = to_int_clamped(floor(fmax(u0, u1) + Spline<R>::base_off)) + Spline<R>::first_off + W;
+        int lo, n, b0;
+        orbit_nodes<R>(x0[a], d[a], P.G.invH[a], lo, n, b0);
         const int rel = min_image(lo - sref[a], P.G.n[a]);
         rmin[a] = min(rmin[a], rel);
-        rmax[a] = max(rmax[a], rel + (hi - lo));
+        rmax[a] = max(rmax[a], rel + n);
+        cmin[a] = min(cmin[a], rel + (b0 - lo));
+        cmax[a] = max(cmax[a], rel + (b0 - lo) + W);
       }
     }
-    int mv[6] = {rmin[0], rmin[1], rmin[2], -rmax[0], -rmax[1], -rmax[2]};
-    block_min_ints<6>(mv);
+    int mv[12] = {rmin[0], rmin[1], rmin[2], -rmax[0], -rmax[1], -rmax[2],
+                  cmin[0], cmin[1], cmin[2], -cmax[0], -cmax[1], -cmax[2]};
+    block_min_ints<12>(mv);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       tlo[a] = mv[a];
       dim[a] = -mv[3 + a] - tlo[a] + 1;
+    }
+    if (slack(dim) < 0) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        tlo[a] = mv[6 + a];
+        dim[a] = -mv[9 + a] - tlo[a] + 1;
+      }
+      const int e = max(slack(dim), 0);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        tlo[a] -= e;
+        dim[a] += 2 * e;
+      }
     }
     if (bx.box && threadIdx.x == 0) {
       int* b = bx.box + (int64_t)blockIdx.x * kBoxInts;
@@ -646,11 +688,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((
     tlo[a] = __builtin_amdgcn_readfirstlane(tlo[a]);
     dim[a] = __builtin_amdgcn_readfirstlane(dim[a]);
   }
-  // block-uniform; each extent is bounded first so that the product cannot overflow
-  const bool use_tile = dim[0] > 0 && dim[0] <= kTileNodes && dim[1] <= kTileNodes &&
-                        dim[2] <= kTileNodes && (int64_t)dim[0] * dim[1] * dim[2] <= kTileNodes;
-  const int nt = use_tile ? dim[0] * dim[1] * dim[2] : 0;
-  if (!use_tile && threadIdx.x == 0) unsafeAtomicAdd(sc.spread_copy(S_SMISS), 1.0);
+}
+
+// MULTI: the particles carry species (one byte each); otherwise every
+// particle has the coefficients of species 0, kept in scalar registers
+template <int R, class PS, bool SPLIT, bool MULTI>
+__global__ __launch_bounds__(kBlock) __attribute__((
+    amdgpu_waves_per_eu(2))) void k_scatter(StepParams P, PS st,
+                                                   const double* __restrict__ vit,
+                                                   const double* __restrict__ vbar,
+                                                   CurrentOut out, Scratch sc,
+                                                   ChunkBoxes bx) {
+  constexpr int W = R + 1;
+  constexpr bool FIX = PS::kMixed;  // int64 fixed-point deposit
+  __shared__ double tile[3 * kScatterNodes];  // FIX: int64 quanta in the same bytes
+  unsigned long long* tile_q = reinterpret_cast<unsigned long long*>(tile);
+  const int per_thread = P.chunk / kBlock;  // at most 16
+  const int64_t base = chunk_base(P.chunk, P.span, blockIdx.x);
+  double js[1] = {0.0};
+  double bad = 0.0;
+  late_reduce_init<2>();
+  int sref[3], tlo[3], dim[3];
+  scatter_box<R>(P, st, vit, vbar, bx, base, per_thread,
+                 [&](int k) { return chunk_particle(base, P.span, k); },
+                 [](const int* d) { return box_slack(d); }, sref, tlo, dim);
+  const bool use_tile = box_slack(dim) >= 0;  // block-uniform
+  const TileStrides ts(dim[1], dim[2]);
+  const int nt = use_tile ? dim[0] * ts.sx : 0;
   for (int t = threadIdx.x; t < 3 * nt; t += kBlock) tile[t] = 0.0;  // also integer zero
   __syncthreads();
   // pass 2: accumulate.  Pieces whose stencil lies outside the tile are
@@ -662,7 +726,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   auto process = [&](int k, auto global_phase) -> bool {
     constexpr bool GLOBAL = decltype(global_phase)::value;
     bool outside = false;
-    const int64_t i = chunk_particle<CH>(base, k);
+    const int64_t i = chunk_particle(base, P.span, k);
     if (i >= P.np) return false;
     double x0[3], d[3], vb[3], c3[3];
     orbit_of(P, st, vit, vbar, i, x0, d, vb);
@@ -676,8 +740,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       c3[a] = cq * vb[a];
-      const double u0 = x0[a] * P.G.invH[a], u1 = (x0[a] + d[a]) * P.G.invH[a];
-      const int lo = to_int_clamped(floor(fmin(u0, u1) + Spline<R>::base_off)) + Spline<R>::first_off - 1;
+      int lo, n, b0;
+      orbit_nodes<R>(x0[a], d[a], P.G.invH[a], lo, n, b0);
       const int raw = lo - sref[a];
       shift[a] = min_image(raw, P.G.n[a]) - raw;  // particle frame -> chunk frame
     }
@@ -695,7 +759,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
           for (int b = 0; b < W; ++b)
 #pragma unroll
             for (int c = 0; c < W; ++c) {
-              const int t = ((ox + a) * dim[1] + (oy + b)) * dim[2] + (oz + c);
+              const int t = (ox + a) * ts.sx + (oy + b) * ts.sy + (oz + c);
               const double w = Iw[a][b][c];
 #pragma unroll
               for (int l = 0; l < 3; ++l) {
@@ -752,7 +816,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
 #pragma unroll
             for (int q = 0; q < NQ; ++q) w += xy[q] * Z[q][c];
             if (!GLOBAL) {
-              const int t = ((ox + a) * dim[1] + (oy + b)) * dim[2] + (oz + c);
+              const int t = (ox + a) * ts.sx + (oy + b) * ts.sy + (oz + c);
 #pragma unroll
               for (int l = 0; l < 3; ++l) {
                 if constexpr (FIX)
@@ -796,8 +860,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
     } else if constexpr (SPLIT) {
       // One x slice of the stencil at a time: the point sums of its 3 x 3 nodes
       // are deposited before the next slice's are formed, so only 9 weights
-      // are live (the same sums, in the same order, as the whole stencil's;
-      // 161 instead of 179 registers, no spills in the 2048-particle form).
+      // are live (the same sums, in the same order, as the whole stencil's).
       ok = for_each_piece<R>(x0, d, P.G, [&](double s0, double s1, const double* base) {
         constexpr int NQ = Quad<R>::NQ;
         double sq[NQ], wq[NQ], tx[NQ], Y[NQ][W], Z[NQ][W];
@@ -843,7 +906,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
             for (int c = 0; c < W; ++c) {
               const double w = Ia[b][c];
               if (!GLOBAL) {
-                const int t = ((ox + a) * dim[1] + (oy + b)) * dim[2] + (oz + c);
+                const int t = (ox + a) * ts.sx + (oy + b) * ts.sy + (oz + c);
 #pragma unroll
                 for (int l = 0; l < 3; ++l) {
                   if constexpr (FIX)
@@ -880,15 +943,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((
     }
     return outside;
   };
-  for (int k = 0; k < kPerThread; ++k)
+  for (int k = 0; k < per_thread; ++k)
     if (process(k, std::false_type{})) outside_mask |= 1u << k;
-  for (int k = 0; k < kPerThread; ++k)
+  for (int k = 0; k < per_thread; ++k)
     if ((outside_mask >> k) & 1u) process(k, std::true_type{});
   __syncthreads();
-  const float inv_d1 = 1.0f / (float)max(dim[1], 1), inv_d2 = 1.0f / (float)max(dim[2], 1);
+  // padding slots stay zero
+  const float inv_sx = 1.0f / (float)ts.sx, inv_sy = 1.0f / (float)ts.sy;
   for (int t = threadIdx.x; t < nt; t += kBlock) {
-    const int q = div_small(t, inv_d2), cx = div_small(q, inv_d1);
-    const int cz = t - q * dim[2], cy = q - cx * dim[1];
+    const int cx = div_small(t, inv_sx), yz = t - cx * ts.sx;
+    const int cy = div_small(yz, inv_sy), cz = yz - cy * ts.sy;
     const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
                                  sref[2] + tlo[2] + cz);
 #pragma unroll
@@ -911,15 +975,248 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   }
 }
 
+// The FP64 current of dense plasmas by matrix instructions (degree 2; when it is
+// taken: use_scatter_mm in api.hip).  In the kernel
+// above every orbit piece takes 3 (r+1)^3 LDS additions per lane, and those
+// bound it.  Consecutive sorted particles share their stencils (the sort's
+// key is the base node of the first piece), and for particles of one stencil
+// the current is a product,
+//   J[node][l] += sum_i Sbar[node][i] c[i][l],   c = q vbar / dV,
+// summed over the particles.  A wavefront therefore takes 64 consecutive
+// particles at a time, forms the weights of one piece of each, groups the
+// lanes by stencil, and hands the weights through LDS to
+// v_mfma_f64_4x4x4: its four blocks are 16 stencil nodes, its K four particles
+// of one group, its columns the three current components (the fourth is not
+// used).  The products of a group stay in one register pair per lane and go to
+// the block's LDS tile with one addition per node and component.  One x slice
+// of the stencil ((r+1)^2 <= 16 nodes) is handled at a time.
+// Pieces outside the tile go to global memory particle by particle, after the
+// main loop.
+constexpr int kMmNodes = 1024;              // 24 KB tile
+constexpr int kMmStride = kWave + 1;        // slots of a row of the weight buffer: odd, so
+                                            // 16 rows read at one slot use 16 bank pairs
+// slots of a wavefront's weight buffer: (r+1)^2 rows of weights, 3 of current
+// components; the last reads of a group may reach 15 slots past the last row
+template <int R>
+constexpr int kMmBuf = ((R + 1) * (R + 1) + 3) * kMmStride + 16;
+
+template <int R, bool MULTI>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scatter_mm(
+    StepParams P, Fp64Store st, const double* __restrict__ vit, const double* __restrict__ vbar,
+    double* __restrict__ J, Scratch sc, ChunkBoxes bx) {
+  constexpr int W = R + 1, NQ = Quad<R>::NQ, kRows = W * W;
+  __shared__ double tile[3 * kMmNodes];
+  __shared__ double wbuf[kBlock / kWave][kMmBuf<R>];
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+  const int run = P.chunk / (kBlock / kWave);  // consecutive particles per wavefront
+  const int64_t base = (int64_t)blockIdx.x * P.chunk;
+  double js[1] = {0.0};
+  double bad = 0.0;
+  late_reduce_init<2>();
+  int sref[3], tlo[3], dim[3];
+  scatter_box<R>(P, st, vit, vbar, bx, base, P.chunk / kBlock,
+                 [&](int k) { return base + wid * run + k * kWave + lane; },
+                 [](const int* d) { return plain_slack(d, kMmNodes); }, sref, tlo, dim);
+  const bool use_tile = plain_slack(dim, kMmNodes) >= 0;  // block-uniform
+  const int sy = dim[2], sx = dim[1] * dim[2], nt = use_tile ? dim[0] * sx : 0;
+  for (int t = threadIdx.x; t < 3 * nt; t += kBlock) tile[t] = 0.0;
+  double* wb = wbuf[wid];
+  for (int t = lane; t < kMmBuf<R>; t += kWave) wb[t] = 0.0;
+  __syncthreads();
+  // operand positions of this lane: A row = lane % 16, B column = lane % 4,
+  // K index = lane / 16; result row 4 ((lane / 4) % 4) + lane / 16, column lane % 4
+  const int kk = lane >> 4, col = lane & 3;
+  const double* wa = wb + min(lane & 15, kRows - 1) * kMmStride + kk;
+  const double* wc = wb + (kRows + min(col, 2)) * kMmStride + kk;
+  const int row = 4 * ((lane >> 2) & 3) + kk;
+  const bool out_lane = row < kRows && col < 3;
+  double* tout = tile + 3 * ((row / W) * sy + row % W) + col;
+  unsigned outside_mask = 0u;
+  for (int it = 0; it * kWave < run; ++it) {
+    const int64_t i = base + wid * run + it * kWave + lane;
+    bool live = i < P.np;
+    if (__ballot(live) == 0ull) break;
+    double x0[3] = {0.0, 0.0, 0.0}, d[3] = {0.0, 0.0, 0.0}, c3[3] = {0.0, 0.0, 0.0};
+    int off[3];  // particle frame -> tile
+    if (live) {
+      double vb[3];
+      orbit_of(P, st, vit, vbar, i, x0, d, vb);
+      const double vmax = fmax(fabs(vb[0]), fmax(fabs(vb[1]), fabs(vb[2])));
+      const int sp = MULTI ? st.species(i) : 0;
+      js[0] += (MULTI ? species_value(P.aq, sp) : P.aq[0]) * vmax;
+      const double cq = MULTI ? species_value(P.cq, sp) : P.cq[0];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) c3[a] = cq * vb[a];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      int lo, n, b0;
+      orbit_nodes<R>(x0[a], d[a], P.G.invH[a], lo, n, b0);
+      const int raw = lo - sref[a];
+      off[a] = min_image(raw, P.G.n[a]) - raw - sref[a] - tlo[a] + Spline<R>::first_off;
+    }
+    Crossings<R> cr;
+    cr.init(x0, d, P.G);
+    double s0 = 0.0;
+    bool outside = false;
+    for (int piece = 0; piece < kMaxPieces; ++piece) {
+      if (__ballot(live) == 0ull) break;
+      const double s1 = cr.next();
+      const int ox = cr.base[0] + off[0], oy = cr.base[1] + off[1], oz = cr.base[2] + off[2];
+      const bool inside = use_tile && ox >= 0 && oy >= 0 && oz >= 0 && ox + W <= dim[0] &&
+                          oy + W <= dim[1] && oz + W <= dim[2];
+      const bool has = live && s1 > s0;
+      outside = outside || (has && !inside);
+      const bool dep = has && inside;
+      const int t0 = ox * sx + oy * sy + oz;
+      // groups of lanes with one stencil, in consecutive slots; lane g keeps
+      // group g's stencil, first slot and size
+      unsigned long long todo = __ballot(dep);
+      int ngroups = 0, filled = 0, slot = 0, gt = 0, gp = 0, gn = 0;
+      while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const int tl = __builtin_amdgcn_readlane(t0, leader);
+        const unsigned long long grp = __ballot(t0 == tl) & todo;
+        const int n = __popcll(grp);
+        if ((grp >> lane) & 1ull)
+          slot = filled + __builtin_amdgcn_mbcnt_hi((unsigned)(grp >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((unsigned)grp, 0u));
+        if (lane == ngroups) {
+          gt = tl;
+          gp = filled;
+          gn = n;
+        }
+        ++ngroups;
+        filled += n;
+        todo &= ~grp;
+      }
+      if (ngroups > 0) {
+        double sq[NQ], wq[NQ], tx[NQ], Y[NQ][W], Z[NQ][W];
+        piece_rule<R>(s0, s1, sq, wq);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          tx[q] = (x0[0] + sq[q] * d[0]) * P.G.invH[0] - (double)cr.base[0];
+          Spline<R>::w((x0[1] + sq[q] * d[1]) * P.G.invH[1] - (double)cr.base[1], Y[q]);
+          Spline<R>::w((x0[2] + sq[q] * d[2]) * P.G.invH[2] - (double)cr.base[2], Z[q]);
+        }
+        if (dep)
+#pragma unroll
+          for (int l = 0; l < 3; ++l) wb[(kRows + l) * kMmStride + slot] = c3[l];
+#pragma unroll
+        for (int a = 0; a < W; ++a) {
+          double Ia[W][W];
+#pragma unroll
+          for (int b = 0; b < W; ++b)
+#pragma unroll
+            for (int c = 0; c < W; ++c) Ia[b][c] = 0.0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            double Xq, dXq;
+            Spline<R>::wk(a, tx[q], Xq, dXq);
+            const double xa = wq[q] * Xq;
+#pragma unroll
+            for (int b = 0; b < W; ++b) {
+              const double xy = xa * Y[q][b];
+#pragma unroll
+              for (int c = 0; c < W; ++c) Ia[b][c] += xy * Z[q][c];
+            }
+          }
+          // a wavefront's LDS operations complete in order: the fences only
+          // keep the compiler from moving them across each other
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          if (dep)
+#pragma unroll
+            for (int b = 0; b < W; ++b)
+#pragma unroll
+              for (int c = 0; c < W; ++c) wb[(b * W + c) * kMmStride + slot] = Ia[b][c];
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          for (int g = 0; g < ngroups; ++g) {
+            const int tg = __builtin_amdgcn_readlane(gt, g);
+            const int p = __builtin_amdgcn_readlane(gp, g), n = __builtin_amdgcn_readlane(gn, g);
+            double acc = 0.0;
+            for (int j = 0; j < n; j += 8) {  // two products, their operands read together
+              double A[2], B[2];
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                A[u] = wa[p + j + 4 * u];
+                const double cv = wc[p + j + 4 * u];
+                B[u] = j + 4 * u + kk < n ? cv : 0.0;
+              }
+#pragma unroll
+              for (int u = 0; u < 2; ++u)
+                acc = __builtin_amdgcn_mfma_f64_4x4x4f64(A[u], B[u], acc, 0, 0, 0);
+            }
+            if (out_lane) atomicAdd(tout + 3 * (tg + a * sx), acc);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+      if (s1 >= 1.0) live = false;
+      cr.consume(s1);
+      s0 = s1;
+    }
+    if (live) bad = 1.0;  // more than kMaxPieces pieces
+    if (outside) outside_mask |= 1u << it;
+  }
+  for (int it = 0; it * kWave < run; ++it) {
+    if (!((outside_mask >> it) & 1u)) continue;
+    const int64_t i = base + wid * run + it * kWave + lane;
+    double x0[3], d[3], vb[3], c3[3];
+    orbit_of(P, st, vit, vbar, i, x0, d, vb);
+    const double cq = MULTI ? species_value(P.cq, st.species(i)) : P.cq[0];
+    int off[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      c3[a] = cq * vb[a];
+      int lo, n, b0;
+      orbit_nodes<R>(x0[a], d[a], P.G.invH[a], lo, n, b0);
+      const int raw = lo - sref[a];
+      off[a] = min_image(raw, P.G.n[a]) - raw - sref[a] - tlo[a] + Spline<R>::first_off;
+    }
+    for_each_piece<R>(x0, d, P.G, [&](double s0, double s1, const double* bs) {
+      const int ox = (int)bs[0] + off[0], oy = (int)bs[1] + off[1], oz = (int)bs[2] + off[2];
+      const bool inside = use_tile && ox >= 0 && oy >= 0 && oz >= 0 && ox + W <= dim[0] &&
+                          oy + W <= dim[1] && oz + W <= dim[2];
+      if (!inside) scatter_piece<R>(P.G, x0, d, s0, s1, bs, c3, J);
+    });
+  }
+  __syncthreads();
+  const int64_t nc = P.G.ncell;
+  const float inv_sx = 1.0f / (float)max(sx, 1), inv_sy = 1.0f / (float)max(sy, 1);
+  for (int t = threadIdx.x; t < nt; t += kBlock) {
+    const int cx = div_small(t, inv_sx), yz = t - cx * sx;
+    const int cy = div_small(yz, inv_sy), cz = yz - cy * sy;
+    const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
+                                 sref[2] + tlo[2] + cz);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      const double val = tile[3 * t + l];
+      if (val != 0.0) unsafeAtomicAdd(J + l * nc + g, val);
+    }
+  }
+  const double part[2] = {js[0], bad};
+  const bool ismax[2] = {false, true};
+  double blk[2];
+  if (late_reduce<2>(part, ismax, blk)) {
+    sc.region(P_JS)[blockIdx.x] = blk[0];  // J_s partials, summed in order by k_finish
+    atomic_max_nonneg(sc.spread_copy(S_BAD), blk[1]);
+  }
+}
+
 // Gather + push of one particle (index i of store st) through accessor acc:
 // grad phi-bar and (D A)^T vbar over the orbit pieces, then P^{n+1,p} and
-// v^{n+1,p+1}.  v^n is read again after the orbit loop rather than kept in
-// registers through it (the loop sets the kernel's register count).
+// v^{n+1,p+1}.  The orbit loop sets the kernel's register count, so nothing that
+// can be had again is kept through it: v^n and the species are read after it,
+// and x0, d and i are hidden from the compiler there, which would otherwise
+// carry cell coordinates and addresses formed before the loop to their uses
+// behind it (28 spilled registers, 0.35 against 0.28 ms per pass at 32^3).
 template <int R, bool SPLIT, class Acc, class PS>
 __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& acc, const PS& st,
-                                                int64_t i, const double* x0, const double* d,
-                                                const double* vb, double qi, double mi,
-                                                double* vn, double& npieces, double& bad) {
+                                                int& i, double (&x0)[3], double (&d)[3],
+                                                const double (&vb)[3], double* vn, double& npieces,
+                                                double& bad) {
   double gp[3] = {0.0, 0.0, 0.0};
   double dtv[3] = {0.0, 0.0, 0.0};  // H_j ((D A)^T vbar)_j until the pieces are summed
   if constexpr (SPLIT) {
@@ -936,10 +1233,15 @@ __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& 
     }
     npieces += 1.0;
   }
+  asm volatile(""
+               : "+v"(i), "+v"(x0[0]), "+v"(x0[1]), "+v"(x0[2]), "+v"(d[0]), "+v"(d[1]), "+v"(d[2])
+               :
+               : "memory");
   // A_h^n(x^n) rebuilds P^n = m v^n + q A_h^n(x^n) (eq. discrete-canonical-relation);
   // A_h^{n+1}(x^{n+1}) at the wrapped end point closes the velocity (eq. orbit-v-update).
+  const int spc = st.species(i);
+  const double qi = species_value(P.qs, spc), mi = species_value(P.ms, spc);
   double va[3];
-  asm volatile("" ::: "memory");  // a fresh load, not the value from before the loop
   st.v_of(P.np, i, va);
   double x1[3], A0s[3], A1e[3];
   int zero[3] = {0, 0, 0}, sh1[3];
@@ -959,264 +1261,326 @@ __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& 
   }
 }
 
-// One block = 256 cell-sorted particles.  TILED = true: the block finds the
-// box of nodes its orbits touch from the rounded u0 and u1 of each orbit, with
-// one node of margin per side (a piece's knot interval, decided against the
-// knot positions, differs from the interval of a rounded end point only
-// within rounding of a knot, and then by one), copies the gather fields of
-// that box into LDS, and
-// every stencil read of the node loop then comes from LDS; a block whose box
-// does not fit the tile appends its index to a work list (work[0] = count,
-// work[1..] = block indices).  After the first Picard pass of a step the
-// block takes the box it stored in an earlier pass and starts copying at
-// once; if one of its orbits has moved out of that box (by the margin test
-// above) it finds and stores the box again, and copies again.  TILED = false: the blocks on that list (all
-// blocks when work is null) read the gather buffer in global memory, a small
-// grid looping over the list.  Two kernels keep each one's register budget.
-constexpr int kGatherTileNodes = 512;
-constexpr int kGatherListGrid = 512;  // blocks of the global-memory kernel with a list
+// Where a gather block reads the fields from.
+//   GATHER_TILE  the block's LDS copy of the nodes its orbits touch
+//   GATHER_MESH  an LDS copy of the whole mesh (meshes of at most
+//                kGatherTileNodes nodes): no box to find, none to miss
+//   GATHER_LIST  global memory, for the particles that GATHER_TILE listed
+enum GatherFrom { GATHER_TILE, GATHER_MESH, GATHER_LIST };
 
-// Block bid of 256 particles; thread 0 must have run late_reduce_init<4>()
-// and late_reduce_init<2>() before a barrier that precedes the call.
-template <int R, bool TILED, class PS, bool SPLIT>
-__device__ __forceinline__ void gather_block(const StepParams& P, const PS& st,
-                                             const double* __restrict__ vit,
-                                             double* __restrict__ vnew,
-                                             double* __restrict__ vbar_out, const AosFields& F,
-                                             int* __restrict__ work, const Scratch& sc,
-                                             const AndersonPrev& prev, int bid,
-                                             const ChunkBoxes& bx) {
-  constexpr int W = R + 1;
-  const int64_t i = (int64_t)bid * kBlock + threadIdx.x;
-  const bool active = i < P.np;
-  double dvm = 0.0, vm = 0.0, bad = 0.0;
-  double npieces[1] = {0.0};
-  double x0[3] = {0.0, 0.0, 0.0}, va[3] = {0.0, 0.0, 0.0}, vi[3] = {0.0, 0.0, 0.0};
-  double vb[3] = {0.0, 0.0, 0.0}, d[3] = {0.0, 0.0, 0.0};
-  double qi = P.q, mi = P.m;
-  if (active) {
-    const int spc = st.species(i);
-    qi = species_value(P.qs, spc);
-    mi = species_value(P.ms, spc);
-    st.x_of(P.G, P.np, i, x0);
-    st.v_of(P.np, i, va);
-    load3(vit, P.np, i, vi);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      vb[a] = 0.5 * (vi[a] + va[a]);
-      d[a] = P.dt * vb[a];
-    }
+// 78 KB of LDS: two blocks share a CU, as their registers would have it anyway
+constexpr int kGatherTileNodes = 1000;
+
+struct MeshGather {  // the whole mesh in LDS, nodes in flat order
+  lds_cdouble* t;
+  int mask0, mask1, mask2, shx, shy;
+  __device__ __forceinline__ int row(int ix, int iy) const {
+    return ((ix & mask0) << shx) | ((iy & mask1) << shy);
   }
-  double vn[3] = {0.0, 0.0, 0.0};
-  if constexpr (TILED) {
-    __shared__ double2 tile2[kGatherTileNodes * kGbufStride / 2];
-    __shared__ int s_ref[3];
-    __shared__ int s_out[kBlock / kWave];
-    int lo[3] = {0, 0, 0}, span[3] = {0, 0, 0};
-    if (active) {
+  __device__ __forceinline__ lds_cdouble* node(int row, int iz) const {
+    return t + (row | (iz & mask2)) * kGbufStride;
+  }
+};
+
+// Maxima, counts and sums of a block's particles, taken wavefront by wavefront
+// as they finish (no block barrier after the orbit loops: a wavefront with fewer
+// pieces does not wait for the block's slowest one), so that they hold no
+// registers through the orbit loops.
+struct GatherTotals {
+  unsigned long long dvm, vm, bad;  // bit patterns of non-negative doubles
+  int pieces;
+  double aa[kBlock / kWave][2];  // one row per wavefront
+  unsigned int done;
+};
+
+// The gather and push of one batch of 256 particles; i = particle, or active
+// false.  With inside(x0, d) false the lane's particle is left to the list.
+template <int R, bool SPLIT, class PS, class Acc, class Inside>
+__device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, int i,
+                                             bool active, const double* __restrict__ vit,
+                                             double* __restrict__ vnew,
+                                             double* __restrict__ vbar_out, Acc&& make_acc,
+                                             Inside&& inside, const AndersonPrev& prev,
+                                             GatherTotals& tot) {
+  double dvm = 0.0, vm = 0.0, bad = 0.0, npieces = 0.0;
+  double aa[2] = {0.0, 0.0};
+  if (active) {
+    double x0[3], vb[3], d[3];
+    {
+      double va[3], vi[3];
+      st.x_of(P.G, P.np, i, x0);
+      st.v_of(P.np, i, va);
+      load3(vit, P.np, i, vi);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        const double u0 = x0[a] * P.G.invH[a], u1 = (x0[a] + d[a]) * P.G.invH[a];
-        lo[a] = to_int_clamped(floor(fmin(u0, u1) + Spline<R>::base_off)) + Spline<R>::first_off - 1;
-        span[a] = to_int_clamped(floor(fmax(u0, u1) + Spline<R>::base_off)) +
-                  Spline<R>::first_off + W - lo[a];
+        vb[a] = 0.5 * (vi[a] + va[a]);
+        d[a] = P.dt * vb[a];
       }
     }
-    // the block's node box: reference node sref, origin tlo relative to it and
-    // extents dim, per axis (dim[0] < 0: the box overflows the tile)
-    int sref[3], shift[3], tlo[3], dim[3];
-    auto uniform = [&]() {
+    int shift[3];
+    if (inside(i, x0, d, shift)) {
+      double vn[3];
+      gather_push_one<R, SPLIT>(P, make_acc(shift), st, i, x0, d, vb, vn, npieces, bad);
+      // vn is complete here: otherwise its y and z sums sink behind the branches
+      // below and every field value they use stays in registers until then
+      // (more than 200 spilled)
+      asm volatile("" : "+v"(vn[0]), "+v"(vn[1]), "+v"(vn[2]), "+v"(i) : : "memory");
+      double va[3], vi[3];
+      st.v_of(P.np, i, va);
+      load3(vit, P.np, i, vi);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
+      for (int j = 0; j < 3; ++j) {
+        vnew[j * P.np + i] = vn[j];
+        if (vbar_out) vbar_out[j * P.np + i] = 0.5 * (vn[j] + va[j]);  // the next pass's vbar
+        dvm = fmax(dvm, fabs(vn[j] - vi[j]));
+        vm = fmax(vm, fabs(vn[j]));
+        if (!isfinite(vn[j])) bad = 2.0;  // max-reductions drop NaN: flag it explicitly
+      }
+      if (prev.w) {  // Anderson mixing over one difference: dF . dF and dF . f_p
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const int64_t e = j * P.np + i;
+          const double f0 = vn[j] - vi[j], df = f0 - (prev.g[e] - prev.w[e]);
+          aa[0] += df * df;
+          aa[1] += df * f0;
+        }
+      }
+    }
+  }
+  dvm = wave_max(dvm);
+  vm = wave_max(vm);
+  bad = wave_max(bad);
+  npieces = wave_sum(npieces);
+  if (threadIdx.x % kWave == 0) {
+    atomicMax(&tot.dvm, (unsigned long long)__double_as_longlong(dvm));
+    atomicMax(&tot.vm, (unsigned long long)__double_as_longlong(vm));
+    if (bad > 0.0) atomicMax(&tot.bad, (unsigned long long)__double_as_longlong(bad));
+    atomicAdd(&tot.pieces, (int)npieces);
+  }
+  if (prev.w) {
+    aa[0] = wave_sum(aa[0]);
+    aa[1] = wave_sum(aa[1]);
+    if (threadIdx.x % kWave == 0)
+      for (int k = 0; k < 2; ++k) tot.aa[threadIdx.x / kWave][k] += aa[k];
+  }
+}
+
+__device__ __forceinline__ void totals_init(GatherTotals& tot) {
+  if (threadIdx.x == 0) {
+    tot.dvm = tot.vm = tot.bad = 0ull;
+    tot.pieces = 0;
+    tot.done = 0u;
+    for (int w = 0; w < kBlock / kWave; ++w) tot.aa[w][0] = tot.aa[w][1] = 0.0;
+  }
+}
+
+// by every wavefront when it has finished; the last one of the block folds the
+// block's totals into the global slots.  aa_row of aa_rows: the block's row of
+// the Anderson sums.
+__device__ __forceinline__ void totals_finish(GatherTotals& tot, const Scratch& sc, bool anderson,
+                                              int aa_row, int aa_rows) {
+  if (threadIdx.x % kWave != 0) return;
+  __threadfence_block();  // the wavefront's totals before its arrival
+  if (atomicAdd(&tot.done, 1u) != kBlock / kWave - 1) return;
+  __threadfence_block();
+  atomic_max_nonneg(sc.spread_copy(S_DVMAX), __longlong_as_double((long long)tot.dvm));
+  atomic_max_nonneg(sc.spread_copy(S_VMAX), __longlong_as_double((long long)tot.vm));
+  atomic_max_nonneg(sc.spread_copy(S_BAD), __longlong_as_double((long long)tot.bad));
+  // integer counts: the atomic sum is exact and order-free
+  if (tot.pieces > 0) unsafeAtomicAdd(sc.spread_copy(S_PIECES), (double)tot.pieces);
+  if (anderson)
+    for (int k = 0; k < 2; ++k) {
+      double a = tot.aa[0][k];
+      for (int w = 1; w < kBlock / kWave; ++w) a += tot.aa[w][k];
+      sc.region(P_AA)[k * aa_rows + aa_row] = a;
+    }
+}
+
+// Two waves per SIMD for the quadratic gather: its orbit loop fits 256
+// registers, and asking for the occupancy makes the compiler keep it (it would
+// otherwise go to one wave and twice the registers for a few more values).
+template <int R>
+constexpr int kGatherWavesPerSimd = R == 2 ? 2 : 1;
+
+// One block = P.gper batches of 256 consecutive cell-sorted particles.
+// GATHER_TILE: the block finds the box of nodes its orbits touch; where that box exceeds the tile it takes the box of its start stencils,
+// widened by as many nodes as fit.  It copies the gather fields of the box into
+// LDS, and every stencil read of the orbit loop then comes from LDS; particles
+// whose orbit leaves the box go to a list (work[0] = count,
+// work[1..] = particles), all of them if not even the start stencils fit.  The
+// list is a second kernel (GATHER_LIST), so each keeps its own register budget.
+// After the first Picard pass of a step the block takes the box it stored in
+// that pass.
+template <int R, int FROM, class PS, bool SPLIT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+    kGatherWavesPerSimd<R>))) void k_gather_push(StepParams P, PS st,
+                                                 const double* __restrict__ vit,
+                                                 double* __restrict__ vnew,
+                                                 double* __restrict__ vbar_out, AosFields F,
+                                                 int* __restrict__ work, Scratch sc,
+                                                 AndersonPrev prev, ChunkBoxes bx, int aa_row0,
+                                                 int aa_rows) {
+  constexpr int W = R + 1;
+  __shared__ GatherTotals tot;
+  totals_init(tot);
+  const int bid = blockIdx.x;
+  if constexpr (FROM == GATHER_LIST) {
+    __syncthreads();
+    const int count = work[0];  // written by the tiled kernel (previous launch)
+    // entry j to block j % grid: few lanes per wavefront.  Every lane reads nodes
+    // of its own, 5 cache lines each, and one CU's line rate bounds a wavefront
+    // (300,007 particles at 9 per cell: 70 us per pass with 64 lanes at a time)
+    for (int t = 0; t * gridDim.x + bid < count; t += kBlock) {
+      const int j = (t + (int)threadIdx.x) * (int)gridDim.x + bid;
+      const bool active = j < count;
+      gather_batch<R, SPLIT>(
+          P, st, active ? work[1 + j] : 0, active, vit, vnew, vbar_out,
+          [&](const int*) {
+            return GlobalGather{F.g, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
+          },
+          [](int, const double*, const double*, int*) { return true; }, prev, tot);
+    }
+    totals_finish(tot, sc, prev.w != nullptr, aa_row0 + bid, aa_rows);
+  } else {
+    __shared__ double2 tile2[kGatherTileNodes * kGbufStride / 2];
+    lds_cdouble* tile = (lds_cdouble*)(reinterpret_cast<double*>(tile2));
+    const double2* g2 = reinterpret_cast<const double2*>(F.g);
+    const int64_t first = (int64_t)bid * P.gper * kBlock;
+    if constexpr (FROM == GATHER_MESH) {
+      const int n2 = (int)P.G.ncell * (kGbufStride / 2);
+      for (int t = threadIdx.x; t < n2; t += kBlock) tile2[t] = g2[t];
+      __syncthreads();
+      for (int k = 0; k < P.gper; ++k) {
+        const int64_t i = first + k * kBlock + threadIdx.x;
+        gather_batch<R, SPLIT>(
+            P, st, (int)i, i < P.np, vit, vnew, vbar_out,
+            [&](const int*) {
+              return MeshGather{tile, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
+            },
+            [](int, const double*, const double*, int*) { return true; }, prev, tot);
+      }
+    } else {
+      // the block's node box: reference node sref, origin tlo relative to it and
+      // extents dim, per axis (dim[0] < 0: not even the start stencils fit)
+      int sref[3], tlo[3], dim[3];
+      if (bx.reuse) {  // the box this block found in the step's first pass
+        const int* b = bx.box + (int64_t)bid * kBoxInts;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          sref[a] = b[a];
+          tlo[a] = b[3 + a];
+          dim[a] = b[6 + a];
+        }
+      } else {
+        __shared__ int s_ref[3];
+        if (threadIdx.x == 0) {
+          double x0[3];
+          st.x_of(P.G, P.np, first, x0);
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            s_ref[a] = to_int_clamped(floor(x0[a] * P.G.invH[a] + Spline<R>::base_off));
+        }
+        __syncthreads();
+        int mv[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) mv[k] = 0x3fffffff;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sref[a] = s_ref[a];
+        for (int k = 0; k < P.gper; ++k) {
+          const int64_t i = first + k * kBlock + threadIdx.x;
+          if (i >= P.np) break;
+          double x0[3], va[3], vi[3];
+          st.x_of(P.G, P.np, i, x0);
+          st.v_of(P.np, i, va);
+          load3(vit, P.np, i, vi);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            const double d = P.dt * (0.5 * (vi[a] + va[a]));
+            int lo, n, b0;
+            orbit_nodes<R>(x0[a], d, P.G.invH[a], lo, n, b0);
+            const int rel = min_image(lo - sref[a], P.G.n[a]);
+            mv[a] = min(mv[a], rel);
+            mv[3 + a] = min(mv[3 + a], -(rel + n));
+            mv[6 + a] = min(mv[6 + a], rel + (b0 - lo));
+            mv[9 + a] = min(mv[9 + a], -(rel + (b0 - lo) + W));
+          }
+        }
+        block_min_ints<12>(mv);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          tlo[a] = mv[a];
+          dim[a] = -mv[3 + a] - tlo[a] + 1;
+        }
+        if (plain_slack(dim, kGatherTileNodes) < 0) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            tlo[a] = mv[6 + a];
+            dim[a] = -mv[9 + a] - tlo[a] + 1;
+          }
+          const int e = plain_slack(dim, kGatherTileNodes);
+          if (e < 0) dim[0] = -1;
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            if (e > 0) {
+              tlo[a] -= e;
+              dim[a] += 2 * e;
+            }
+        }
+        if (bx.box && threadIdx.x == 0) {
+          int* b = bx.box + (int64_t)bid * kBoxInts;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            b[a] = sref[a];
+            b[3 + a] = tlo[a];
+            b[6 + a] = dim[a];
+          }
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {  // block-uniform
         sref[a] = __builtin_amdgcn_readfirstlane(sref[a]);
         tlo[a] = __builtin_amdgcn_readfirstlane(tlo[a]);
         dim[a] = __builtin_amdgcn_readfirstlane(dim[a]);
       }
-    };
-    auto to_global_kernel = [&]() {
-      if (threadIdx.x == 0) work[1 + atomicAdd(work, 1)] = bid;
-    };
-    auto fill_tile = [&]() {
-      const int nt2 = dim[0] * dim[1] * dim[2] * (kGbufStride / 2);
-      const double2* g2 = reinterpret_cast<const double2*>(F.g);
-      const float inv_d1 = 1.0f / (float)dim[1], inv_d2 = 1.0f / (float)dim[2];
-      for (int t = threadIdx.x; t < nt2; t += kBlock) {
-        const int nd = t / (kGbufStride / 2), part = t % (kGbufStride / 2);
-        const int q = div_small(nd, inv_d2), cx = div_small(q, inv_d1);
-        const int cz = nd - q * dim[2], cy = q - cx * dim[1];
-        const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
-                                     sref[2] + tlo[2] + cz);
-        tile2[t] = g2[g * (kGbufStride / 2) + part];
-      }
-    };
-    bool find_box = true;
-    if (bx.reuse) {  // the box this block found in an earlier pass of the step
-      const int* b = bx.box + (int64_t)bid * kBoxInts;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        sref[a] = b[a];
-        tlo[a] = b[3 + a];
-        dim[a] = b[6 + a];
-      }
-      uniform();
-      if (dim[0] < 0) {
-        to_global_kernel();
-        return;
-      }
-      bool outside = false;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int raw = lo[a] - sref[a];
-        const int rel = min_image(raw, P.G.n[a]);
-        shift[a] = rel - raw;
-        outside = outside || (active && (rel < tlo[a] || rel + span[a] > tlo[a] + dim[a] - 1));
-      }
-      fill_tile();  // the loads start before the vote below is known
-      const bool wave_out = __ballot(outside) != 0ull;  // all lanes take part
-      if (threadIdx.x % kWave == 0) s_out[threadIdx.x / kWave] = wave_out;
-      __syncthreads();
-      find_box = false;
-#pragma unroll
-      for (int w = 0; w < kBlock / kWave; ++w) find_box = find_box || s_out[w] != 0;
-    }
-    if (find_box) {  // first pass of the step, or an orbit left the stored box
-      if (threadIdx.x == 0)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) s_ref[a] = lo[a];
-      __syncthreads();
-      int mv[6];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        sref[a] = s_ref[a];
-        const int raw = lo[a] - sref[a];
-        const int rel = min_image(raw, P.G.n[a]);
-        shift[a] = rel - raw;
-        mv[a] = active ? rel : 0x3fffffff;
-        mv[3 + a] = active ? -(rel + span[a]) : 0x3fffffff;
-      }
-      block_min_ints<6>(mv);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        tlo[a] = mv[a];
-        dim[a] = -mv[3 + a] - tlo[a] + 1;
-      }
-      // each extent is bounded first so that the product cannot overflow
-      const bool fits = dim[0] <= kGatherTileNodes && dim[1] <= kGatherTileNodes &&
-                        dim[2] <= kGatherTileNodes &&
-                        (int64_t)dim[0] * dim[1] * dim[2] <= kGatherTileNodes;
-      if (!fits) dim[0] = -1;
-      uniform();
-      if (bx.box && threadIdx.x == 0) {
-        int* b = bx.box + (int64_t)bid * kBoxInts;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          b[a] = sref[a];
-          b[3 + a] = tlo[a];
-          b[6 + a] = dim[a];
+      const bool use_tile = dim[0] > 0;
+      if (use_tile) {
+        const int nt2 = dim[0] * dim[1] * dim[2] * (kGbufStride / 2);
+        const float inv_d1 = 1.0f / (float)dim[1], inv_d2 = 1.0f / (float)dim[2];
+        for (int t = threadIdx.x; t < nt2; t += kBlock) {
+          const int nd = t / (kGbufStride / 2), part = t % (kGbufStride / 2);
+          const int q = div_small(nd, inv_d2), cx = div_small(q, inv_d1);
+          const int cz = nd - q * dim[2], cy = q - cx * dim[1];
+          const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
+                                       sref[2] + tlo[2] + cz);
+          tile2[t] = g2[g * (kGbufStride / 2) + part];
         }
       }
-      if (dim[0] < 0) {
-        to_global_kernel();
-        return;
-      }
-      fill_tile();
       __syncthreads();
-    }
-    if (active) {
-      TileGather acc;
-      acc.t = (lds_cdouble*)(reinterpret_cast<double*>(tile2));
-      acc.ox = shift[0] - sref[0] - tlo[0];
-      acc.oy = shift[1] - sref[1] - tlo[1];
-      acc.oz = shift[2] - sref[2] - tlo[2];
-      acc.dy = dim[1];
-      acc.dz = dim[2];
-      gather_push_one<R, SPLIT>(P, acc, st, i, x0, d, vb, qi, mi, vn, npieces[0], bad);
-    }
-  } else {
-    if (active) {
-      GlobalGather acc{F.g, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
-      gather_push_one<R, SPLIT>(P, acc, st, i, x0, d, vb, qi, mi, vn, npieces[0], bad);
-    }
-  }
-  if (active) {
-    // v^n and v^{n+1,p} again (see gather_push_one)
-    asm volatile("" ::: "memory");
-    st.v_of(P.np, i, va);
-    load3(vit, P.np, i, vi);
+      for (int k = 0; k < P.gper; ++k) {
+        const int64_t i = first + k * kBlock + threadIdx.x;
+        gather_batch<R, SPLIT>(
+            P, st, (int)i, i < P.np, vit, vnew, vbar_out,
+            [&](const int* shift) {
+              return TileGather{tile, shift[0] - sref[0] - tlo[0], shift[1] - sref[1] - tlo[1],
+                                shift[2] - sref[2] - tlo[2], dim[1], dim[2]};
+            },
+            [&](int ip, const double* x0, const double* d, int* shift) {
+              bool in = use_tile;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      vnew[j * P.np + i] = vn[j];
-      if (vbar_out) vbar_out[j * P.np + i] = 0.5 * (vn[j] + va[j]);  // the next pass's vbar
-      dvm = fmax(dvm, fabs(vn[j] - vi[j]));
-      vm = fmax(vm, fabs(vn[j]));
-      if (!isfinite(vn[j])) bad = 2.0;  // max-reductions drop NaN: flag it explicitly
-    }
-  }
-  // no block barrier after the orbit loops: a wavefront with fewer pieces
-  // does not wait for the block's slowest one
-  const double part[4] = {dvm, vm, bad, npieces[0]};
-  const bool ismax[4] = {true, true, true, false};
-  double blk[4];
-  if (late_reduce<4>(part, ismax, blk)) {
-    atomic_max_nonneg(sc.spread_copy(S_DVMAX), blk[0]);
-    atomic_max_nonneg(sc.spread_copy(S_VMAX), blk[1]);
-    atomic_max_nonneg(sc.spread_copy(S_BAD), blk[2]);
-    // integer counts: the atomic sum is exact and order-free
-    if (blk[3] > 0.0) unsafeAtomicAdd(sc.spread_copy(S_PIECES), blk[3]);
-  }
-  if (prev.w) {  // Anderson mixing over one difference: dF . dF and dF . f_p
-    double aa[2] = {0.0, 0.0};
-    if (active) {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const int64_t e = j * P.np + i;
-        const double f0 = vn[j] - vi[j], df = f0 - (prev.g[e] - prev.w[e]);
-        aa[0] += df * df;
-        aa[1] += df * f0;
+              for (int a = 0; a < 3; ++a) {
+                int lo, n, b0;
+                orbit_nodes<R>(x0[a], d[a], P.G.invH[a], lo, n, b0);
+                const int rel = min_image(lo - sref[a], P.G.n[a]);
+                shift[a] = rel - (lo - sref[a]);
+                in = in && d[a] == d[a] && rel >= tlo[a] && rel + n < tlo[a] + dim[a];
+              }
+              if (!in) work[1 + atomicAdd(work, 1)] = ip;
+              return in;
+            },
+            prev, tot);
       }
     }
-    const bool sums[2] = {false, false};
-    double ab[2];
-    if (late_reduce<2>(aa, sums, ab)) {
-      const int64_t nb = (P.np + kBlock - 1) / kBlock;
-      sc.region(P_AA)[bid] = ab[0];
-      sc.region(P_AA)[nb + bid] = ab[1];
-    }
-  }
-}
-
-// Two waves per SIMD for the tiled quadratic gather: its orbit loop fits 256
-// registers, and asking for the occupancy makes the compiler keep it (it would
-// otherwise go to one wave and twice the registers for a few more values).
-// The global-memory kernel, which only takes blocks whose box overflows the
-// tile, is left to the compiler's choice.
-template <int R, bool TILED>
-constexpr int kGatherWavesPerSimd = (R == 2 && TILED) ? 2 : 1;
-
-template <int R, bool TILED, class PS, bool SPLIT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    kGatherWavesPerSimd<R, TILED>))) void k_gather_push(StepParams P, PS st,
-                                                       const double* __restrict__ vit,
-                                                       double* __restrict__ vnew,
-                                                       double* __restrict__ vbar_out, AosFields F,
-                                                       int* __restrict__ work, Scratch sc,
-                                                       AndersonPrev prev, ChunkBoxes bx) {
-  if (TILED || !work) {
-    late_reduce_init<4>();
-    late_reduce_init<2>();
-    if (!TILED) __syncthreads();  // the tiled path has a barrier before its first use
-    gather_block<R, TILED, PS, SPLIT>(P, st, vit, vnew, vbar_out, F, work, sc, prev, blockIdx.x,
-                                      bx);
-    return;
-  }
-  const int count = work[0];  // written by the tiled kernel (previous launch)
-  for (int j = blockIdx.x; j < count; j += gridDim.x) {
-    __syncthreads();  // the previous block's LDS reductions are complete
-    late_reduce_init<4>();
-    late_reduce_init<2>();
-    __syncthreads();
-    gather_block<R, TILED, PS, SPLIT>(P, st, vit, vnew, vbar_out, F, work, sc, prev, work[1 + j],
-                                      ChunkBoxes{});
+    totals_finish(tot, sc, prev.w != nullptr, aa_row0 + bid, aa_rows);
   }
 }
 
@@ -1493,7 +1857,9 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 
 }  // namespace
 
-int64_t scatter_blocks(int64_t np, int chunk) { return (np + chunk - 1) / chunk; }
+int64_t scatter_blocks(int64_t np, int chunk, int span) {
+  return (np + span - 1) / span * (span / chunk);
+}
 int64_t particle_blocks(int64_t np) { return (np + kBlock - 1) / kBlock; }
 
 // ---- launchers ---------------------------------------------------------------
@@ -1520,24 +1886,71 @@ void launch_scatter(hipStream_t s, int r, const StepParams& P, const PS& st, con
                     const double* vbar, CurrentOut out, Scratch sc, ChunkBoxes bx) {
   if (P.np <= 0) return;
   const bool multi = P.nsp > 1;
-  // degree x (split) x species x chunk length (4096 for r <= 2 only; the
-  // host validates P.chunk, whose block count the reductions also use)
+  // degree x (split) x species
+  const unsigned nblk = (unsigned)scatter_blocks(P.np, P.chunk, P.span);
   auto go = [&](auto R, auto SPLIT) {
-    auto launch = [&](auto MULTI, auto CH) {
-      const unsigned nblk = (unsigned)scatter_blocks(P.np, CH.value);
-      k_scatter<R.value, PS, SPLIT.value, MULTI.value, CH.value>
+    if (multi)
+      k_scatter<R.value, PS, SPLIT.value, true>
           <<<nblk, kBlock, 0, s>>>(P, st, vit, vbar, out, sc, bx);
-    };
-    auto by_multi = [&](auto CH) {
-      if (multi)
-        launch(std::true_type{}, CH);
-      else
-        launch(std::false_type{}, CH);
-    };
-    if (R.value < 3 && P.chunk == 4096)
-      by_multi(std::integral_constant<int, 4096>{});
     else
-      by_multi(std::integral_constant<int, 2048>{});
+      k_scatter<R.value, PS, SPLIT.value, false>
+          <<<nblk, kBlock, 0, s>>>(P, st, vit, vbar, out, sc, bx);
+  };
+  if constexpr (!PS::kMixed) {
+    if (!P.split) {
+      by_degree(r, [&](auto R) { go(R, std::false_type{}); });
+      return;
+    }
+  }
+  if constexpr (!PS::kMixed) {
+    if (P.scatter_mm) {  // degree 2
+      if (multi)
+        k_scatter_mm<2, true><<<nblk, kBlock, 0, s>>>(P, st, vit, vbar, out.J, sc, bx);
+      else
+        k_scatter_mm<2, false><<<nblk, kBlock, 0, s>>>(P, st, vit, vbar, out.J, sc, bx);
+      return;
+    }
+  }
+  by_degree(r, [&](auto R) { go(R, std::true_type{}); });
+}
+
+// Batches of 256 particles per gather block: as many as leave four blocks per
+// compute unit, at most 4, and no more than the particles of 16 cells, whose box
+// fits the tile.
+int gather_batches(int64_t np, int64_t ncell) {
+  int g = 4;
+  while (g > 1 && (np < (int64_t)g * kBlock * 1024 || g * kBlock * ncell > 16 * np)) g /= 2;
+  return g;
+}
+
+GatherGrid gather_grid(int64_t np, int64_t ncell) {
+  GatherGrid g;
+  g.batches = gather_batches(np, ncell);
+  g.blocks = (int)((np + (int64_t)g.batches * kBlock - 1) / ((int64_t)g.batches * kBlock));
+  g.whole_mesh = ncell <= kGatherTileNodes;
+  g.list_blocks = g.whole_mesh ? 0 : std::min((int)blocks_for(np), 512);
+  return g;
+}
+
+template <class PS>
+void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const double* vit,
+                        double* vnew, double* vbar_out, const double* gbuf, int* work, Scratch sc,
+                        AndersonPrev prev, ChunkBoxes bx) {
+  if (P.np <= 0) return;
+  AosFields F{gbuf};
+  const GatherGrid g = gather_grid(P.np, P.G.ncell);
+  P.gper = g.batches;
+  const int rows = g.blocks + g.list_blocks;
+  auto go = [&](auto R, auto SPLIT) {
+    if (g.whole_mesh) {
+      k_gather_push<R.value, GATHER_MESH, PS, SPLIT.value><<<g.blocks, kBlock, 0, s>>>(
+          P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+      return;
+    }
+    k_gather_push<R.value, GATHER_TILE, PS, SPLIT.value><<<g.blocks, kBlock, 0, s>>>(
+        P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+    k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value><<<g.list_blocks, kBlock, 0, s>>>(
+        P, st, vit, vnew, vbar_out, F, work, sc, prev, ChunkBoxes{}, g.blocks, rows);
   };
   if constexpr (!PS::kMixed) {
     if (!P.split) {
@@ -1546,29 +1959,6 @@ void launch_scatter(hipStream_t s, int r, const StepParams& P, const PS& st, con
     }
   }
   by_degree(r, [&](auto R) { go(R, std::true_type{}); });
-}
-
-template <class PS>
-void launch_gather_push(hipStream_t s, int r, const StepParams& P, const PS& st,
-                        const double* vit, double* vnew, double* vbar_out, const double* gbuf,
-                        int* work, Scratch sc, AndersonPrev prev, ChunkBoxes bx) {
-  if (P.np <= 0) return;
-  AosFields F{gbuf};
-  const unsigned nb = blocks_for(P.np);
-  const unsigned ng = work ? std::min<unsigned>(nb, kGatherListGrid) : nb;
-#define ECPIC_GATHER_PAIR(R_, SPLIT_)                                                          \
-  k_gather_push<R_, true, PS, SPLIT_><<<nb, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F,    \
-                                                             work, sc, prev, bx);              \
-  k_gather_push<R_, false, PS, SPLIT_><<<ng, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F,   \
-                                                              work, sc, prev, ChunkBoxes{})
-  if constexpr (!PS::kMixed) {
-    if (!P.split) {
-      by_degree(r, [&](auto R) { ECPIC_GATHER_PAIR(R.value, false); });
-      return;
-    }
-  }
-  by_degree(r, [&](auto R) { ECPIC_GATHER_PAIR(R.value, true); });
-#undef ECPIC_GATHER_PAIR
 }
 
 template <class PS>
@@ -1632,8 +2022,8 @@ void launch_fixed_current(hipStream_t s, int64_t n, unsigned long long* Jfix, do
   template void launch_extrapolate<PS>(hipStream_t, int64_t, const PS&, double*, double*);                \
   template void launch_scatter<PS>(hipStream_t, int, const StepParams&, const PS&, const double*, \
                                    const double*, CurrentOut, Scratch, ChunkBoxes);              \
-  template void launch_gather_push<PS>(hipStream_t, int, const StepParams&, const PS&,           \
-                                       const double*, double*, double*, const double*, int*,     \
+  template void launch_gather_push<PS>(hipStream_t, int, StepParams, const PS&, const double*,  \
+                                       double*, double*, const double*, int*,     \
                                        Scratch, AndersonPrev, ChunkBoxes);                       \
   template void launch_sweep<PS>(hipStream_t, int, const StepParams&, const PS&, const double*,  \
                                  const double*, const double*, Scratch);                         \

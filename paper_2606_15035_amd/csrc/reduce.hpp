@@ -134,12 +134,10 @@ __device__ __forceinline__ void block_partials(double (&v)[M], double* region) {
 }
 
 // Periodic minimum image of a node-index difference: raw mod n in
-// [-n/2, n/2].
+// (-n/2, n/2]; n is a power of two.
 __device__ __forceinline__ int min_image(int raw, int n) {
-  int r = raw % n;
-  if (2 * r > n) r -= n;
-  if (2 * r < -n) r += n;
-  return r;
+  const int r = raw & (n - 1);
+  return 2 * r > n ? r - n : r;
 }
 
 // block-wide minimum of M ints at once (one barrier pair for all of them)

@@ -5,8 +5,12 @@
 // two-stream problem drift apart by 2 v0 dt per step, so without re-sorting
 // a chunk's box grows linearly in time.
 //
-// Cells are numbered like nodes (z fastest); inside a cell the particles are
-// grouped by the octant of their velocity.  The order inside a group is the
+// The key of a particle is the base node of its stencil at x^n (the node
+// nearest to it for degree 2, else the lower corner of its cell), so that the
+// particles of one key share the stencil of their orbits' first pieces.  Keys
+// are numbered along a path of neighbouring nodes (node_rank below) that keeps
+// any run of consecutive particles in a compact box of cells; inside a key the
+// particles are grouped by the octant of their velocity.  The order inside a group is the
 // order in which the atomic cursor hands out slots, so it is not
 // reproducible; every result of the method is invariant under particle
 // permutation up to rounding.  A particle id array travels with the
@@ -25,13 +29,18 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // Wavefront-aggregated atomicAdd(counter + key, 1): the lanes of a wavefront
 // that share a key take one atomic for the whole group and consecutive
 // slots in lane order.  With sorted keys a wavefront has only a few distinct
-// keys, so this replaces tens of same-address atomics by one.  Returns the
-// lane's slot (old value + rank among the group's lanes).
+// keys, so this replaces tens of same-address atomics by one.  After kRounds
+// groups the remaining lanes take an atomic each: a round costs a serial trip to
+// the counter, and a wavefront of few particles per key has tens of them
+// (k_permute, 100,002 particles at 12 per cell: 32.7 us without a limit, 14.2
+// with 8 rounds; 2,097,152 at 64 per cell: 111 us, with 4 rounds 129, with 8 111).
+// Returns the lane's slot (old value + rank among the group's lanes).
+constexpr int kRounds = 12;
 __device__ __forceinline__ int wave_aggregated_inc(int* counter, int key, bool active) {
   const int lane = threadIdx.x % kWave;
   unsigned long long todo = __ballot(active);
   int slot = 0;
-  while (todo) {
+  for (int r = 0; r < kRounds && todo; ++r) {
     const int leader = __ffsll((long long)todo) - 1;
     const int lkey = __shfl(key, leader, kWave);
     const unsigned long long group = __ballot(active && key == lkey) & todo;
@@ -41,6 +50,7 @@ __device__ __forceinline__ int wave_aggregated_inc(int* counter, int key, bool a
     if ((group >> lane) & 1ull) slot = base + __popcll(group & ((1ull << lane) - 1ull));
     todo &= ~group;
   }
+  if ((todo >> lane) & 1ull) slot = atomicAdd(counter + key, 1);
   return slot;
 }
 
@@ -54,11 +64,29 @@ __global__ __launch_bounds__(kBlock) void k_iota(int64_t n, int* p) {
   if (i < n) p[i] = (int)i;
 }
 
-// key = 8 * cell + octant of v^n: inside a cell, particles moving the same
-// way stay together, which keeps the orbit-piece structure of a wavefront's
-// lanes alike (less divergence in the gather).
+// Position of a node in the sorted order: columns of 4x4 nodes along z, one
+// after the other, each walked layer by layer, so that consecutive nodes are
+// neighbours (the columns, the layers and the rows inside a layer alternate
+// direction).  Any run of 64 nodes is then a 4x4x5 box wherever it starts, and
+// a shorter run a part of one.  In plain z-fastest order 64 nodes are two rows
+// of 32 (a node box with orbits and stencils of 6x7x40, here 9x9x10), and the
+// particles of one block at 10 per cell lie in two or three separate rows.
+// Morton order is as compact inside its blocks, but a run that straddles two
+// blocks spans both.
+__device__ __forceinline__ int node_rank(const Grid& G, const int* c) {
+  const int nby = G.n[1] >> 2, bx = c[0] >> 2, by = c[1] >> 2;
+  const int col = bx * nby + (bx & 1 ? nby - 1 - by : by);
+  const int z = col & 1 ? G.mask[2] - c[2] : c[2];
+  const int lx = c[0] & 3, ly = lx & 1 ? 3 - (c[1] & 3) : c[1] & 3;
+  const int p = lx * 4 + ly;
+  return (col * G.n[2] + z) * 16 + (z & 1 ? 15 - p : p);
+}
+
+// key = 8 * rank of the base node + octant of v^n: inside a cell, particles
+// moving the same way stay together, which keeps the orbit-piece structure of
+// a wavefront's lanes alike (less divergence in the gather).
 template <class PS>
-__global__ __launch_bounds__(kBlock) void k_cell_keys(Grid G, int64_t np, PS st,
+__global__ __launch_bounds__(kBlock) void k_cell_keys(Grid G, int64_t np, PS st, bool nearest,
                                                      int* __restrict__ key,
                                                      int* __restrict__ count) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -67,12 +95,12 @@ __global__ __launch_bounds__(kBlock) void k_cell_keys(Grid G, int64_t np, PS st,
   if (active) {
     int c[3];
     double va[3];
-    st.cell_of(G, np, i, c);
+    st.base_of(G, np, i, nearest, c);
     st.v_of(np, i, va);
     int oct = 0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) oct |= (va[a] > 0.0 ? 1 : 0) << a;
-    k = (node_index(G, c[0], c[1], c[2]) << 3) | oct;
+    k = (node_rank(G, c) << 3) | oct;
     key[i] = k;
   }
   wave_aggregated_inc(count, k, active);
@@ -216,12 +244,12 @@ void launch_iota(hipStream_t s, int64_t n, int* p) {
 }
 
 template <class PS>
-void launch_sort(hipStream_t s, const Grid& G, int64_t np, PS& cur, PS& alt, int*& id, int*& id2,
-                 const SortScratch& b, double* vit, double* vbar) {
+void launch_sort(hipStream_t s, const Grid& G, int r, int64_t np, PS& cur, PS& alt, int*& id,
+                 int*& id2, const SortScratch& b, double* vit, double* vbar) {
   if (np <= 0) return;
   const int64_t nkeys = 8 * G.ncell;
   k_fill_int<<<blocks_for(nkeys), kBlock, 0, s>>>(nkeys, b.count, 0);
-  k_cell_keys<PS><<<blocks_for(np), kBlock, 0, s>>>(G, np, cur, b.key, b.count);
+  k_cell_keys<PS><<<blocks_for(np), kBlock, 0, s>>>(G, np, cur, r == 2, b.key, b.count);
   const int64_t nb = (nkeys + kScanTile - 1) / kScanTile;
   k_scan_totals<<<(unsigned)nb, kBlock, 0, s>>>(nkeys, b.count, b.scan_totals);
   k_scan_block_totals<<<1, kBlock, 0, s>>>(nb, b.scan_totals, b.offset, nkeys);
@@ -237,12 +265,10 @@ void launch_sort(hipStream_t s, const Grid& G, int64_t np, PS& cur, PS& alt, int
   id2 = ti;
 }
 
-template void launch_sort<Fp64Store>(hipStream_t, const Grid&, int64_t, Fp64Store&, Fp64Store&,
-                                     int*&, int*&, const SortScratch&, double*,
-                                     double*);
-template void launch_sort<MixedStore>(hipStream_t, const Grid&, int64_t, MixedStore&,
-                                      MixedStore&, int*&, int*&, const SortScratch&, double*,
-                                     double*);
+template void launch_sort<Fp64Store>(hipStream_t, const Grid&, int, int64_t, Fp64Store&, Fp64Store&,
+                                     int*&, int*&, const SortScratch&, double*, double*);
+template void launch_sort<MixedStore>(hipStream_t, const Grid&, int, int64_t, MixedStore&, MixedStore&,
+                                      int*&, int*&, const SortScratch&, double*, double*);
 
 void launch_to_caller(hipStream_t s, int64_t np, const int* id, const double* src, double* dst) {
   if (np > 0) k_to_caller<<<blocks_for(np), kBlock, 0, s>>>(np, id, src, dst);

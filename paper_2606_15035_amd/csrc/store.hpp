@@ -84,10 +84,14 @@ struct Fp64Store {
       out[a] = w[a];
     }
   }
-  // cell of x^n (lower-corner node per axis)
-  __device__ __forceinline__ void cell_of(const Grid& G, int64_t np, int64_t i, int* c) const {
+  // node at or below x^n per axis (wrapped into the mesh), or with nearest the
+  // node nearest to it: the base node of a degree-2 stencil
+  __device__ __forceinline__ void base_of(const Grid& G, int64_t np, int64_t i, bool nearest,
+                                          int* c) const {
+    const double off = nearest ? 0.5 : 0.0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) c[a] = to_int_clamped(floor(x[a * np + i] * G.invH[a]));
+    for (int a = 0; a < 3; ++a)
+      c[a] = to_int_clamped(floor(x[a * np + i] * G.invH[a] + off)) & G.mask[a];
   }
   // particle i of this store -> particle j of dst
   __device__ __forceinline__ void move_to(const Fp64Store& dst, int64_t np, int64_t i,
@@ -193,11 +197,15 @@ struct MixedStore {
       out[a] = (double)f;
     }
   }
-  __device__ __forceinline__ void cell_of(const Grid& G, int64_t, int64_t i, int* c) const {
+  __device__ __forceinline__ void base_of(const Grid& G, int64_t np, int64_t i, bool nearest,
+                                          int* c) const {
     const int k = cell[i];
     c[0] = k >> G.shx;
     c[1] = (k >> G.shy) & G.mask[1];
     c[2] = k & G.mask[2];
+    if (nearest)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) c[a] = (c[a] + (off[a * np + i] >= 0.5f ? 1 : 0)) & G.mask[a];
   }
   __device__ __forceinline__ void move_to(const MixedStore& dst, int64_t np, int64_t i,
                                           int64_t j) const {
