@@ -39,40 +39,56 @@ struct Axis2 {
   }
 };
 
-// Where the push's mesh adjoints go (nine values per node: component l of
-// grad phi, A^n and A^{n+1} as 0 + l, 3 + l and 6 + l).  add() takes the node
-// in the particle's unwrapped frame (ix, iy, iz) and its flat index g.
-struct GlobalAdjSink {
-  const AdjParticleArgs* P;
-  __device__ __forceinline__ double* target(int comp) const {
-    double* base = comp < 3 ? P->lgphi : (comp < 6 ? P->lA0 : P->lA1);
-    return base + (int64_t)(comp % 3) * P->G.ncell;
-  }
-  __device__ __forceinline__ void add(int comp, int, int, int, int64_t g, double v) const {
-    unsafeAtomicAdd(target(comp) + g, v);
-  }
-};
-
-// The block's LDS tile over its chunk's node box (nine doubles per node);
-// o[] takes the particle's frame to the tile's.  A node outside the box
-// (not expected: the box holds every orbit) goes to global
-// memory.  The tile pointer carries the LDS address space, so the additions
-// are LDS atomics (through a plain pointer they compiled to flat atomics,
-// the slower path that serves either memory).
+// The nine values of a node that the push reads (components l of grad phi, A^n
+// and A^{n+1} as 0 + l, 3 + l and 6 + l) and the nine adjoints that it adds to,
+// in the block's LDS tile over its particles' node box, or in global memory for
+// a node outside the box.  at() takes the node in the particle's unwrapped frame
+// (ix, iy, iz).  The tile pointers carry the LDS address space, so the additions
+// are LDS atomics (through a plain pointer they compiled to flat atomics, the
+// slower path that serves either memory).
 typedef __attribute__((address_space(3))) double lds_double;
-struct TileAdjSink {
-  GlobalAdjSink glob;
-  lds_double* tile;
-  int o[3], dim[3];
-  bool use;
-  __device__ __forceinline__ void add(int comp, int ix, int iy, int iz, int64_t g,
-                                      double v) const {
+struct AdjNode {
+  int t;      // first of the node's nine values in the tile, negative outside it
+  int64_t g;  // flat index in the mesh
+};
+struct AdjTile {
+  const AdjParticleArgs* P;
+  lds_double* field;
+  lds_double* sum;
+  int o[3], dim[3];  // particle's frame -> tile, extents (0: no tile)
+  int sy, sx;        // nodes between neighbours along y and x; along z 1
+  __device__ __forceinline__ AdjNode at(int ix, int iy, int iz) const {
     const int tx = ix + o[0], ty = iy + o[1], tz = iz + o[2];
-    if (use && tx >= 0 && ty >= 0 && tz >= 0 && tx < dim[0] && ty < dim[1] && tz < dim[2])
-      __hip_atomic_fetch_add(&tile[9 * ((tx * dim[1] + ty) * dim[2] + tz) + comp], v,
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    else
-      glob.add(comp, ix, iy, iz, g, v);
+    const bool in = tx >= 0 && ty >= 0 && tz >= 0 && tx < dim[0] && ty < dim[1] && tz < dim[2];
+    return {in ? 9 * (tx * sx + ty * sy + tz) : -1, node_index(P->G, ix, iy, iz)};
+  }
+  __device__ __forceinline__ const double* global_field(int k) const {
+    return (k < 3 ? P->gphi : (k < 6 ? P->A0 : P->A1)) + (int64_t)(k % 3) * P->G.ncell;
+  }
+  __device__ __forceinline__ double* global_sum(int k) const {
+    return (k < 3 ? P->lgphi : (k < 6 ? P->lA0 : P->lA1)) + (int64_t)(k % 3) * P->G.ncell;
+  }
+  template <int K0, int N>
+  __device__ __forceinline__ void load(const AdjNode& n, double (&f)[N]) const {
+    if (n.t >= 0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) f[k] = field[n.t + K0 + k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k) f[k] = global_field(K0 + k)[n.g];
+    }
+  }
+  template <int K0, int N>
+  __device__ __forceinline__ void add(const AdjNode& n, const double (&v)[N]) const {
+    if (n.t >= 0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        __hip_atomic_fetch_add(&sum[n.t + K0 + k], v[k], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k) unsafeAtomicAdd(global_sum(K0 + k) + n.g, v[k]);
+    }
   }
 };
 
@@ -90,11 +106,10 @@ struct TileAdjSink {
 //    every point); the row's x and y factors then give the Hessian terms.
 // The same sums as a node-by-node evaluation, with about a quarter of its
 // arithmetic.
-template <class Sink>
 __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i,
-                                             const Sink& sink) {
+                                             const AdjTile& tile) {
   const Grid& G = P.G;
-  const int64_t np = P.np, nc = G.ncell;
+  const int64_t np = P.np;
   double x0[3], vb[3], d[3], eta[3], ep[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -142,17 +157,15 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const double ddZ = c == 1 ? -2.0 : 1.0;
-          const int ix = fx + a, iy = fy + b, iz = fz + c;
-          const int64_t g = node_index(G, ix, iy, iz);
-          double A0g[3], A1g[3];
+          const AdjNode node = tile.at(fx + a, fy + b, fz + c);
+          double f[9];  // grad phi, A^n, A^{n+1}
+          tile.load<0>(node, f);
           double b0 = 0.0, b1 = 0.0, eg = 0.0;
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            A0g[l] = P.A0[l * nc + g];
-            A1g[l] = P.A1[l * nc + g];
-            b0 += vb[l] * A0g[l];
-            b1 += vb[l] * A1g[l];
-            eg += eta[l] * P.gphi[l * nc + g];
+            b0 += vb[l] * f[3 + l];
+            b1 += vb[l] * f[6 + l];
+            eg += eta[l] * f[l];
           }
           double Sbar = 0.0, T0 = 0.0, T1 = 0.0;
 #pragma unroll
@@ -171,13 +184,15 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
           }
           C0dd += b0 * ddZ;
           C1dd += b1 * ddZ;
+          double v[9];
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            lvb[l] += P.dt * (A0g[l] * T0 + A1g[l] * T1);
-            sink.add(l, ix, iy, iz, g, -P.dt * eta[l] * Sbar);
-            sink.add(3 + l, ix, iy, iz, g, P.dt * vb[l] * T0);
-            sink.add(6 + l, ix, iy, iz, g, P.dt * vb[l] * T1);
+            lvb[l] += P.dt * (f[3 + l] * T0 + f[6 + l] * T1);
+            v[l] = -P.dt * eta[l] * Sbar;
+            v[3 + l] = P.dt * vb[l] * T0;
+            v[6 + l] = P.dt * vb[l] * T1;
           }
+          tile.add<0>(node, v);
         }
         // the row's share of sum_g b (eta'.grad)(d_k S_g) (with b0 and b1) and
         // of sum_g eg d_k S_g, per point
@@ -215,7 +230,6 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     const double sgn = e == 0 ? 1.0 : -1.0;
-    const double* F = e == 0 ? P.A0 : P.A1;
     double base[3];
     int first[3], sh[3];
     Axis2 ax[3];
@@ -232,18 +246,27 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
     for (int a = 0; a < 3; ++a)
       for (int b = 0; b < 3; ++b)
         for (int c = 0; c < 3; ++c) {
-          const int64_t g = node_index(G, first[0] + a, first[1] + b, first[2] + c);
+          const AdjNode node =
+              tile.at(first[0] + a + sh[0], first[1] + b + sh[1], first[2] + c + sh[2]);
           const double S = ax[0].w[a] * ax[1].w[b] * ax[2].w[c];
           const double dS[3] = {ax[0].dw[a] * ax[1].w[b] * ax[2].w[c],
                                 ax[0].w[a] * ax[1].dw[b] * ax[2].w[c],
                                 ax[0].w[a] * ax[1].w[b] * ax[2].dw[c]};
+          double f[3], v[3];
+          if (e == 0)
+            tile.load<3>(node, f);
+          else
+            tile.load<6>(node, f);
           double eF = 0.0;
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            eF += eta[l] * F[l * nc + g];
-            sink.add((e == 0 ? 3 : 6) + l, first[0] + a + sh[0], first[1] + b + sh[1],
-                     first[2] + c + sh[2], g, sgn * eta[l] * S);
+            eF += eta[l] * f[l];
+            v[l] = sgn * eta[l] * S;
           }
+          if (e == 0)
+            tile.add<3>(node, v);
+          else
+            tile.add<6>(node, v);
 #pragma unroll
           for (int kk = 0; kk < 3; ++kk) {
             lx[kk] += sgn * eF * dS[kk];
@@ -356,92 +379,138 @@ __global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P) {
   }
 }
 
-// The push terms over cell-sorted particles, one block per chunk of kAdjChunk
-// particles whose wavefronts' lanes sit kAdjChunk / 64 particles apart (one
-// cell apart at 64 particles per cell), as in the current scatter: the block
-// finds the node box of its chunk's orbits and end points, sums the nine mesh adjoints of its particles in an LDS
-// tile over that box, and adds the tile to global memory once.  A chunk
-// whose box exceeds the tile adds straight to global memory.  The kernel
-// runs at one wavefront per SIMD (its registers), so one block per CU loses
-// nothing to the 144 KB tile.
-constexpr int kAdjChunk = 4096;
-constexpr int kAdjTileNodes = 2048;
+// The push terms over cell-sorted particles, in blocks of P.chunk particles
+// whose lanes are spread over P.span, as in the current scatter: the block finds
+// the node box of its particles' orbits and end points (clipped to the start
+// stencils plus what fits, where the box exceeds the tile), copies the box's
+// fields into LDS, sums the nine mesh adjoints of its particles in a second LDS
+// array over it, and adds that to global memory once.  The kernel runs at one
+// wavefront per SIMD (its registers), so one block per CU loses nothing to the
+// 144 KB.
+// Rows are padded where that fits (as TileStrides in particles.hip: the 64-bit
+// additions of 16 neighbouring lanes then rarely share a bank pair).
+constexpr int kAdjTileNodes = 1000;
 
-__device__ __forceinline__ int64_t adj_chunk_particle(int64_t base, int k) {
-  return base + (int64_t)(threadIdx.x % kWave) * (kAdjChunk / kWave) + threadIdx.x / kWave +
-         (int64_t)(kBlock / kWave) * k;
-}
+struct AdjStrides {
+  int sy, sx;
+  bool fits;
+  __device__ __forceinline__ AdjStrides(const int* dim) : sy(1), sx(1), fits(false) {
+    // each extent is bounded first so that the products cannot overflow
+    if (!(dim[0] > 0 && dim[0] <= kAdjTileNodes && dim[1] <= kAdjTileNodes &&
+          dim[2] <= kAdjTileNodes))
+      return;
+    sy = (dim[2] + 15) & ~15;
+    sx = dim[1] * sy + 4;
+    if ((int64_t)dim[0] * sx > kAdjTileNodes) {
+      sy = dim[2];
+      sx = dim[1] * sy;
+    }
+    fits = (int64_t)dim[0] * sx <= kAdjTileNodes;
+  }
+};
 
 __global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P) {
-  constexpr int kPerThread = kAdjChunk / kBlock;
-  __shared__ double tile[9 * kAdjTileNodes];
+  __shared__ double field[9 * kAdjTileNodes];
+  __shared__ double sum[9 * kAdjTileNodes];
   __shared__ int s_ref[3];
   const Grid& G = P.G;
-  const int64_t base = (int64_t)blockIdx.x * kAdjChunk;
+  const int per_thread = P.chunk / kBlock;
+  const int64_t base = chunk_base(P.chunk, P.span, blockIdx.x);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-      s_ref[a] = to_int_clamped(floor(P.x[a * P.np + base] * G.invH[a] + Spline<2>::base_off));
+    for (int a = 0; a < 3; ++a)  // a span's last blocks may be empty
+      s_ref[a] = to_int_clamped(
+          floor(P.x[a * P.np + min(base, P.np - 1)] * G.invH[a] + Spline<2>::base_off));
   __syncthreads();
-  // node box of the chunk: the orbits from x0 to x0 + d (unwrapped), which
-  // also hold both end points' stencils
-  int rmin[3] = {0x3fffffff, 0x3fffffff, 0x3fffffff};
-  int rmax[3] = {-0x3fffffff, -0x3fffffff, -0x3fffffff};
-  for (int k = 0; k < kPerThread; ++k) {
-    const int64_t i = adj_chunk_particle(base, k);
+  // node boxes: the orbits from x0 to x0 + d (unwrapped), which also hold both end
+  // points' stencils, and the start stencils alone
+  int mv[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) mv[k] = 0x3fffffff;
+  for (int k = 0; k < per_thread; ++k) {
+    const int64_t i = chunk_particle(base, P.span, k);
     if (i >= P.np) continue;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       int lo, n, b0;
       orbit_nodes<2>(P.x[a * P.np + i], P.dt * P.vb[a * P.np + i], G.invH[a], lo, n, b0);
       const int rel = min_image(lo - s_ref[a], G.n[a]);
-      rmin[a] = min(rmin[a], rel);
-      rmax[a] = max(rmax[a], rel + n);
+      mv[a] = min(mv[a], rel);
+      mv[3 + a] = min(mv[3 + a], -(rel + n));
+      mv[6 + a] = min(mv[6 + a], rel + (b0 - lo));
+      mv[9 + a] = min(mv[9 + a], -(rel + (b0 - lo) + 3));
     }
   }
-  int tlo[3], dim[3];
-  {
-    int mv[6] = {rmin[0], rmin[1], rmin[2], -rmax[0], -rmax[1], -rmax[2]};
-    block_min_ints<6>(mv);
+  block_min_ints<12>(mv);
+  AdjTile tile{&P, (lds_double*)field, (lds_double*)sum, {0, 0, 0}, {0, 0, 0}, 1, 1};
+  int tlo[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    tlo[a] = mv[a];
+    tile.dim[a] = -mv[3 + a] - tlo[a] + 1;
+  }
+  if (!AdjStrides(tile.dim).fits) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      tlo[a] = mv[a];
-      dim[a] = -mv[3 + a] - tlo[a] + 1;
+      tlo[a] = mv[6 + a];
+      tile.dim[a] = -mv[9 + a] - tlo[a] + 1;
+    }
+    for (int e = 0; e < 4; ++e) {  // widened while it fits
+      const int wider[3] = {tile.dim[0] + 2, tile.dim[1] + 2, tile.dim[2] + 2};
+      if (!AdjStrides(wider).fits) break;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        tlo[a] -= 1;
+        tile.dim[a] = wider[a];
+      }
     }
   }
-  // block-uniform; each extent is bounded first so that the product cannot overflow
-  const bool use_tile = dim[0] > 0 && dim[0] <= kAdjTileNodes && dim[1] <= kAdjTileNodes &&
-                        dim[2] <= kAdjTileNodes &&
-                        (int64_t)dim[0] * dim[1] * dim[2] <= kAdjTileNodes;
-  const int nt = use_tile ? dim[0] * dim[1] * dim[2] : 0;
-  for (int t = threadIdx.x; t < 9 * nt; t += kBlock) tile[t] = 0.0;
+  const AdjStrides str(tile.dim);
+  tile.sy = str.sy;
+  tile.sx = str.sx;
+  if (!str.fits) tile.dim[0] = tile.dim[1] = tile.dim[2] = 0;  // every node in global memory
+  const int nt = tile.dim[0] * tile.dim[1] * tile.dim[2];
+  const float inv_d1 = 1.0f / (float)max(tile.dim[1], 1), inv_d2 = 1.0f / (float)max(tile.dim[2], 1);
+  // node t of the box: its slot in the tile and its place in the mesh
+  auto box_node = [&](int t, int& slot, int64_t& g) {
+    const int q = div_small(t, inv_d2), cx = div_small(q, inv_d1);
+    const int cz = t - q * tile.dim[2], cy = q - cx * tile.dim[1];
+    slot = 9 * (cx * tile.sx + cy * tile.sy + cz);
+    g = node_index(G, s_ref[0] + tlo[0] + cx, s_ref[1] + tlo[1] + cy, s_ref[2] + tlo[2] + cz);
+  };
+  for (int t = threadIdx.x; t < nt; t += kBlock) {
+    int slot;
+    int64_t g;
+    box_node(t, slot, g);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      field[slot + k] = tile.global_field(k)[g];
+      sum[slot + k] = 0.0;
+    }
+  }
   __syncthreads();
-  for (int k = 0; k < kPerThread; ++k) {
-    const int64_t i = adj_chunk_particle(base, k);
-    if (i >= P.np) break;
-    TileAdjSink sink{GlobalAdjSink{&P}, (lds_double*)tile, {0, 0, 0}, {dim[0], dim[1], dim[2]},
-                     use_tile};
+  for (int k = 0; k < per_thread; ++k) {
+    const int64_t i = chunk_particle(base, P.span, k);
+    if (i >= P.np) continue;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       int lo, n, b0;
       orbit_nodes<2>(P.x[a * P.np + i], P.dt * P.vb[a * P.np + i], G.invH[a], lo, n, b0);
       const int raw = lo - s_ref[a];
       // particle frame -> chunk frame -> tile
-      sink.o[a] = min_image(raw, G.n[a]) - raw - s_ref[a] - tlo[a];
+      tile.o[a] = min_image(raw, G.n[a]) - raw - s_ref[a] - tlo[a];
     }
-    push_adjoint(P, i, sink);
+    push_adjoint(P, i, tile);
   }
   __syncthreads();
-  if (!use_tile) return;
-  const GlobalAdjSink glob{&P};
   for (int t = threadIdx.x; t < nt; t += kBlock) {
-    const int cz = t % dim[2], cy = (t / dim[2]) % dim[1], cx = t / (dim[1] * dim[2]);
-    const int64_t g = node_index(G, s_ref[0] + tlo[0] + cx, s_ref[1] + tlo[1] + cy,
-                                 s_ref[2] + tlo[2] + cz);
+    int slot;
+    int64_t g;
+    box_node(t, slot, g);
 #pragma unroll
-    for (int comp = 0; comp < 9; ++comp) {
-      const double val = tile[9 * t + comp];
-      if (val != 0.0) unsafeAtomicAdd(glob.target(comp) + g, val);
+    for (int k = 0; k < 9; ++k) {
+      const double val = sum[slot + k];
+      if (val != 0.0) unsafeAtomicAdd(tile.global_sum(k) + g, val);
     }
   }
 }
@@ -509,7 +578,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_out(int64_t n3, const double
 void launch_particle_adjoint(hipStream_t s, const AdjParticleArgs& P, bool eta, bool mu) {
   if (P.np <= 0) return;
   if (eta)
-    k_push_adjoint_tiled<<<(unsigned)((P.np + kAdjChunk - 1) / kAdjChunk), kBlock, 0, s>>>(P);
+    k_push_adjoint_tiled<<<(unsigned)scatter_blocks(P.np, P.chunk, P.span), kBlock, 0, s>>>(P);
   if (mu) k_current_adjoint<<<blocks_for(P.np), kBlock, 0, s>>>(P);
 }
 

@@ -413,16 +413,11 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   if (ws_bytes) *ws_bytes = w.off + 256;
 }
 
-// Real output descriptors for the inverse transform of the step.
-RealIO gather_fields_out(ecpic_sim* S) {
-  RealIO io{};
-  for (int l = 0; l < 3; ++l) {
-    io.p[l] = S->gbuf + l;          // grad_h phi^{n+1/2}
-    io.stride[l] = kGbufStride;
-    io.p[3 + l] = S->gbuf + 6 + l;  // A^{n+1}
-    io.stride[3 + l] = kGbufStride;
-  }
-  return io;
+GatherOut gather_fields_out(ecpic_sim* S, bool both_levels) {
+  GatherOut o{};
+  o.gbuf = S->gbuf;
+  o.both_levels = both_levels;
+  return o;
 }
 
 RealIO soa_io(double* base, int64_t nc, int nb) {
@@ -515,12 +510,23 @@ ecpic_status sync_read(ecpic_sim* S, int first, int count) {
   return ECPIC_OK;
 }
 
-// forward transform of the 9 real fields in realbuf into spec[cur]; A^n into gbuf
-ecpic_status load_fields_from_realbuf(ecpic_sim* S) {
+// whether p is device memory that kernels on the current device can use in place
+bool on_device(const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();  // ordinary host memory
+    return false;
+  }
+  int dev = -1;
+  return at.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && at.device == dev;
+}
+
+// forward transform of 9 real device fields into spec[cur]; A^n into gbuf
+ecpic_status load_fields(ecpic_sim* S, const double* fields) {
   const int64_t nc = S->G.ncell;
-  RealIO in = soa_io(S->realbuf, nc, 9);
-  fft3_forward(S->stream, S->G, 9, S->spec[S->cur], &in, nullptr, twp(S), S->sc);
-  launch_set_A0(S->stream, nc, S->realbuf + 2 * nc, S->gbuf);
+  const RealIO in = soa_io(const_cast<double*>(fields), nc, 9);
+  fft3_forward(S->stream, S->G, 9, S->spec[S->cur], in, twp(S), S->sc);
+  launch_set_A0(S->stream, nc, fields + 2 * nc, S->gbuf);
   HIPCHK(hipGetLastError());
   return ECPIC_OK;
 }
@@ -599,9 +605,8 @@ ecpic_status check_adjoint_config(const ecpic_config* cfg) {
 // (the adjoint of J given the adjoint of its forward transform); lJh is used up
 void current_adjoint(ecpic_sim* S, const AdjWs& A) {
   const int64_t nc = S->G.ncell;
-  launch_spec_copy(S->stream, 3 * nc, A.lJh, A.lJh, S->q / S->G.dV);
   RealIO o = soa_io(A.mu, nc, 3);
-  fft3_inverse(S->stream, S->G, 3, A.lJh, &o, twp(S));
+  fft3_inverse(S->stream, S->G, 3, A.lJh, A.lJh, o, twp(S), S->q / S->G.dV);
 }
 
 }  // namespace
@@ -709,13 +714,13 @@ ecpic_status init_state(ecpic_sim* S, const double* x, const double* v) {
   if (np > 0) {  // through the iterate buffers into the store (x wrapped; v^{-1} = v^0)
     HIPCHK(hipMemcpyAsync(S->vit, x, sizeof(double) * 3 * np, hipMemcpyHostToDevice, S->stream));
     HIPCHK(hipMemcpyAsync(S->vnew, v, sizeof(double) * 3 * np, hipMemcpyHostToDevice, S->stream));
+    launch_iota(S->stream, np, S->id);
     on_store(S, [&](auto& st, auto&) {
-      launch_import(S->stream, S->pp(), st, 0, S->vit);
-      launch_import(S->stream, S->pp(), st, 1, S->vnew);
-      launch_import(S->stream, S->pp(), st, 2, S->vnew);
+      launch_import(S->stream, S->pp(), st, 0, S->id, S->vit);
+      launch_import(S->stream, S->pp(), st, 1, S->id, S->vnew);
+      launch_import(S->stream, S->pp(), st, 2, S->id, S->vnew);
     });
   }
-  launch_iota(S->stream, np, S->id);
   // rho^0: point-shape deposit, transformed; then the Poisson solve
   launch_fill(S->stream, nc, S->realbuf, 0.0);
   on_store(S, [&](auto& st, auto&) {
@@ -728,7 +733,7 @@ ecpic_status init_state(ecpic_sim* S, const double* x, const double* v) {
   in.p[0] = S->realbuf;
   in.stride[0] = 1;
   S->cur = 0;
-  fft3_forward(S->stream, S->G, 1, S->spec[0] + 8 * nc, &in, nullptr, twp(S), S->sc);
+  fft3_forward(S->stream, S->G, 1, S->spec[0] + 8 * nc, in, twp(S), S->sc);
   launch_poisson_init(S->stream, S->fp(), S->spec[0]);
   launch_fill(S->stream, kGbufStride * nc, S->gbuf, 0.0);
   launch_fill(S->stream, 3 * nc, S->Jb[0], 0.0);
@@ -821,7 +826,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   const StepParams P = S->pp();
   const FieldParams F = S->fp();
   hipStream_t s = S->stream;
-  RealIO gout = gather_fields_out(S);
+  const GatherOut gout = gather_fields_out(S, false);
   double2* cur = S->spec[S->cur];
   double2* nxt = S->spec[1 - S->cur];
 
@@ -849,7 +854,6 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     on_store(S, [&](auto& st, auto&) { launch_extrapolate(s, S->np, st, S->vit, S->vbar); });
   const CurrentOut cout{nullptr, S->Jfix, S->fix_scale};
   const double fix_unit = S->q / S->G.dV / S->fix_scale;
-  const bool fused = fused_field_solve_fits(S->G);
   launch_reset_slots(s, S->sc, S_PIECES, 1);
   int p = 0, jcur = 1 - S->jlast;
   if (!S->jclean && !S->mixed()) launch_fill(s, 3 * nc, S->Jb[jcur], 0.0);  // after a failed step
@@ -902,15 +906,8 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     // pass's J, cleared in FP64), continuity + CN, inverse transform of
     // grad phi^{n+1/2} and A^{n+1} into the gather buffer
     double* jclear = S->mixed() ? nullptr : Jprev;
-    if (fused) {
-      field_solve_fused(s, F, J, p >= 1 ? Jprev : nullptr, jclear, cur, nxt, S->Jh, S->batch, gout,
-                        twp(S), S->sc);
-    } else {
-      RealIO jin = soa_io(J, nc, 3);
-      fft3_forward(s, S->G, 3, S->Jh, &jin, p >= 1 ? Jprev : nullptr, twp(S), S->sc, jclear);
-      launch_cn_update(s, F, cur, S->Jh, nxt, S->batch, S->sc);
-      fft3_inverse(s, S->G, 6, S->batch, &gout, twp(S));
-    }
+    field_solve(s, F, soa_io(J, nc, 3), p >= 1 ? Jprev : nullptr, jclear, cur, nxt, S->Jh, S->batch,
+                gout, twp(S), S->sc);
     if (prof_g) HIPCHK(hipEventRecord(S->ev[2], s));
     on_store(S, [&](auto& st, auto&) {  // v^{n+1,p+1}
       launch_gather_push(s, r, P, st, S->vit, S->vnew, S->vbar, S->gbuf, S->gwork, S->sc, prev,
@@ -924,8 +921,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     }
     if (mk >= 2) launch_anderson_dots(s, mk, n3, av, S->sc);
     {
-      const FinishJob jobs[7] = {{P_CN, fused ? cn_pencil_blocks(S->G) : (int)mesh_blocks(nc), 3,
-                                  S_JE},
+      const FinishJob jobs[7] = {{P_CN, cn_pencil_blocks(S->G), 3, S_JE},
                                  {0, 0, 1, S_DJMAX, F_SPREAD_MAX},
                                  {P_JS, (int)scatter_blocks(S->np, P.chunk, P.span), 1, S_JS},
                                  {0, 0, 2, S_DVMAX, F_SPREAD_MAX},
@@ -1001,10 +997,9 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   // consistency sweep of the accepted iterate (its orbit, current and fields)
   if (prof) HIPCHK(hipEventRecord(S->ev[0], s));
   if (S->cfg.diagnostics) {
-    launch_reset_slots(s, S->sc, S_RAMAX, 2);
     launch_half_U(s, S->G, cur, nxt, S->batch);
     RealIO uo = soa_io(S->Uhalf, nc, 3);
-    fft3_inverse(s, S->G, 3, S->batch, &uo, twp(S));
+    fft3_inverse(s, S->G, 3, S->batch, S->batch, uo, twp(S));
     on_store(S, [&](auto& st, auto&) {
       launch_sweep(s, r, P, st, S->vit, S->gbuf, S->Uhalf, S->sc);
     });
@@ -1016,13 +1011,14 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   });
   if (S->np <= 0) {
     launch_reset_slots(s, S->sc, S_K, 2);
-    launch_reset_slots(s, S->sc, S_WORK, 2);
+    launch_reset_slots(s, S->sc, S_WORK, 4);
   }
   launch_accept_A(s, nc, S->gbuf);
   if (S->np > 0) {
-    const FinishJob jobs[2] = {{P_K, (int)particle_blocks(S->np), 2, S_K},
-                               {P_SWEEP, (int)particle_blocks(S->np), 2, S_WORK}};
-    launch_finish(s, S->sc, jobs, S->cfg.diagnostics ? 2 : 1);
+    const FinishJob jobs[3] = {{P_K, (int)particle_blocks(S->np), 2, S_K},
+                               {P_SWEEP, (int)particle_blocks(S->np), 2, S_WORK},
+                               {0, 0, 2, S_RAMAX, F_SPREAD_MAX}};
+    launch_finish(s, S->sc, jobs, S->cfg.diagnostics ? 3 : 1);
   }
   if (prof) HIPCHK(hipEventRecord(S->ev[2], s));
   S->cur = 1 - S->cur;
@@ -1082,16 +1078,10 @@ ecpic_status ecpic_field_solve(ecpic_sim* S, const double* J_dev) {
                           hipMemcpyDeviceToDevice, s));
     J = S->Jb[S->jlast];
   }
-  RealIO jin = soa_io(const_cast<double*>(J), nc, 3);
-  double2* cur = S->spec[S->cur];
-  double2* nxt = S->spec[1 - S->cur];
-  fft3_forward(s, S->G, 3, S->Jh, &jin, nullptr, twp(S), S->sc);
-  launch_cn_update(s, S->fp(), cur, S->Jh, nxt, S->batch, S->sc);
-  RealIO gout = gather_fields_out(S);
-  fft3_inverse(s, S->G, 6, S->batch, &gout, twp(S));
-  launch_accept_A(s, nc, S->gbuf);
+  field_solve(s, S->fp(), soa_io(const_cast<double*>(J), nc, 3), nullptr, nullptr, S->spec[S->cur],
+              S->spec[1 - S->cur], S->Jh, S->batch, gather_fields_out(S, true), twp(S), S->sc);
   {
-    const FinishJob job = {P_CN, (int)mesh_blocks(nc), 3, S_JE};
+    const FinishJob job = {P_CN, cn_pencil_blocks(S->G), 3, S_JE};
     launch_finish(s, S->sc, &job, 1);
   }
   S->cur = 1 - S->cur;
@@ -1109,15 +1099,15 @@ ecpic_status ecpic_energy_diagnostics(ecpic_sim* S, ecpic_energy* out) {
   if (!S->initialized) return fail(ECPIC_ESTATE, "diagnostics before init_particles/set_state");
   const int64_t nc = S->G.ncell;
   hipStream_t s = S->stream;
-  launch_reset_slots(s, S->sc, S_GMAX, 2);
   launch_constraint_spectra(s, S->fp(), S->spec[S->cur], S->batch, S->sc);
   RealIO o = soa_io(S->realbuf, nc, 2);
-  fft3_inverse(s, S->G, 2, S->batch, &o, twp(S));
+  fft3_inverse(s, S->G, 2, S->batch, S->batch, o, twp(S));
   launch_constraint_norms(s, nc, S->realbuf, S->realbuf + nc, S->sc);
   {
-    const FinishJob jobs[2] = {{P_W, (int)mesh_blocks(nc), 1, S_WCUR},
-                               {P_NORM, (int)mesh_blocks(nc), 2, S_GL2}};
-    launch_finish(s, S->sc, jobs, 2);
+    const FinishJob jobs[3] = {{P_W, (int)mesh_blocks(nc), 1, S_WCUR},
+                               {P_NORM, (int)mesh_blocks(nc), 2, S_GL2},
+                               {0, 0, 2, S_GMAX, F_SPREAD_MAX}};
+    launch_finish(s, S->sc, jobs, 3);
   }
   HIPCHK(hipGetLastError());
   ecpic_status st = sync_read(S, 0, S_NSLOTS);
@@ -1138,23 +1128,25 @@ ecpic_status ecpic_get_state(ecpic_sim* S, double* x, double* v, double* vprev, 
   if (!S) return fail(ECPIC_EINVAL, "null simulation");
   const int64_t np = S->np, nc = S->G.ncell;
   hipStream_t s = S->stream;
-  if (np > 0) {  // store -> FP64 (stored order) -> caller order, through the iterate buffers
+  if (np > 0) {  // store -> FP64 in the caller's order, staged in the iterate buffer for the host
     double* dst[3] = {x, v, vprev};
     for (int k = 0; k < 3; ++k) {
       if (!dst[k]) continue;
-      on_store(S, [&](auto& st, auto&) { launch_export(s, S->pp(), st, k, S->vnew); });
-      launch_to_caller(s, np, S->id, S->vnew, S->vit);
+      double* to = on_device(dst[k]) ? dst[k] : S->vit;
+      on_store(S, [&](auto& st, auto&) { launch_export(s, S->pp(), st, k, S->id, to); });
       HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(dst[k], S->vit, sizeof(double) * 3 * np, hipMemcpyDefault, s));
+      if (to == dst[k]) continue;
+      HIPCHK(hipMemcpyAsync(dst[k], to, sizeof(double) * 3 * np, hipMemcpyDefault, s));
       HIPCHK(hipStreamSynchronize(s));
     }
   }
   if (fields) {
-    launch_spec_copy(s, 9 * nc, S->spec[S->cur], S->batch, 1.0 / (double)nc);
-    RealIO o = soa_io(S->realbuf, nc, 9);
-    fft3_inverse(s, S->G, 9, S->batch, &o, twp(S));
+    double* to = on_device(fields) ? fields : S->realbuf;
+    const RealIO o = soa_io(to, nc, 9);
+    fft3_inverse(s, S->G, 9, S->spec[S->cur], S->batch, o, twp(S), 1.0 / (double)nc);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(fields, S->realbuf, sizeof(double) * 9 * nc, hipMemcpyDefault, s));
+    if (to != fields)
+      HIPCHK(hipMemcpyAsync(fields, to, sizeof(double) * 9 * nc, hipMemcpyDefault, s));
   }
   HIPCHK(hipStreamSynchronize(s));
   return ECPIC_OK;
@@ -1174,15 +1166,22 @@ ecpic_status ecpic_set_state(ecpic_sim* S, const double* x, const double* v, con
     const double* src[3] = {x, v, vprev};
     for (int k = 0; k < 3; ++k) {
       if (!src[k]) continue;
-      HIPCHK(hipMemcpyAsync(S->vit, src[k], sizeof(double) * 3 * np, hipMemcpyDefault, s));
-      launch_from_caller(s, np, S->id, S->vit, S->vnew);
-      on_store(S, [&](auto& st, auto&) { launch_import(s, S->pp(), st, k, S->vnew); });
+      const double* from = src[k];
+      if (!on_device(from)) {
+        HIPCHK(hipMemcpyAsync(S->vit, from, sizeof(double) * 3 * np, hipMemcpyDefault, s));
+        from = S->vit;
+      }
+      on_store(S, [&](auto& st, auto&) { launch_import(s, S->pp(), st, k, S->id, from); });
       HIPCHK(hipGetLastError());
     }
   }
   if (fields) {
-    HIPCHK(hipMemcpyAsync(S->realbuf, fields, sizeof(double) * 9 * nc, hipMemcpyDefault, s));
-    ecpic_status st = load_fields_from_realbuf(S);
+    const double* from = fields;
+    if (!on_device(from)) {
+      HIPCHK(hipMemcpyAsync(S->realbuf, from, sizeof(double) * 9 * nc, hipMemcpyDefault, s));
+      from = S->realbuf;
+    }
+    ecpic_status st = load_fields(S, from);
     if (st != ECPIC_OK) return st;
   } else if (!S->initialized) {
     for (int b = 0; b < 2; ++b) launch_spec_copy(s, 9 * nc, S->spec[b], S->spec[b], 0.0);
@@ -1458,18 +1457,18 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
     Fp64Store view{const_cast<double*>(x), const_cast<double*>(v), nullptr};
     launch_scatter(s, 2, P, view, w, nullptr, CurrentOut{A.J, nullptr, 0.0}, S->sc);
   }
-  RealIO jin = soa_io(A.J, nc, 3);
-  fft3_forward(s, G, 3, A.Jh, &jin, nullptr, twp(S), S->sc);
-  RealIO fin = soa_io(const_cast<double*>(fields), nc, 9);
-  fft3_forward(s, G, 9, A.Fh, &fin, nullptr, twp(S), S->sc);
-  launch_cn_update(s, FP, A.Fh, A.Jh, A.F1h, A.inv, S->sc);
-  RealIO gout = soa_io(A.gfield, nc, 6);
-  fft3_inverse(s, G, 6, A.inv, &gout, twp(S));
+  const RealIO fin = soa_io(const_cast<double*>(fields), nc, 9);
+  fft3_forward(s, G, 9, A.Fh, fin, twp(S), S->sc);
+  GatherOut gout{};
+  gout.io = soa_io(A.gfield, nc, 6);
+  field_solve(s, FP, soa_io(A.J, nc, 3), nullptr, nullptr, A.Fh, A.F1h, A.Jh, A.inv, gout, twp(S),
+              S->sc);
   const double* gphi = A.gfield;
   const double* A1r = A.gfield + 3 * nc;
   const double* A0r = fields + 2 * nc;
 
-  AdjParticleArgs PA{G, dt, S->q / S->m, np, x, A.vb, A.xi, A.mu, gphi, A0r, A1r,
+  const int span = auto_span(np, nc);
+  AdjParticleArgs PA{G, dt, S->q / S->m, np, auto_chunk(np, span), span, x, A.vb, A.xi, A.mu, gphi, A0r, A1r,
                      A.lx, A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.red + 2};
   launch_fill(s, 4, A.red, 0.0);
 
@@ -1477,8 +1476,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   launch_fill(s, 2 * 9 * nc, reinterpret_cast<double*>(A.lcur), 0.0);
   if (lF1) {
     RealIO l1in = soa_io(const_cast<double*>(lF1), nc, 9);
-    fft3_forward(s, G, 9, A.l1, &l1in, nullptr, twp(S), S->sc);
-    launch_spec_copy(s, 9 * nc, A.l1, A.l1, 1.0 / (double)nc);
+    fft3_forward(s, G, 9, A.l1, l1in, twp(S), S->sc, 1.0 / (double)nc);
   }
   launch_cn_adjoint(s, FP, lF1 ? A.l1 : nullptr, nullptr, A.lcur, A.lJh);
   current_adjoint(S, A);
@@ -1498,8 +1496,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
     PA.xi = A.xi;
     launch_particle_adjoint(s, PA, true, false);
     RealIO lgin = soa_io(A.lg_r, nc, 9);  // [grad phi, A^{n+1}, A^n]
-    fft3_forward(s, G, 9, A.lg, &lgin, nullptr, twp(S), S->sc);
-    launch_spec_copy(s, 9 * nc, A.lg, A.lg, 1.0 / (double)nc);
+    fft3_forward(s, G, 9, A.lg, lgin, twp(S), S->sc, 1.0 / (double)nc);
     launch_cn_adjoint(s, FP, nullptr, A.lg, nullptr, A.lJh);
     current_adjoint(S, A);
     launch_particle_adjoint(s, PA, false, true);
@@ -1522,7 +1519,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
       launch_to_caller(s, np, A.id, A.lx0s, lx0);
       launch_to_caller(s, np, A.id, A.lv0s, lv0);
       RealIO fo = soa_io(lF0, nc, 9);
-      fft3_inverse(s, G, 9, A.lcur, &fo, twp(S));
+      fft3_inverse(s, G, 9, A.lcur, A.lcur, fo, twp(S));
       break;
     }
     std::swap(A.xi, A.xn);
@@ -1597,13 +1594,11 @@ ecpic_status ecpic_field_energy_grad(ecpic_sim* S, double* lF) {
   launch_spec_copy(s, 3 * nc, S->batch, S->batch, S->G.dV / S->cfg.sigma1);
   launch_spec_copy(s, 3 * nc, S->batch + 3 * nc, S->batch + 3 * nc, S->G.dV / S->cfg.sigma2);
   RealIO eb = soa_io(S->realbuf, nc, 6);
-  fft3_inverse(s, S->G, 6, S->batch, &eb, twp(S));
-  fft3_forward(s, S->G, 6, S->batch, &eb, nullptr, twp(S), S->sc);
-  launch_spec_copy(s, 6 * nc, S->batch, S->batch, 1.0 / (double)nc);
+  fft3_inverse(s, S->G, 6, S->batch, S->batch, eb, twp(S));
+  fft3_forward(s, S->G, 6, S->batch, eb, twp(S), S->sc, 1.0 / (double)nc);
   launch_energy_adjoint(s, S->G, S->batch, S->batch);  // 6 -> 9 spectra in place
-  RealIO out = soa_io(S->realbuf, nc, 9);
-  fft3_inverse(s, S->G, 9, S->batch, &out, twp(S));
-  HIPCHK(hipMemcpyAsync(lF, S->realbuf, sizeof(double) * 9 * nc, hipMemcpyDeviceToDevice, s));
+  RealIO out = soa_io(lF, nc, 9);
+  fft3_inverse(s, S->G, 9, S->batch, S->batch, out, twp(S));
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return ECPIC_OK;

@@ -214,11 +214,13 @@ void launch_kinetic(hipStream_t s, const StepParams& P, const PS& st, Scratch sc
 template <class PS>
 void launch_deposit_rho(hipStream_t s, int r, const StepParams& P, const PS& st, CurrentOut out);
 // which: 0 = x (wrapped into [0, L) on import), 1 = v^n, 2 = v^{n-1};
-// src/dst are 3 x np doubles in stored order
+// src/dst are 3 x np doubles in the caller's order (id: stored -> caller index)
 template <class PS>
-void launch_import(hipStream_t s, const StepParams& P, const PS& st, int which, const double* src);
+void launch_import(hipStream_t s, const StepParams& P, const PS& st, int which, const int* id,
+                   const double* src);
 template <class PS>
-void launch_export(hipStream_t s, const StepParams& P, const PS& st, int which, double* dst);
+void launch_export(hipStream_t s, const StepParams& P, const PS& st, int which, const int* id,
+                   double* dst);
 // J = unit * Jfix (as signed integers), then Jfix = 0
 void launch_fixed_current(hipStream_t s, int64_t n, unsigned long long* Jfix, double* J,
                           double unit);
@@ -260,36 +262,34 @@ struct RealIO {
 };
 
 // 3D FFT of nb fields held as complex arrays data[b*ncell + g], z fastest.
-// forward: real input from `in` (may be nullptr for complex in-place), and
-// optionally max|in - prev| folded into S_DJMAX.  inverse: real part of the
-// result to `out` (nullptr keeps the complex result in place).
-// clear (optional): a real buffer laid out like prev, zeroed by the first pass
-void fft3_forward(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO* in,
-                  const double* prev, const double2* const* tw, Scratch sc,
-                  double* clear = nullptr);
-void fft3_inverse(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO* out,
-                  const double2* const* tw);
+// forward: real input, the spectrum times scale into data.
+// inverse: src times scale (src may be data, which is used up), real part of the
+// result to out.
+void fft3_forward(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO& in,
+                  const double2* const* tw, Scratch sc, double scale = 1.0);
+void fft3_inverse(hipStream_t s, const Grid& G, int nb, const double2* src, double2* data,
+                  const RealIO& out, const double2* const* tw, double scale = 1.0);
 
 struct FieldParams {
   Grid G;
   double dt, kappa, sigma1, sigma2;
 };
 
-// Continuity + CN update of every mode; writes the next spectral level, the
-// inverse-transform inputs [i k (phi0+phi1)/2, A1] / ncell, and S_JE, S_WNEXT,
-// S_DW.
-// The field solve of a Picard pass in three kernels (transforms along z and y
-// per x-plane, then x with the continuity + CN update per block of x-pencils,
-// then the inverse along y and z into the gather buffer); same results as
-// fft3_forward + launch_cn_update + fft3_inverse up to rounding.  Needs
-// ny nz <= 4096; the P_CN partial rows have cn_pencil_blocks(G) blocks.
-bool fused_field_solve_fits(const Grid& G);
+// Where a field solve puts grad_h phi^{n+1/2} and A^{n+1}: the gather buffer (with
+// both_levels A^{n+1} in its A^n slots too), or with gbuf null six real fields.
+struct GatherOut {
+  double* gbuf = nullptr;
+  bool both_levels = false;
+  RealIO io{};
+};
+// Continuity + CN update of every mode with the real current J: writes the next
+// spectral level, the gather fields, and the partial sums of S_JE, S_WNEXT and
+// S_DW (site P_CN, cn_pencil_blocks(G) rows); max|J - prev| into S_DJMAX if prev,
+// and clear (a real buffer laid out like prev) zeroed if given.
 int cn_pencil_blocks(const Grid& G);
-void field_solve_fused(hipStream_t s, const FieldParams& F, const double* J, const double* prev,
-                       double* clear, const double2* cur, double2* next, double2* Jh,
-                       double2* batch, const RealIO& out, const double2* const* tw, Scratch sc);
-void launch_cn_update(hipStream_t s, const FieldParams& F, const double2* cur, const double2* Jh,
-                      double2* next, double2* inv, Scratch sc);
+void field_solve(hipStream_t s, const FieldParams& F, const RealIO& J, const double* prev,
+                 double* clear, const double2* cur, double2* next, double2* Jh, double2* batch,
+                 const GatherOut& out, const double2* const* tw, Scratch sc);
 // (U0 + U1)/2 / ncell into inv[0..2]
 void launch_half_U(hipStream_t s, const Grid& G, const double2* cur, const double2* next,
                    double2* inv);
@@ -317,6 +317,7 @@ struct AdjParticleArgs {
   Grid G;
   double dt, qm;       // time step, q/m
   int64_t np;
+  int chunk, span;     // particles per block of the push terms, span of its lanes
   const double* x;     // x^n, 3 x np
   const double* vb;    // vbar of the converged iterate, 3 x np
   const double* xi;    // adjoint of the push output (eta = qm xi), 3 x np

@@ -19,98 +19,169 @@ namespace ecpic {
 
 namespace {
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 // i * k * a
 __device__ __forceinline__ double2 ik(double k, double2 a) { return make_double2(-k * a.y, k * a.x); }
 
+__device__ __forceinline__ int brev(int e, int logn) {
+  return (int)(__brev((unsigned)e) >> (32 - logn));
+}
+
+// w v, or conj(w) v, with the products rounded in a fixed order: the same bits
+// whichever kernel a transform runs in (in the mixed form the rounding of the
+// accepted velocities is keyed by the stored bits, down to transverse velocities
+// that are themselves rounding).
+template <bool CONJ>
+__device__ __forceinline__ double2 twiddle(double2 w, double2 v) {
+#pragma clang fp contract(off)
+  if (CONJ)
+    return make_double2(__builtin_fma(w.x, v.x, w.y * v.y), __builtin_fma(w.x, v.y, -(w.y * v.x)));
+  return make_double2(__builtin_fma(w.x, v.x, -(w.y * v.y)), __builtin_fma(w.y, v.x, w.x * v.y));
+}
+
+// LDS slot of point e of a run: one slot of padding every 8 points, so that
+// threads that hold 8 neighbouring points each, and bit-reversed writes, do not
+// share a bank
+__device__ __forceinline__ int pad8(int e) { return e + (e >> 3); }
+
+// Transforms of pencils of N = 2^logN points held in LDS: radix-2 decimation in
+// time on bit-reversed input, up to three stages at a time in registers (8
+// points per thread and LDS round trip, one barrier for the three).  Pencil p's
+// point e is at(p, e); count pencils (a power of two if ACROSS), all threads of
+// the block; tw: the table exp(-2 pi i t / N), t < N/2 (in LDS or global memory),
+// conjugated for INV.  Neighbouring threads take neighbouring groups of one
+// pencil, or with ACROSS the same group of neighbouring pencils.  Ends with a
+// barrier.
+template <bool INV, bool ACROSS, int S, class At>
+__device__ __forceinline__ void fft_stages(int N, int logN, int count, int loghs,
+                                           const double2* tw, At&& at) {
+  constexpr int R = 1 << S;
+  const int logper = logN - S, per = 1 << logper;  // groups of R points per pencil
+  const int hs = 1 << loghs, logcount = 31 - __clz(count);
+  for (int u = threadIdx.x; u < count * per; u += blockDim.x) {
+    const int p = ACROSS ? u & (count - 1) : u >> logper;
+    const int j = ACROSS ? u >> logcount : u & (per - 1);
+    const int pos = j & (hs - 1), i0 = ((j >> loghs) << (loghs + S)) + pos;
+    double2 v[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m) v[m] = at(p, i0 + m * hs);
+#pragma unroll
+    for (int st = 0; st < S; ++st) {
+      const int h = 1 << st;
+#pragma unroll
+      for (int k = 0; k < h; ++k) {  // the twiddle of stage loghs + st at pos + k hs
+        const double2 w = tw[(pos + k * hs) << (logN - 1 - loghs - st)];
+#pragma unroll
+        for (int m = k; m < R; m += 2 * h) {
+          const double2 x = v[m], y = twiddle<INV>(w, v[m + h]);
+          v[m] = cadd(x, y);
+          v[m + h] = csub(x, y);
+        }
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < R; ++m) at(p, i0 + m * hs) = v[m];
+  }
+  __syncthreads();
+}
+
+template <bool INV, bool ACROSS, class At>
+__device__ __forceinline__ void fft_pencils(int N, int logN, int count, const double2* tw,
+                                            At&& at) {
+  int done = 0;
+  while (logN - done >= 5 || logN - done == 3) {
+    fft_stages<INV, ACROSS, 3>(N, logN, count, done, tw, at);
+    done += 3;
+  }
+  while (logN - done >= 2) {  // 2 or 4 stages left
+    fft_stages<INV, ACROSS, 2>(N, logN, count, done, tw, at);
+    done += 2;
+  }
+  if (logN - done == 1) fft_stages<INV, ACROSS, 1>(N, logN, count, done, tw, at);
+}
+
 struct FftPass {
+  const double2* src;  // complex input of MODE 0 and 2 (may be data), times scale
+  double scale;
   double2* data;
   const double2* tw;  // exp(-2 pi i t / N), t < N/2
   int64_t ncell;
   int64_t stride;     // distance between consecutive elements of a pencil
   int64_t npb;        // pencils per batch field = ncell / N
   int64_t npencils;   // nb * npb
-  int N, logN;
-  double sgn;         // -1 forward, +1 inverse (sign of the exponent)
+  int N, logN, logS;  // logS = log2(stride)
+  int logpts;         // log2 of the points per block
   RealIO io;          // real input (forward first pass) or output (inverse last pass)
   const double* prev; // optional: max |in - prev| -> S_DJMAX (a spread slot)
   double* clear;      // optional: real buffer (same layout as prev) zeroed by the pass
   Scratch sc;
 };
 
-// MODE 0: complex in place; 1: real input -> complex; 2: complex -> real output.
-// Each block transforms 256 / (N/2) pencils held in LDS; one thread per
-// butterfly; input in bit-reversed order, decimation in time.
-template <int MODE>
+// MODE 0: complex to complex; 1: real input -> complex; 2: complex -> real output.
+// A block holds 2^logpts points, P = 2^logpts / N neighbouring pencils: 2048, so
+// that a strided pass moves runs of at least 8 points (128 bytes; with 512 points
+// per block the y and x passes at 128^3 moved 64-byte runs at 2.5 TB/s), or 512
+// where 2048 would leave compute units without a block (launch_pass).
+constexpr int kFftPoints = 2048;
+
+template <int MODE, bool INV>
 __global__ __launch_bounds__(kBlock) void k_fft(FftPass A) {
-  __shared__ double2 buf[2 * kBlock];
-  const int N = A.N, half = N >> 1, P = kBlock / half;
-  const int t = threadIdx.x;
-  int pl, j;
-  if (A.stride == 1) {
-    pl = t / half;
-    j = t % half;
-  } else {
-    pl = t % P;
-    j = t / P;
-  }
-  const int64_t pencil = (int64_t)blockIdx.x * P + pl;
-  const bool active = pencil < A.npencils;
-  int64_t b = 0, off = 0;
-  if (active) {
-    b = pencil / A.npb;
-    const int64_t pin = pencil % A.npb;
-    const int64_t outer = pin / A.stride, inner = pin % A.stride;
-    off = outer * N * A.stride + inner;
-  }
-  double2* lds = buf + pl * N;
-  double dmax = 0.0;
-  if (active) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = j + h * half;
-      const int64_t g = off + e * A.stride;
-      double2 val;
-      if constexpr (MODE == 1) {
-        const double re = A.io.p[b][g * A.io.stride[b]];
-        if (A.prev) dmax = fmax(dmax, fabs(re - A.prev[b * A.ncell + g]));
-        if (A.clear) A.clear[b * A.ncell + g] = 0.0;  // after prev was read (same element)
-        val = make_double2(re, 0.0);
-      } else {
-        val = A.data[b * A.ncell + g];
-      }
-      lds[__brev((unsigned)e) >> (32 - A.logN)] = val;
+  // P runs of N + N / 8 + 1 slots, P <= kFftPoints / 4
+  __shared__ double2 buf[kFftPoints + kFftPoints / 8 + kFftPoints / 4];
+  __shared__ double2 tw[128];
+  const int N = A.N, logP = A.logpts - A.logN, P = 1 << logP, ld = pad8(N) + 1;
+  const int points = 1 << A.logpts;
+  for (int t = threadIdx.x; t < N / 2; t += kBlock) tw[t] = A.tw[t];
+  const int64_t first = (int64_t)blockIdx.x << logP;
+  const int count = (int)min((int64_t)P, A.npencils - first);
+  const int lognpb = 63 - __clzll((unsigned long long)A.npb);
+  // element u of the block: pencil and position, neighbouring threads at
+  // neighbouring addresses
+  auto place = [&](int u, int& pl, int& e, int64_t& b, int64_t& g) {
+    if (A.stride == 1) {
+      pl = u >> A.logN;
+      e = u & (N - 1);
+    } else {
+      pl = u & (P - 1);
+      e = u >> logP;
     }
+    const int64_t pencil = first + pl;
+    b = pencil >> lognpb;
+    const int64_t pin = pencil & (A.npb - 1);
+    const int64_t outer = pin >> A.logS, inner = pin & (A.stride - 1);
+    g = (((outer << A.logN) + e) << A.logS) + inner;
+  };
+  double dmax = 0.0;
+  for (int u = threadIdx.x; u < points; u += kBlock) {
+    int pl, e;
+    int64_t b, g;
+    place(u, pl, e, b, g);
+    if (pl >= count) continue;
+    double2 val;
+    if constexpr (MODE == 1) {
+      const double re = A.io.p[b][g * A.io.stride[b]];
+      if (A.prev) dmax = fmax(dmax, fabs(re - A.prev[b * A.ncell + g]));
+      if (A.clear) A.clear[b * A.ncell + g] = 0.0;  // after prev was read (same element)
+      val = make_double2(re, 0.0);
+    } else {
+      val = cscale(A.src[b * A.ncell + g], A.scale);
+    }
+    buf[pl * ld + pad8(brev(e, A.logN))] = val;
   }
   __syncthreads();
-  for (int hs = 1; hs < N; hs <<= 1) {
-    if (active) {
-      const int pos = j % hs;
-      const int i0 = (j / hs) * 2 * hs + pos, i1 = i0 + hs;
-      double2 w = A.tw[pos * (half / hs)];  // exp(-2 pi i pos / (2 hs))
-      if (A.sgn > 0.0) w.y = -w.y;           // inverse: conjugate twiddle
-      const double2 a = lds[i0];
-      const double2 bb = cmul(lds[i1], w);
-      lds[i0] = cadd(a, bb);
-      lds[i1] = csub(a, bb);
-    }
-    __syncthreads();
-  }
-  if (active) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = j + h * half;
-      const int64_t g = off + e * A.stride;
-      if constexpr (MODE == 2)
-        A.io.p[b][g * A.io.stride[b]] = lds[e].x;
-      else
-        A.data[b * A.ncell + g] = lds[e];
-    }
+  fft_pencils<INV, false>(N, A.logN, count, tw,
+                          [&](int p, int e) -> double2& { return buf[p * ld + pad8(e)]; });
+  for (int u = threadIdx.x; u < points; u += kBlock) {
+    int pl, e;
+    int64_t b, g;
+    place(u, pl, e, b, g);
+    if (pl >= count) continue;
+    if constexpr (MODE == 2)
+      A.io.p[b][g * A.io.stride[b]] = buf[pl * ld + pad8(e)].x;
+    else
+      A.data[b * A.ncell + g] = buf[pl * ld + pad8(e)];
   }
   if constexpr (MODE == 1) {
     if (A.prev) {
@@ -127,9 +198,9 @@ __device__ __forceinline__ double ktil(int m, int N, double L) {
 }
 
 __device__ __forceinline__ void mode_k(const Grid& G, int64_t g, double* k) {
-  const int iz = (int)(g % G.n[2]);
-  const int iy = (int)((g / G.n[2]) % G.n[1]);
-  const int ix = (int)(g / ((int64_t)G.n[2] * G.n[1]));
+  const int iz = (int)g & G.mask[2];
+  const int iy = ((int)g >> G.shy) & G.mask[1];
+  const int ix = (int)g >> G.shx;
   k[0] = ktil(ix, G.n[0], G.L[0]);
   k[1] = ktil(iy, G.n[1], G.L[1]);
   k[2] = ktil(iz, G.n[2], G.L[2]);
@@ -164,15 +235,6 @@ __device__ __forceinline__ double mode_energy(const double* k, double2 phi, cons
 //   phi1 = phi0 + a (psi0 + psi1),  a = dt/2, w^2 = kappa^2 |k|^2,
 // and (A_l, U_l) likewise with sigma2 J_l.  The closed form is the exact
 // inverse of the 2x2 CN system of each (value, rate) pair.
-struct CNArgs {
-  FieldParams F;
-  const double2* cur;
-  const double2* Jh;
-  double2* next;
-  double2* inv;
-  Scratch sc;
-};
-
 // One mode: c = the 9 level-n spectra (field order of a level), J = the 3
 // current spectra; out = the 9 level-(n+1) spectra, inv = the inverse-transform
 // inputs [i k phi^{n+1/2} (3), A^{n+1} (3)] / ncell, sums = JE, W^{n+1} and
@@ -259,28 +321,6 @@ __device__ __forceinline__ void cn_mode(const FieldParams& F, const double* k, c
   sums[0] = je * f;
   sums[1] = e1 * f;
   sums[2] = de * f;
-}
-
-__global__ __launch_bounds__(kBlock) void k_cn(CNArgs C) {
-  const Grid& G = C.F.G;
-  const int64_t nc = G.ncell;
-  const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  double sums[3] = {0.0, 0.0, 0.0};  // JE, W^{n+1}, W^{n+1} - W^n
-  if (g < nc) {
-    double k[3];
-    mode_k(G, g, k);
-    double2 J[3], c[9], out[9], inv[6];
-#pragma unroll
-    for (int l = 0; l < 3; ++l) J[l] = C.Jh[l * nc + g];
-#pragma unroll
-    for (int f = 0; f < 9; ++f) c[f] = ld(C.cur, f, nc, g);
-    cn_mode(C.F, k, J, c, out, inv, sums);
-#pragma unroll
-    for (int f = 0; f < 9; ++f) C.next[f * nc + g] = out[f];
-#pragma unroll
-    for (int f = 0; f < 6; ++f) C.inv[f * nc + g] = inv[f];
-  }
-  block_partials<3>(sums, C.sc.region(P_CN));  // -> S_JE, S_WNEXT, S_DW
 }
 
 __global__ __launch_bounds__(kBlock) void k_half_U(Grid G, const double2* cur, const double2* next,
@@ -386,8 +426,11 @@ __global__ __launch_bounds__(kBlock) void k_norms(int64_t nc, const double* gf, 
     gv = gf[g];
     rv = rf[g];
   }
-  block_max_to(fabs(gv), sc.red + S_GMAX);
-  block_max_to(fabs(rv), sc.red + S_RMAX);
+  const double gm = block_max(fabs(gv)), rm = block_max(fabs(rv));
+  if (threadIdx.x == 0) {
+    atomic_max_nonneg(sc.spread_copy(S_GMAX), gm);
+    atomic_max_nonneg(sc.spread_copy(S_RMAX), rm);
+  }
   double s[2] = {gv * gv, rv * rv};
   block_partials<2>(s, sc.region(P_NORM));  // -> S_GL2, S_RL2
 }
@@ -486,11 +529,13 @@ int ilog2(int n) {
 }
 
 // One pass along `axis` over nb batch fields.
-template <int MODE>
-void fft_pass(hipStream_t s, const Grid& G, int nb, double2* data, int axis, double sgn,
+template <int MODE, bool INV>
+void fft_pass(hipStream_t s, const Grid& G, int nb, const double2* src, double2* data, int axis,
               const double2* tw, const RealIO* io, const double* prev, double* clear,
-              const Scratch& sc) {
-  FftPass A;
+              const Scratch& sc, double scale = 1.0) {
+  FftPass A{};
+  A.src = src;
+  A.scale = scale;
   A.data = data;
   A.tw = tw;
   A.ncell = G.ncell;
@@ -499,56 +544,43 @@ void fft_pass(hipStream_t s, const Grid& G, int nb, double2* data, int axis, dou
   int64_t stride = 1;
   for (int a = axis + 1; a < 3; ++a) stride *= G.n[a];
   A.stride = stride;
+  A.logS = ilog2((int)stride);
   A.npb = G.ncell / A.N;
   A.npencils = (int64_t)nb * A.npb;
-  A.sgn = sgn;
   if (io) A.io = *io;
-  else
-    for (int b = 0; b < kMaxBatch; ++b) {
-      A.io.p[b] = nullptr;
-      A.io.stride[b] = 1;
-    }
   A.prev = prev;
   A.clear = clear;
   A.sc = sc;
-  const int P = kBlock / (A.N / 2);
+  // (16^3, 9 fields: 72 blocks of 512 points 5.6 us, 18 of 2048 7.4 us)
+  A.logpts = nb * G.ncell >= (int64_t)512 * kFftPoints ? 11 : 9;
+  const int P = (1 << A.logpts) / A.N;
   const unsigned nblk = (unsigned)((A.npencils + P - 1) / P);
-  k_fft<MODE><<<nblk, kBlock, 0, s>>>(A);
+  k_fft<MODE, INV><<<nblk, kBlock, 0, s>>>(A);
 }
 
-// ---- fused field solve of a Picard pass -----------------------------------
-// Three kernels instead of seven: (1) per field and x-plane, the forward
-// transform along z and y of the real current in LDS (with max|J - J_prev|
-// and the clearing of J_prev); (2) per block of x-pencils, the forward
-// transform along x, the continuity + CN update of every mode of those
-// pencils, and the inverse transform along x of the six gather fields;
-// (3) per field and x-plane, the inverse transform along y and z with the real
-// part written to the gather buffer.  Four x-pencils per block: at 32^3
-// that is 256 blocks (16 pencils per block: 64 blocks, 23 us for the pencil
-// kernel alone; 4: 0.035 ms for the whole solve against 0.047 for seven
-// kernels).  Every 1-D transform is the radix-2
-// decimation in time of k_fft with bit-reversed LDS input; in a plane both
-// indices are bit-reversed at load, so the z and y stages run back to back.
+// ---- field solve ------------------------------------------------------------
+// Forward transform of the current along z and y, then per block of x-pencils the
+// forward transform along x, the continuity + CN update of every mode of those
+// pencils and the inverse transform along x of the six gather fields, then the
+// inverse along y and z into the gather buffer.  Where an x-plane fits LDS
+// (ny nz <= 4096) the two directions of a plane run back to back in one kernel
+// per field and plane (both indices bit-reversed at load): three kernels in all.
+// Four x-pencils per block: at 32^3 that is 256 blocks (16 pencils per block: 64
+// blocks, 23 us for the pencil kernel alone).  Three radix-2 stages per LDS round
+// trip against one: the pencil kernel 8.9 -> 7.1 us at 16x4x4, 18.2 -> 11.3 us at
+// 64x32x16, 13.4 -> 10.4 us at 32^3, 53.5 -> 42.4 us at 64^3.  At 128^3 the
+// separate x passes and CN kernel read and wrote 1.5 GB, the pencil kernel 0.9.
 constexpr int kPlaneMax = 4096;  // ny nz limit of the plane kernels (64 KB of LDS)
 
-__device__ __forceinline__ int brev(int e, int logn) {
-  return (int)(__brev((unsigned)e) >> (32 - logn));
-}
-
-__device__ __forceinline__ void butterfly(double2* lds, int i0, int i1, double2 w) {
-  const double2 a = lds[i0];
-  const double2 b = cmul(lds[i1], w);
-  lds[i0] = cadd(a, b);
-  lds[i1] = csub(a, b);
-}
+bool plane_fits(const Grid& G) { return G.n[1] * G.n[2] <= kPlaneMax; }
 
 struct PlaneArgs {
   Grid G;
   const double2* tw_y;  // exp(-2 pi i t / ny), t < ny/2
   const double2* tw_z;
   int logy, logz;
-  // forward: real SoA input (nb fields), optional prev / clear, complex output
-  const double* in;
+  // forward: real input (io), optional prev / clear (laid out like the fields one
+  // after the other), complex output
   const double* prev;
   double* clear;
   double2* cout;
@@ -562,8 +594,11 @@ struct PlaneArgs {
 // true: of the inverse transform (conjugate twiddles, real output).
 template <bool INVERSE>
 __global__ __launch_bounds__(kBlock) void k_fft_plane(PlaneArgs A) {
-  __shared__ double2 buf[kPlaneMax];
+  __shared__ double2 buf[kPlaneMax + kPlaneMax / 8];
+  __shared__ double2 tw_y[128], tw_z[128];
   const Grid& G = A.G;
+  for (int t = threadIdx.x; t < G.n[1] / 2; t += kBlock) tw_y[t] = A.tw_y[t];
+  for (int t = threadIdx.x; t < G.n[2] / 2; t += kBlock) tw_z[t] = A.tw_z[t];
   const int ny = G.n[1], nz = G.n[2], plane = ny * nz, nx = G.n[0];
   const int b = blockIdx.x / nx, ix = blockIdx.x % nx;
   const int64_t base = (int64_t)ix * plane, fo = (int64_t)b * G.ncell;
@@ -575,41 +610,27 @@ __global__ __launch_bounds__(kBlock) void k_fft_plane(PlaneArgs A) {
     if constexpr (INVERSE) {
       v = A.cin[fo + g];
     } else {
-      const double re = A.in[fo + g];
+      const double re = A.io.p[b][g * A.io.stride[b]];
       if (A.prev) dmax = fmax(dmax, fabs(re - A.prev[fo + g]));
       if (A.clear) A.clear[fo + g] = 0.0;  // after prev was read (same element)
       v = make_double2(re, 0.0);
     }
-    buf[(brev(iy, A.logy) << A.logz) | brev(iz, A.logz)] = v;
+    buf[pad8((brev(iy, A.logy) << A.logz) | brev(iz, A.logz))] = v;
   }
   __syncthreads();
-  const int hz = nz >> 1, hy = ny >> 1;
-  for (int hs = 1; hs < nz; hs <<= 1) {  // along z: rows of nz
-    for (int u = threadIdx.x; u < ny * hz; u += kBlock) {
-      const int row = u / hz, j = u - row * hz, pos = j % hs;
-      const int i0 = (j / hs) * 2 * hs + pos;
-      double2 w = A.tw_z[pos * (hz / hs)];
-      if (INVERSE) w.y = -w.y;
-      butterfly(buf + row * nz, i0, i0 + hs, w);
-    }
-    __syncthreads();
-  }
-  for (int hs = 1; hs < ny; hs <<= 1) {  // along y: columns of ny, stride nz
-    for (int u = threadIdx.x; u < hy * nz; u += kBlock) {
-      const int col = u & (nz - 1), j = u >> A.logz, pos = j % hs;
-      const int i0 = (j / hs) * 2 * hs + pos;
-      double2 w = A.tw_y[pos * (hy / hs)];
-      if (INVERSE) w.y = -w.y;
-      butterfly(buf, i0 * nz + col, (i0 + hs) * nz + col, w);
-    }
-    __syncthreads();
-  }
+  // along z: rows of nz; along y: columns of ny, nz apart
+  fft_pencils<INVERSE, false>(nz, A.logz, ny, tw_z, [&](int p, int e) -> double2& {
+    return buf[pad8((p << A.logz) + e)];
+  });
+  fft_pencils<INVERSE, true>(ny, A.logy, nz, tw_y, [&](int p, int e) -> double2& {
+    return buf[pad8((e << A.logz) + p)];
+  });
   for (int e = threadIdx.x; e < plane; e += kBlock) {
     const int64_t g = base + e;
     if constexpr (INVERSE)
-      A.io.p[b][g * A.io.stride[b]] = buf[e].x;
+      A.io.p[b][g * A.io.stride[b]] = buf[pad8(e)].x;
     else
-      A.cout[fo + g] = buf[e];
+      A.cout[fo + g] = buf[pad8(e)];
   }
   if constexpr (!INVERSE) {
     if (A.prev) {
@@ -630,80 +651,131 @@ struct PencilArgs {
   Scratch sc;
 };
 
-constexpr int kPencilLds = 2 * kBlock + 16;  // npl * (nx + 1) <= 2 kBlock + npl, npl <= 16
+// slots of a field: npl runs of nx + nx / 8 + 1 points, npl nx <= 2 kBlock, npl <= 4
+constexpr int kXcds = 8;
+constexpr int kPencilLds = 2 * kBlock + kBlock / 4 + 4;
 
 __global__ __launch_bounds__(kBlock) void k_cn_pencils(PencilArgs A) {
-  __shared__ double2 jb[3 * kPencilLds];
-  __shared__ double2 ib[6 * kPencilLds];
+  __shared__ double2 buf[6 * kPencilLds];  // three currents, then six gather fields
+  __shared__ double2 tw[128];
   const Grid& G = A.F.G;
-  const int nx = G.n[0], hx = nx >> 1, npl = A.npl, ld = nx + 1;  // padded pencil stride
+  for (int t = threadIdx.x; t < G.n[0] / 2; t += kBlock) tw[t] = A.tw_x[t];
+  const int nx = G.n[0], npl = A.npl, lognpl = 31 - __clz(npl), ld = pad8(nx) + 1;
   const int64_t S = (int64_t)G.n[1] * G.n[2], nc = G.ncell;
-  const int64_t q0 = (int64_t)blockIdx.x * npl;  // first pencil (iy nz + iz) of the block
+  // Blocks go round robin to the 8 XCDs, each with its own L2.  A block reads and
+  // writes 64 of the 128 bytes of a line, so neighbouring blocks take places 8
+  // apart: both halves of a line then meet in one L2 (315 -> 270 us at 128^3, 41 -> 34
+  // us at 64^3).
+  const int per_xcd = gridDim.x / kXcds;
+  const int block = gridDim.x % kXcds == 0
+                        ? (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds
+                        : blockIdx.x;
+  const int64_t q0 = (int64_t)block * npl;  // first pencil (iy nz + iz) of the block
   const int span = npl * nx;
+  auto slot = [&](int f, int pl, int e) -> double2& {
+    return buf[f * kPencilLds + pl * ld + pad8(e)];
+  };
+  // pencil q of a transform: field q / npl, pencil q % npl of the block
+  auto at = [&](int q, int e) -> double2& { return slot(q >> lognpl, q & (npl - 1), e); };
   // the three current spectra, pencil by pencil, bit-reversed along x
   for (int f = 0; f < 3; ++f)
-    for (int e = threadIdx.x; e < span; e += kBlock) {
-      const int kx = e / npl, pl = e - kx * npl;
-      jb[f * kPencilLds + pl * ld + brev(kx, A.logx)] = A.Jh[f * nc + kx * S + q0 + pl];
+    for (int u = threadIdx.x; u < span; u += kBlock) {
+      const int kx = u >> lognpl, pl = u & (npl - 1);
+      slot(f, pl, brev(kx, A.logx)) = A.Jh[f * nc + kx * S + q0 + pl];
     }
   __syncthreads();
-  for (int hs = 1; hs < nx; hs <<= 1) {
-    for (int u = threadIdx.x; u < 3 * npl * hx; u += kBlock) {
-      const int f = u / (npl * hx), r = u - f * npl * hx, pl = r / hx, j = r - pl * hx;
-      const int pos = j % hs, i0 = (j / hs) * 2 * hs + pos;
-      butterfly(jb + f * kPencilLds + pl * ld, i0, i0 + hs, A.tw_x[pos * (hx / hs)]);
-    }
-    __syncthreads();
-  }
-  // continuity + CN of every mode of the block's pencils
+  fft_pencils<false, false>(nx, A.logx, 3 * npl, tw, at);
+  // continuity + CN of every mode of the block's pencils, at most two per thread;
+  // every current is read before the first gather field takes its place
   double sums[3] = {0.0, 0.0, 0.0};
-  for (int e = threadIdx.x; e < span; e += kBlock) {
-    const int kx = e / npl, pl = e - kx * npl;
+  double2 J[2][3];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = threadIdx.x + h * kBlock;
+    if (u < span)
+#pragma unroll
+      for (int l = 0; l < 3; ++l) J[h][l] = slot(l, u & (npl - 1), u >> lognpl);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = threadIdx.x + h * kBlock;
+    if (u >= span) continue;
+    const int kx = u >> lognpl, pl = u & (npl - 1);
     const int64_t g = kx * S + q0 + pl;
     double k[3];
     mode_k(G, g, k);
-    double2 J[3], c[9], out[9], iv[6];
+    double2 c[9], out[9], iv[6];
     double s3[3];
 #pragma unroll
-    for (int l = 0; l < 3; ++l) J[l] = jb[l * kPencilLds + pl * ld + kx];
-#pragma unroll
     for (int f = 0; f < 9; ++f) c[f] = A.cur[f * nc + g];
-    cn_mode(A.F, k, J, c, out, iv, s3);
+    cn_mode(A.F, k, J[h], c, out, iv, s3);
 #pragma unroll
     for (int f = 0; f < 9; ++f) A.next[f * nc + g] = out[f];
 #pragma unroll
-    for (int f = 0; f < 6; ++f) ib[f * kPencilLds + pl * ld + brev(kx, A.logx)] = iv[f];
+    for (int f = 0; f < 6; ++f) slot(f, pl, brev(kx, A.logx)) = iv[f];
     sums[0] += s3[0];
     sums[1] += s3[1];
     sums[2] += s3[2];
   }
   __syncthreads();
-  for (int hs = 1; hs < nx; hs <<= 1) {
-    for (int u = threadIdx.x; u < 6 * npl * hx; u += kBlock) {
-      const int f = u / (npl * hx), r = u - f * npl * hx, pl = r / hx, j = r - pl * hx;
-      const int pos = j % hs, i0 = (j / hs) * 2 * hs + pos;
-      double2 w = A.tw_x[pos * (hx / hs)];
-      w.y = -w.y;
-      butterfly(ib + f * kPencilLds + pl * ld, i0, i0 + hs, w);
-    }
-    __syncthreads();
-  }
+  fft_pencils<true, false>(nx, A.logx, 6 * npl, tw, at);
   for (int f = 0; f < 6; ++f)
-    for (int e = threadIdx.x; e < span; e += kBlock) {
-      const int kx = e / npl, pl = e - kx * npl;
-      A.inv[f * nc + kx * S + q0 + pl] = ib[f * kPencilLds + pl * ld + kx];
+    for (int u = threadIdx.x; u < span; u += kBlock) {
+      const int kx = u >> lognpl, pl = u & (npl - 1);
+      A.inv[f * nc + kx * S + q0 + pl] = slot(f, pl, kx);
     }
   block_partials<3>(sums, A.sc.region(P_CN));  // -> S_JE, S_WNEXT, S_DW
 }
 
+// Inverse transform along z of the six gather fields of kGatherFftNodes
+// neighbouring nodes, written into the gather buffer's records: whole runs of
+// records leave together (one field at a time, 8 of every 80 bytes per pass, took
+// 178 us at 128^3).  both_levels: A^{n+1} into the A^n slots too.
+constexpr int kGatherFftNodes = 512;
+
+struct GatherPass {
+  const double2* data;
+  const double2* tw;
+  int64_t ncell;
+  int N, logN;
+  double* gbuf;
+  int both_levels;
+};
+
+__global__ __launch_bounds__(kBlock) void k_fft_gather(GatherPass A) {
+  constexpr int kRun = kGatherFftNodes + kGatherFftNodes / 8;
+  __shared__ double2 buf[6 * kRun];
+  __shared__ double2 tw[128];
+  for (int t = threadIdx.x; t < A.N / 2; t += kBlock) tw[t] = A.tw[t];
+  const int64_t g0 = (int64_t)blockIdx.x * kGatherFftNodes;
+  for (int u = threadIdx.x; u < 6 * kGatherFftNodes; u += kBlock) {
+    const int f = u / kGatherFftNodes, e = u % kGatherFftNodes;
+    const int row = e & ~(A.N - 1);
+    buf[f * kRun + pad8(row | brev(e & (A.N - 1), A.logN))] = A.data[f * A.ncell + g0 + e];
+  }
+  __syncthreads();
+  const int logrows = 9 - A.logN;  // rows of N points per field: 512 / N
+  fft_pencils<true, false>(A.N, A.logN, 6 << logrows, tw, [&](int p, int e) -> double2& {
+    return buf[(p >> logrows) * kRun + pad8(((p & ((1 << logrows) - 1)) << A.logN) + e)];
+  });
+  const int per = A.both_levels ? 9 : 6;
+  for (int u = threadIdx.x; u < per * kGatherFftNodes; u += kBlock) {
+    const int e = u / per, k = u - e * per;
+    const int slot = per == 9 || k < 3 ? k : k + 3;  // place in the record
+    const int f = slot < 6 ? slot : slot - 3;        // grad phi 0-2, A 3-5
+    A.gbuf[(g0 + e) * kGbufStride + slot] = buf[f * kRun + pad8(e)].x;
+  }
+}
+
 // ---- adjoint of the field update ----------------------------------------
 // Complex spectra carry adjoints in the convention dL = Re sum conj(lambda) dz;
-// every coefficient of k_cn is real except -dt i k of the continuity update,
+// every coefficient of cn_mode is real except -dt i k of the continuity update,
 // whose adjoint is +dt i k.  Given the adjoints l1 of the next level (9
 // fields, may be null) and the gather-side adjoints lg = [grad phi^{n+1/2}
 // (3), A^{n+1} (3), A^n (3)] as spectra (may be null; A^n only when lcur is
 // set), writes the adjoint of J^ to lJh and adds the current level's share to
-// lcur (may be null).  Transposes k_cn's arithmetic step by step.
+// lcur (may be null).  Transposes cn_mode's arithmetic step by step.
 __global__ __launch_bounds__(kBlock) void k_cn_adjoint(FieldParams F, const double2* l1,
                                                       const double2* lg, double2* lcur,
                                                       double2* lJh) {
@@ -816,79 +888,113 @@ __global__ __launch_bounds__(kBlock) void k_fields_EB(Grid G, const double2* cur
 
 }  // namespace
 
-void fft3_forward(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO* in,
-                  const double* prev, const double2* const* tw, Scratch sc, double* clear) {
-  // z (contiguous) first, reading the real input; then y and x in place
-  if (in)
-    fft_pass<1>(s, G, nb, data, 2, -1.0, tw[2], in, prev, clear, sc);
-  else
-    fft_pass<0>(s, G, nb, data, 2, -1.0, tw[2], nullptr, nullptr, nullptr, sc);
-  fft_pass<0>(s, G, nb, data, 1, -1.0, tw[1], nullptr, nullptr, nullptr, sc);
-  fft_pass<0>(s, G, nb, data, 0, -1.0, tw[0], nullptr, nullptr, nullptr, sc);
+namespace {
+
+// the z and y passes of a forward transform, real input; max|in - prev| and clear
+// as in fft3_forward
+void forward_zy(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO& in,
+                const double* prev, const double2* const* tw, const Scratch& sc, double* clear) {
+  if (plane_fits(G)) {
+    PlaneArgs A{};
+    A.G = G;
+    A.tw_y = tw[1];
+    A.tw_z = tw[2];
+    A.logy = ilog2(G.n[1]);
+    A.logz = ilog2(G.n[2]);
+    A.io = in;
+    A.prev = prev;
+    A.clear = clear;
+    A.cout = data;
+    A.sc = sc;
+    k_fft_plane<false><<<nb * G.n[0], kBlock, 0, s>>>(A);
+    return;
+  }
+  fft_pass<1, false>(s, G, nb, nullptr, data, 2, tw[2], &in, prev, clear, sc);
+  fft_pass<0, false>(s, G, nb, data, data, 1, tw[1], nullptr, nullptr, nullptr, sc);
 }
 
-void fft3_inverse(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO* out,
-                  const double2* const* tw) {
-  const Scratch none{};
-  fft_pass<0>(s, G, nb, data, 0, +1.0, tw[0], nullptr, nullptr, nullptr, none);
-  fft_pass<0>(s, G, nb, data, 1, +1.0, tw[1], nullptr, nullptr, nullptr, none);
-  if (out)
-    fft_pass<2>(s, G, nb, data, 2, +1.0, tw[2], out, nullptr, nullptr, none);
-  else
-    fft_pass<0>(s, G, nb, data, 2, +1.0, tw[2], nullptr, nullptr, nullptr, none);
+// the y and z passes of an inverse transform, real output
+void inverse_yz(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO& out,
+                const double2* const* tw) {
+  if (plane_fits(G)) {
+    PlaneArgs B{};
+    B.G = G;
+    B.tw_y = tw[1];
+    B.tw_z = tw[2];
+    B.logy = ilog2(G.n[1]);
+    B.logz = ilog2(G.n[2]);
+    B.cin = data;
+    B.io = out;
+    k_fft_plane<true><<<nb * G.n[0], kBlock, 0, s>>>(B);
+    return;
+  }
+  fft_pass<0, true>(s, G, nb, data, data, 1, tw[1], nullptr, nullptr, nullptr, Scratch{});
+  fft_pass<2, true>(s, G, nb, data, data, 2, tw[2], &out, nullptr, nullptr, Scratch{});
 }
 
-bool fused_field_solve_fits(const Grid& G) {
-  return G.n[1] * G.n[2] <= kPlaneMax && G.n[0] <= 2 * kBlock;
+}  // namespace
+
+void fft3_forward(hipStream_t s, const Grid& G, int nb, double2* data, const RealIO& in,
+                  const double2* const* tw, Scratch sc, double scale) {
+  forward_zy(s, G, nb, data, in, nullptr, tw, sc, nullptr);
+  fft_pass<0, false>(s, G, nb, data, data, 0, tw[0], nullptr, nullptr, nullptr, sc, scale);
 }
+
+void fft3_inverse(hipStream_t s, const Grid& G, int nb, const double2* src, double2* data,
+                  const RealIO& out, const double2* const* tw, double scale) {
+  fft_pass<0, true>(s, G, nb, src, data, 0, tw[0], nullptr, nullptr, nullptr, Scratch{}, scale);
+  inverse_yz(s, G, nb, data, out, tw);
+}
+
+namespace {
+int pencils_per_block(const Grid& G) { return std::min(4, kBlock / (G.n[0] / 2)); }
+}  // namespace
 
 int cn_pencil_blocks(const Grid& G) {
-  const int npl = std::min(4, kBlock / (G.n[0] / 2));
-  return (int)((int64_t)G.n[1] * G.n[2] / npl);
+  return (int)((int64_t)G.n[1] * G.n[2] / pencils_per_block(G));
 }
 
-void field_solve_fused(hipStream_t s, const FieldParams& F, const double* J, const double* prev,
-                       double* clear, const double2* cur, double2* next, double2* Jh,
-                       double2* batch, const RealIO& out, const double2* const* tw, Scratch sc) {
+void field_solve(hipStream_t s, const FieldParams& F, const RealIO& J, const double* prev,
+                 double* clear, const double2* cur, double2* next, double2* Jh, double2* batch,
+                 const GatherOut& out, const double2* const* tw, Scratch sc) {
   const Grid& G = F.G;
-  PlaneArgs A{};
-  A.G = G;
-  A.tw_y = tw[1];
-  A.tw_z = tw[2];
-  A.logy = ilog2(G.n[1]);
-  A.logz = ilog2(G.n[2]);
-  A.in = J;
-  A.prev = prev;
-  A.clear = clear;
-  A.cout = Jh;
-  A.sc = sc;
-  k_fft_plane<false><<<3 * G.n[0], kBlock, 0, s>>>(A);
+  forward_zy(s, G, 3, Jh, J, prev, tw, sc, clear);
   PencilArgs C{};
   C.F = F;
   C.tw_x = tw[0];
   C.logx = ilog2(G.n[0]);
-  C.npl = std::min(4, kBlock / (G.n[0] / 2));
+  C.npl = pencils_per_block(G);
   C.Jh = Jh;
   C.cur = cur;
   C.next = next;
   C.inv = batch;
   C.sc = sc;
   k_cn_pencils<<<cn_pencil_blocks(G), kBlock, 0, s>>>(C);
-  PlaneArgs B{};
-  B.G = G;
-  B.tw_y = tw[1];
-  B.tw_z = tw[2];
-  B.logy = A.logy;
-  B.logz = A.logz;
-  B.cin = batch;
-  B.io = out;
-  k_fft_plane<true><<<6 * G.n[0], kBlock, 0, s>>>(B);
-}
-
-void launch_cn_update(hipStream_t s, const FieldParams& F, const double2* cur, const double2* Jh,
-                      double2* next, double2* inv, Scratch sc) {
-  CNArgs C{F, cur, Jh, next, inv, sc};
-  k_cn<<<blocks_for(F.G.ncell), kBlock, 0, s>>>(C);
+  if (!out.gbuf) {
+    inverse_yz(s, G, 6, batch, out.io, tw);
+    return;
+  }
+  if (plane_fits(G)) {
+    RealIO io{};
+    for (int l = 0; l < 3; ++l) {
+      io.p[l] = out.gbuf + l;          // grad_h phi^{n+1/2}
+      io.p[3 + l] = out.gbuf + 6 + l;  // A^{n+1}
+      io.stride[l] = io.stride[3 + l] = kGbufStride;
+    }
+    inverse_yz(s, G, 6, batch, io, tw);
+    if (out.both_levels) launch_accept_A(s, G.ncell, out.gbuf);
+    return;
+  }
+  fft_pass<0, true>(s, G, 6, batch, batch, 1, tw[1], nullptr, nullptr, nullptr, Scratch{});
+  GatherPass P{};
+  P.data = batch;
+  P.tw = tw[2];
+  P.ncell = G.ncell;
+  P.N = G.n[2];
+  P.logN = ilog2(P.N);
+  P.gbuf = out.gbuf;
+  P.both_levels = out.both_levels ? 1 : 0;
+  k_fft_gather<<<(unsigned)(G.ncell / kGatherFftNodes), kBlock, 0, s>>>(P);
 }
 
 void launch_half_U(hipStream_t s, const Grid& G, const double2* cur, const double2* next,

@@ -501,25 +501,6 @@ struct TileStrides {
       : sy((dz + 15) & ~15), sx(dy * sy + 4) {}
 };
 
-// t / d for 0 <= t < 2^22 and d >= 1, with inv_d = 1.0f / d: (t + 1/2) / d
-// lies at least 1/(2d) away from an integer, further than the float rounding
-// error (t + 1/2) 2^-23 / d, so the truncation is exact (no integer division)
-__device__ __forceinline__ int div_small(int t, float inv_d) {
-  return (int)(((float)t + 0.5f) * inv_d);
-}
-
-// first particle of scatter block blk, and particle k of this thread in it: the
-// block's lanes sit span / 64 particles apart, chunk / 64 consecutive particles
-// each; span / chunk blocks share a span
-__device__ __forceinline__ int64_t chunk_base(int chunk, int span, int blk) {
-  const int per_span = span / chunk;
-  return (int64_t)(blk / per_span) * span + (blk % per_span) * (chunk / kWave);
-}
-__device__ __forceinline__ int64_t chunk_particle(int64_t base, int span, int k) {
-  const int lane = threadIdx.x % kWave, seg = 4 * (lane % 16) + lane / 16;
-  return base + seg * (span / kWave) + (int)(threadIdx.x / kWave) + (kBlock / kWave) * k;
-}
-
 // Extra nodes per side, at most 4, by which a box of extents dim can grow and
 // still fit `nodes` slots; -1 if it does not fit as it is.
 __device__ __forceinline__ int plain_slack(const int* dim, int nodes) {
@@ -1634,8 +1615,11 @@ __global__ __launch_bounds__(kBlock) void k_sweep(StepParams P, PS st,
     }
     poudev = fabs(pou - 1.0);
   }
-  block_max_to(ramax, sc.red + S_RAMAX);
-  block_max_to(poudev, sc.red + S_POU);
+  const double rm = block_max(ramax), pm = block_max(poudev);
+  if (threadIdx.x == 0) {
+    atomic_max_nonneg(sc.spread_copy(S_RAMAX), rm);
+    atomic_max_nonneg(sc.spread_copy(S_POU), pm);
+  }
   double s2[2] = {sums[0], sums[1]};
   block_partials<2>(s2, sc.region(P_SWEEP));  // -> S_WORK, S_RA2
 }
@@ -1688,14 +1672,16 @@ __global__ __launch_bounds__(kBlock) void k_kinetic(StepParams P, PS st, Scratch
   block_partials<2>(s, sc.region(P_K));
 }
 
-// which = 0: x (wrapped into [0, L)), 1: v^n, 2: v^{n-1}
+// which = 0: x (wrapped into [0, L)), 1: v^n, 2: v^{n-1}; src and dst in the
+// caller's order, particle i at id[i]
 template <class PS>
 __global__ __launch_bounds__(kBlock) void k_import(StepParams P, PS st, int which,
+                                                  const int* __restrict__ id,
                                                   const double* __restrict__ src) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= P.np) return;
   double w[3];
-  load3(src, P.np, i, w);
+  load3(src, P.np, id[i], w);
   if (which == 0) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) w[a] = wrap_pos(w[a], P.G.L[a], P.G.invL[a]);
@@ -1709,6 +1695,7 @@ __global__ __launch_bounds__(kBlock) void k_import(StepParams P, PS st, int whic
 
 template <class PS>
 __global__ __launch_bounds__(kBlock) void k_export(StepParams P, PS st, int which,
+                                                  const int* __restrict__ id,
                                                   double* __restrict__ dst) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= P.np) return;
@@ -1719,8 +1706,9 @@ __global__ __launch_bounds__(kBlock) void k_export(StepParams P, PS st, int whic
     st.v_of(P.np, i, w);
   else
     st.vp_of(P.np, i, w);
+  const int64_t k = id[i];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) dst[a * P.np + i] = w[a];
+  for (int a = 0; a < 3; ++a) dst[a * P.np + k] = w[a];
 }
 
 __global__ __launch_bounds__(kBlock) void k_fixed_current(int64_t n,
@@ -2001,15 +1989,17 @@ void launch_deposit_rho(hipStream_t s, int r, const StepParams& P, const PS& st,
 }
 
 template <class PS>
-void launch_import(hipStream_t s, const StepParams& P, const PS& st, int which, const double* src) {
+void launch_import(hipStream_t s, const StepParams& P, const PS& st, int which, const int* id,
+                   const double* src) {
   if (P.np <= 0) return;
-  k_import<PS><<<blocks_for(P.np), kBlock, 0, s>>>(P, st, which, src);
+  k_import<PS><<<blocks_for(P.np), kBlock, 0, s>>>(P, st, which, id, src);
 }
 
 template <class PS>
-void launch_export(hipStream_t s, const StepParams& P, const PS& st, int which, double* dst) {
+void launch_export(hipStream_t s, const StepParams& P, const PS& st, int which, const int* id,
+                   double* dst) {
   if (P.np <= 0) return;
-  k_export<PS><<<blocks_for(P.np), kBlock, 0, s>>>(P, st, which, dst);
+  k_export<PS><<<blocks_for(P.np), kBlock, 0, s>>>(P, st, which, id, dst);
 }
 
 void launch_fixed_current(hipStream_t s, int64_t n, unsigned long long* Jfix, double* J,
@@ -2032,8 +2022,10 @@ void launch_fixed_current(hipStream_t s, int64_t n, unsigned long long* Jfix, do
   template void launch_kinetic<PS>(hipStream_t, const StepParams&, const PS&, Scratch);          \
   template void launch_deposit_rho<PS>(hipStream_t, int, const StepParams&, const PS&,          \
                                        CurrentOut);                                              \
-  template void launch_import<PS>(hipStream_t, const StepParams&, const PS&, int, const double*); \
-  template void launch_export<PS>(hipStream_t, const StepParams&, const PS&, int, double*);
+  template void launch_import<PS>(hipStream_t, const StepParams&, const PS&, int, const int*,    \
+                                  const double*);                                                \
+  template void launch_export<PS>(hipStream_t, const StepParams&, const PS&, int, const int*,    \
+                                  double*);
 
 ECPIC_INSTANTIATE_STORE(Fp64Store)
 ECPIC_INSTANTIATE_STORE(MixedStore)

@@ -140,6 +140,25 @@ __device__ __forceinline__ int min_image(int raw, int n) {
   return 2 * r > n ? r - n : r;
 }
 
+// t / d for 0 <= t < 2^22 and d >= 1, with inv_d = 1.0f / d: (t + 1/2) / d
+// lies at least 1/(2d) away from an integer, further than the float rounding
+// error (t + 1/2) 2^-23 / d, so the truncation is exact (no integer division)
+__device__ __forceinline__ int div_small(int t, float inv_d) {
+  return (int)(((float)t + 0.5f) * inv_d);
+}
+
+// first particle of scatter block blk, and particle k of this thread in it: the
+// block's lanes sit span / 64 particles apart, chunk / 64 consecutive particles
+// each; span / chunk blocks share a span
+__device__ __forceinline__ int64_t chunk_base(int chunk, int span, int blk) {
+  const int per_span = span / chunk;
+  return (int64_t)(blk / per_span) * span + (blk % per_span) * (chunk / kWave);
+}
+__device__ __forceinline__ int64_t chunk_particle(int64_t base, int span, int k) {
+  const int lane = threadIdx.x % kWave, seg = 4 * (lane % 16) + lane / 16;
+  return base + seg * (span / kWave) + (int)(threadIdx.x / kWave) + (kBlock / kWave) * k;
+}
+
 // block-wide minimum of M ints at once (one barrier pair for all of them)
 template <int M>
 __device__ __forceinline__ void block_min_ints(int (&v)[M]) {
