@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "orbit.hpp"
@@ -41,73 +42,113 @@ struct Axis2 {
 
 // The nine values of a node that the push reads (components l of grad phi, A^n
 // and A^{n+1} as 0 + l, 3 + l and 6 + l) and the nine adjoints that it adds to,
-// in the block's LDS tile over its particles' node box, or in global memory for
-// a node outside the box.  at() takes the node in the particle's unwrapped frame
-// (ix, iy, iz).  The tile pointers carry the LDS address space, so the additions
-// are LDS atomics (through a plain pointer they compiled to flat atomics, the
-// slower path that serves either memory).
+// in the block's LDS tile over its particles' node box, or in global memory.
+// Nodes are given in the particle's unwrapped frame.  The tile pointers carry the
+// LDS address space, so the additions are LDS atomics (through a plain pointer
+// they compiled to flat atomics, the slower path that serves either memory).
+constexpr int kAdjTileNodes = 1000;
 typedef __attribute__((address_space(3))) double lds_double;
-struct AdjNode {
-  int t;      // first of the node's nine values in the tile, negative outside it
-  int64_t g;  // flat index in the mesh
-};
-struct AdjTile {
-  const AdjParticleArgs* P;
+struct TileNodes {
   lds_double* field;
   lds_double* sum;
-  int o[3], dim[3];  // particle's frame -> tile, extents (0: no tile)
-  int sy, sx;        // nodes between neighbours along y and x; along z 1
-  __device__ __forceinline__ AdjNode at(int ix, int iy, int iz) const {
-    const int tx = ix + o[0], ty = iy + o[1], tz = iz + o[2];
-    const bool in = tx >= 0 && ty >= 0 && tz >= 0 && tx < dim[0] && ty < dim[1] && tz < dim[2];
-    return {in ? 9 * (tx * sx + ty * sy + tz) : -1, node_index(P->G, ix, iy, iz)};
+  int o[3];    // particle's frame -> tile
+  int sy, sx;  // nodes between neighbours along y and x; along z 1
+  __device__ __forceinline__ int at(int ix, int iy, int iz) const {
+    return (ix + o[0]) * sx + (iy + o[1]) * sy + (iz + o[2]);
   }
-  __device__ __forceinline__ const double* global_field(int k) const {
-    return (k < 3 ? P->gphi : (k < 6 ? P->A0 : P->A1)) + (int64_t)(k % 3) * P->G.ncell;
+  __device__ __forceinline__ double get(int n, int k) const { return field[n + k * kAdjTileNodes]; }
+  __device__ __forceinline__ void add(int n, int k, double v) const {
+    __hip_atomic_fetch_add(&sum[n + k * kAdjTileNodes], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  __device__ __forceinline__ double* global_sum(int k) const {
-    return (k < 3 ? P->lgphi : (k < 6 ? P->lA0 : P->lA1)) + (int64_t)(k % 3) * P->G.ncell;
+};
+__device__ __forceinline__ const double* mesh_field(const AdjParticleArgs& P, int k) {
+  return (k < 3 ? P.gphi : (k < 6 ? P.A0 : P.A1)) + (int64_t)(k % 3) * P.G.ncell;
+}
+__device__ __forceinline__ double* mesh_sum(const AdjParticleArgs& P, int k) {
+  return (k < 3 ? P.lgphi : (k < 6 ? P.lA0 : P.lA1)) + (int64_t)(k % 3) * P.G.ncell;
+}
+struct MeshNodes {
+  const AdjParticleArgs& P;
+  __device__ __forceinline__ int64_t at(int ix, int iy, int iz) const {
+    return node_index(P.G, ix, iy, iz);
   }
-  template <int K0, int N>
-  __device__ __forceinline__ void load(const AdjNode& n, double (&f)[N]) const {
-    if (n.t >= 0) {
-#pragma unroll
-      for (int k = 0; k < N; ++k) f[k] = field[n.t + K0 + k];
-    } else {
-#pragma unroll
-      for (int k = 0; k < N; ++k) f[k] = global_field(K0 + k)[n.g];
-    }
-  }
-  template <int K0, int N>
-  __device__ __forceinline__ void add(const AdjNode& n, const double (&v)[N]) const {
-    if (n.t >= 0) {
-#pragma unroll
-      for (int k = 0; k < N; ++k)
-        __hip_atomic_fetch_add(&sum[n.t + K0 + k], v[k], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-#pragma unroll
-      for (int k = 0; k < N; ++k) unsafeAtomicAdd(global_sum(K0 + k) + n.g, v[k]);
-    }
+  __device__ __forceinline__ double get(int64_t n, int k) const { return mesh_field(P, k)[n]; }
+  __device__ __forceinline__ void add(int64_t n, int k, double v) const {
+    unsafeAtomicAdd(mesh_sum(P, k) + n, v);
   }
 };
 
-// The push terms of particle i (eta = (q/m) xi) in tensor-product form.
-// With eta'_j = eta_j / H_j and derivatives per unit of cell coordinate
-// (S_g = X_a Y_b Z_c; the degree-2 second derivatives are 1, -2, 1):
+// Node values of the polynomial functional with moments m[k] = M(t^k): the
+// degree-2 node weights along an axis are 1/8 - t/2 + t^2/2, 3/4 - t^2 and
+// 1/8 + t/2 + t^2/2.
+__device__ __forceinline__ void nodes_of_moments(double (&m)[3]) {
+  const double lo = 0.125 * m[0] + 0.5 * (m[2] - m[1]);
+  const double mid = 0.75 * m[0] - m[2];
+  m[2] = lo + m[1];
+  m[1] = mid;
+  m[0] = lo;
+}
+// and the coefficients in t of the sum of node values f[k] against these weights
+__device__ __forceinline__ void coefficients_of_nodes(double (&f)[3]) {
+  const double c2 = 0.5 * (f[0] + f[2]) - f[1];
+  const double c1 = 0.5 * (f[2] - f[0]);
+  f[0] = f[1] + 0.25 * c2;
+  f[1] = c1;
+  f[2] = c2;
+}
+
+// Values that the compiler may not carry over in derived form: it kept the points'
+// weights and their products from one row, and from one half of a row, to the next
+// (96 registers spilled at two wavefronts per SIMD).
+template <int N>
+__device__ __forceinline__ void recompute_from(double (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) asm volatile("" : "+v"(v[k]));
+}
+
+// weight and derivative (per unit of cell coordinate) of stencil node k at t, for
+// a k that differs from lane to lane
+__device__ __forceinline__ void weight_at(int k, double t, double& w, double& dw) {
+  const double c0 = k == 1 ? 0.75 : 0.125, c2 = k == 1 ? -1.0 : 0.5;
+  const double m = 0.5 * (k - 1) + c2 * t;
+  w = c0 + t * m;
+  dw = m + c2 * t;
+}
+
+// sum over the four lanes of a quad, to each of them
+__device__ __forceinline__ double quad_sum(double v) {
+  auto swap = [](double u, auto perm) {
+    constexpr int kPerm = decltype(perm)::value;
+    return __hiloint2double(
+        __builtin_amdgcn_mov_dpp(__double2hiint(u), kPerm, 0xf, 0xf, true),
+        __builtin_amdgcn_mov_dpp(__double2loint(u), kPerm, 0xf, 0xf, true));
+  };
+  v += swap(v, std::integral_constant<int, 0xB1>{});  // lanes 1 0 3 2
+  v += swap(v, std::integral_constant<int, 0x4E>{});  // lanes 2 3 0 1
+  return v;
+}
+
+// The push terms of one particle (eta = (q/m) xi) in tensor-product form.  With
+// eta'_j = eta_j / H_j and derivatives per unit of cell coordinate (S_g = X_a Y_b
+// Z_c; the degree-2 second derivatives are 1, -2, 1), w_q the weights of the
+// four-point rule of a piece:
 //  - per node, three point sums feed the mesh adjoints and the vbar adjoint:
 //      Sbar = sum_q w S,  T0 = sum_q w (1 - s) eta'.grad S,  T1 = sum_q w s eta'.grad S
 //    (dL/dgphi_l = -dt eta_l Sbar, dL/dA0_l = dt vbar_l T0, dL/dA1_l = dt vbar_l T1;
-//    lvbar += dt (A0_g T0 + A1_g T1));
+//    lvbar += dt (A0_g T0 + A1_g T1)); a stencil row (a, b) takes them from three
+//    moments each in the z coordinate of the points;
 //  - the x and d adjoints, dt / H_k sum_g sum_q w_q (1, s) [b_g(s_q) (eta'.grad)(d_k S_g)
-//    - (eta.gphi_g) d_k S_g] with b_g(s) = (1 - s) vbar.A0_g + s vbar.A1_g, need
-//    per stencil row only the z-column sums of b0 = vbar.A0, b1 = vbar.A1 and
-//    eg = eta.gphi against Z and Z' at each point (and against Z'', the same at
-//    every point); the row's x and y factors then give the Hessian terms.
-// The same sums as a node-by-node evaluation, with about a quarter of its
-// arithmetic.
-__device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i,
-                                             const AdjTile& tile) {
+//    - (eta.gphi_g) d_k S_g] with b_g(s) = (1 - s) vbar.A0_g + s vbar.A1_g, need of a
+//    row the polynomials in z that its values b0 = vbar.A0, b1 = vbar.A1 and eg =
+//    eta.gphi make; their values and derivatives at the points meet the row's x
+//    and y factors, which give the Hessian terms.
+// With the polynomials in place of the points' z weights a particle fits one lane
+// at 256 registers.
+// LANES = 1: one lane per particle.  4: lane `part` of a quad takes the stencil
+// planes a = part (part = 3: none) of the pieces and of the end points.
+template <int LANES, class Nodes>
+__device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i, int part,
+                                             const Nodes& nodes) {
   const Grid& G = P.G;
   const int64_t np = P.np;
   double x0[3], vb[3], d[3], eta[3], ep[3];
@@ -119,167 +160,188 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
     eta[a] = P.qm * P.xi[a * np + i];
     ep[a] = eta[a] * G.invH[a];
   }
-  // piece terms of lx and ld per unit of cell coordinate (times dt / H_k below)
+  // piece terms of lx and ld per unit of cell coordinate (times 1 / H_k below)
   double lx[3] = {0.0, 0.0, 0.0}, ld[3] = {0.0, 0.0, 0.0}, lvb[3] = {0.0, 0.0, 0.0};
   const bool ok = for_each_piece<2>(x0, d, G, [&](double s0, double s1, const double* base) {
-    const double h = s1 - s0;
-    double sq[4], wq[4], tx[4], ty[4], Z[4][3], dZ[4][3];
+    const double len = s1 - s0;
+    double sq[4], tx[4], ty[4], tz[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      sq[q] = s0 + 0.5 * h * (1.0 + Gauss<4>::x(q));
-      wq[q] = 0.5 * h * Gauss<4>::w(q);
+      sq[q] = s0 + 0.5 * len * (1.0 + Gauss<4>::x(q));
       tx[q] = (x0[0] + sq[q] * d[0]) * G.invH[0] - base[0];
       ty[q] = (x0[1] + sq[q] * d[1]) * G.invH[1] - base[1];
-      Spline<2>::wd((x0[2] + sq[q] * d[2]) * G.invH[2] - base[2], Z[q], dZ[q]);
+      tz[q] = (x0[2] + sq[q] * d[2]) * G.invH[2] - base[2];
     }
+    double hw[1] = {0.5 * P.dt * len};  // dt in the weights
     const int fx = to_int_clamped(base[0]) + Spline<2>::first_off;
     const int fy = to_int_clamped(base[1]) + Spline<2>::first_off;
     const int fz = to_int_clamped(base[2]) + Spline<2>::first_off;
 #pragma unroll 1
-    for (int a = 0; a < 3; ++a) {
-      const double ddX = a == 1 ? -2.0 : 1.0;
-      double Xq[4], dXq[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) Spline<2>::wk(a, tx[q], Xq[q], dXq[q]);
+    for (int a = LANES == 1 ? 0 : part; a < 3; a += LANES) {
+      const double ex = a == 1 ? -2.0 * ep[0] : ep[0];  // eta'_x X''
 #pragma unroll 1
       for (int b = 0; b < 3; ++b) {
-        const double ddY = b == 1 ? -2.0 : 1.0;
-        double Yq[4], dYq[4], xy[4], dxy[4], xdy[4], pe[4];
+        const double ey = b == 1 ? -2.0 * ep[1] : ep[1];  // eta'_y Y''
+        recompute_from(hw);
+        recompute_from(sq);
+        recompute_from(tx);
+        recompute_from(ty);
+        recompute_from(tz);
+        double S[3] = {0.0, 0.0, 0.0}, T0[3] = {0.0, 0.0, 0.0}, T1[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          Spline<2>::wk(b, ty[q], Yq[q], dYq[q]);
-          xy[q] = Xq[q] * Yq[q];
-          dxy[q] = dXq[q] * Yq[q];
-          xdy[q] = Xq[q] * dYq[q];
-          pe[q] = ep[0] * dxy[q] + ep[1] * xdy[q];  // (eta'_x d_x + eta'_y d_y)(X Y)
+          double X, dX, Y, dY;
+          if constexpr (LANES == 1)
+            Spline<2>::wk(a, tx[q], X, dX);
+          else
+            weight_at(a, tx[q], X, dX);
+          Spline<2>::wk(b, ty[q], Y, dY);
+          const double w = hw[0] * Gauss<4>::w(q), q1 = w * sq[q], q0 = w - q1;
+          const double xy = X * Y, pe = ep[0] * (dX * Y) + ep[1] * (X * dY), r = ep[2] * xy;
+          const double u0 = w * xy, u1 = u0 * tz[q];
+          const double e1 = pe * tz[q] + r, e2 = (e1 + r) * tz[q];
+          S[0] += u0;
+          S[1] += u1;
+          S[2] += u1 * tz[q];
+          T0[0] += q0 * pe;
+          T0[1] += q0 * e1;
+          T0[2] += q0 * e2;
+          T1[0] += q1 * pe;
+          T1[1] += q1 * e1;
+          T1[2] += q1 * e2;
         }
-        double C0[4], C0d[4], C1[4], C1d[4], Eg[4], Egd[4], C0dd = 0.0, C1dd = 0.0;
+        nodes_of_moments(S);
+        nodes_of_moments(T0);
+        nodes_of_moments(T1);
+        double b0[3], b1[3], eg[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const double ddZ = c == 1 ? -2.0 : 1.0;
-          const AdjNode node = tile.at(fx + a, fy + b, fz + c);
+          const auto n = nodes.at(fx + a, fy + b, fz + c);
           double f[9];  // grad phi, A^n, A^{n+1}
-          tile.load<0>(node, f);
-          double b0 = 0.0, b1 = 0.0, eg = 0.0;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) f[k] = nodes.get(n, k);
+          b0[c] = b1[c] = eg[c] = 0.0;
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            b0 += vb[l] * f[3 + l];
-            b1 += vb[l] * f[6 + l];
-            eg += eta[l] * f[l];
+            eg[c] += eta[l] * f[l];
+            b0[c] += vb[l] * f[3 + l];
+            b1[c] += vb[l] * f[6 + l];
+            lvb[l] += f[3 + l] * T0[c] + f[6 + l] * T1[c];
           }
-          double Sbar = 0.0, T0 = 0.0, T1 = 0.0;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double z = Z[q][c], dz = dZ[q][c];
-            C0[q] = c == 0 ? b0 * z : C0[q] + b0 * z;
-            C0d[q] = c == 0 ? b0 * dz : C0d[q] + b0 * dz;
-            C1[q] = c == 0 ? b1 * z : C1[q] + b1 * z;
-            C1d[q] = c == 0 ? b1 * dz : C1d[q] + b1 * dz;
-            Eg[q] = c == 0 ? eg * z : Eg[q] + eg * z;
-            Egd[q] = c == 0 ? eg * dz : Egd[q] + eg * dz;
-            const double edS = pe[q] * z + ep[2] * xy[q] * dz;  // eta'.grad S
-            Sbar += wq[q] * xy[q] * z;
-            T0 += wq[q] * (1.0 - sq[q]) * edS;
-            T1 += wq[q] * sq[q] * edS;
-          }
-          C0dd += b0 * ddZ;
-          C1dd += b1 * ddZ;
-          double v[9];
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            lvb[l] += P.dt * (f[3 + l] * T0 + f[6 + l] * T1);
-            v[l] = -P.dt * eta[l] * Sbar;
-            v[3 + l] = P.dt * vb[l] * T0;
-            v[6 + l] = P.dt * vb[l] * T1;
+            nodes.add(n, l, -eta[l] * S[c]);
+            nodes.add(n, 3 + l, vb[l] * T0[c]);
+            nodes.add(n, 6 + l, vb[l] * T1[c]);
           }
-          tile.add<0>(node, v);
         }
-        // the row's share of sum_g b (eta'.grad)(d_k S_g) (with b0 and b1) and
-        // of sum_g eg d_k S_g, per point
+        recompute_from(hw);
+        recompute_from(sq);
+        recompute_from(tx);
+        recompute_from(ty);
+        recompute_from(tz);
+        coefficients_of_nodes(b0);
+        coefficients_of_nodes(b1);
+        coefficients_of_nodes(eg);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const double dxdy = dXq[q] * dYq[q];
-          // (eta'.grad)(d_k S) summed over the row against b0 and b1
-          const double hx = ep[0] * ddX * Yq[q] + ep[1] * dxdy;     // with Z
-          const double hy = ep[0] * dxdy + ep[1] * Xq[q] * ddY;     // with Z
-          const double u0x = hx * C0[q] + ep[2] * dxy[q] * C0d[q];
-          const double u0y = hy * C0[q] + ep[2] * xdy[q] * C0d[q];
-          const double u0z = pe[q] * C0d[q] + ep[2] * xy[q] * C0dd;
-          const double u1x = hx * C1[q] + ep[2] * dxy[q] * C1d[q];
-          const double u1y = hy * C1[q] + ep[2] * xdy[q] * C1d[q];
-          const double u1z = pe[q] * C1d[q] + ep[2] * xy[q] * C1dd;
-          // d_k S summed over the row against eg
-          const double vx = dxy[q] * Eg[q], vy = xdy[q] * Eg[q], vz = xy[q] * Egd[q];
-          const double q0 = wq[q] * (1.0 - sq[q]), q1 = wq[q] * sq[q];
-          lx[0] += q0 * u0x + q1 * u1x - wq[q] * vx;
-          lx[1] += q0 * u0y + q1 * u1y - wq[q] * vy;
-          lx[2] += q0 * u0z + q1 * u1z - wq[q] * vz;
-          ld[0] += sq[q] * (q0 * u0x + q1 * u1x - wq[q] * vx);
-          ld[1] += sq[q] * (q0 * u0y + q1 * u1y - wq[q] * vy);
-          ld[2] += sq[q] * (q0 * u0z + q1 * u1z - wq[q] * vz);
+          double X, dX, Y, dY;
+          if constexpr (LANES == 1)
+            Spline<2>::wk(a, tx[q], X, dX);
+          else
+            weight_at(a, tx[q], X, dX);
+          Spline<2>::wk(b, ty[q], Y, dY);
+          const double t = tz[q], w = hw[0] * Gauss<4>::w(q), q1 = w * sq[q], q0 = w - q1;
+          // the row's b(s) and eta.grad phi at the point, with the weight, and their z derivatives
+          const double B2 = q0 * b0[2] + q1 * b1[2], B1 = q0 * b0[1] + q1 * b1[1];
+          const double m = B1 + t * B2, C = q0 * b0[0] + q1 * b1[0] + t * m, dC = m + t * B2;
+          const double k = eg[1] + t * eg[2];
+          const double E = w * (eg[0] + t * k), dE = w * (k + t * eg[2]);
+          const double g = ep[2] * dC - E, h = 2.0 * ep[2] * B2 - dE;
+          const double YC = Y * C, dYC = dY * C;
+          const double rx = ex * YC + dX * (ep[1] * dYC + Y * g);
+          const double ry = dX * (ep[0] * dYC) + X * (ey * C + dY * g);
+          const double rz = ep[0] * (dX * (Y * dC)) + X * (ep[1] * (dY * dC) + Y * h);
+          lx[0] += rx;
+          lx[1] += ry;
+          lx[2] += rz;
+          ld[0] += sq[q] * rx;
+          ld[1] += sq[q] * ry;
+          ld[2] += sq[q] * rz;
         }
       }
     }
   });
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    lx[k] *= P.dt * G.invH[k];
-    ld[k] *= P.dt * G.invH[k];
+    lx[k] *= G.invH[k];
+    ld[k] *= G.invH[k];
   }
-  // + A0_h(x0) - A1_h(x0 + d), end point wrapped
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const double sgn = e == 0 ? 1.0 : -1.0;
-    double base[3];
-    int first[3], sh[3];
+  // + A0_h(x0) and - A1_h(x0 + d), end point wrapped
+#pragma unroll 1
+  for (int end = 0; end < 2; ++end) {
+    const double sgn = end ? -1.0 : 1.0;
+    const int comp = end ? 6 : 3;
+    recompute_from(x0);
+    recompute_from(d);
+    int first[3];
     Axis2 ax[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double xp = e == 0 ? x0[a] : wrap_pos(x0[a] + d[a], G.L[a], G.invL[a]);
-      const double u = xp * G.invH[a];
-      base[a] = floor(u + Spline<2>::base_off);
-      first[a] = to_int_clamped(base[a]) + Spline<2>::first_off;
-      ax[a].at(u - base[a], G.invH[a]);
-      // periods between the wrapped end point and the unwrapped orbit end
-      sh[a] = e == 0 ? 0 : (int)rint((x0[a] + d[a] - xp) * G.invL[a]) * G.n[a];
+      const double x1 = wrap_pos(x0[a] + d[a], G.L[a], G.invL[a]);
+      const double u = (end ? x1 : x0[a]) * G.invH[a];
+      const double base = floor(u + Spline<2>::base_off);
+      ax[a].at(u - base, G.invH[a]);
+      // back to the frame of the unwrapped orbit
+      first[a] = to_int_clamped(base) + Spline<2>::first_off +
+                 (end ? (int)rint((x0[a] + d[a] - x1) * G.invL[a]) * G.n[a] : 0);
     }
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b)
+    double e[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int a = LANES == 1 ? 0 : part; a < 3; a += LANES) {
+      const double wx = a == 0 ? ax[0].w[0] : (a == 1 ? ax[0].w[1] : ax[0].w[2]);
+      const double dwx = a == 0 ? ax[0].dw[0] : (a == 1 ? ax[0].dw[1] : ax[0].dw[2]);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const double wxy = wx * ax[1].w[b];
+        double f0 = 0.0, f1 = 0.0;  // the row's eta.A against Z and Z'
+#pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const AdjNode node =
-              tile.at(first[0] + a + sh[0], first[1] + b + sh[1], first[2] + c + sh[2]);
-          const double S = ax[0].w[a] * ax[1].w[b] * ax[2].w[c];
-          const double dS[3] = {ax[0].dw[a] * ax[1].w[b] * ax[2].w[c],
-                                ax[0].w[a] * ax[1].dw[b] * ax[2].w[c],
-                                ax[0].w[a] * ax[1].w[b] * ax[2].dw[c]};
-          double f[3], v[3];
-          if (e == 0)
-            tile.load<3>(node, f);
-          else
-            tile.load<6>(node, f);
+          const auto n = nodes.at(first[0] + a, first[1] + b, first[2] + c);
+          const double Sg = sgn * (wxy * ax[2].w[c]);
           double eF = 0.0;
 #pragma unroll
           for (int l = 0; l < 3; ++l) {
-            eF += eta[l] * f[l];
-            v[l] = sgn * eta[l] * S;
+            eF += eta[l] * nodes.get(n, comp + l);
+            nodes.add(n, comp + l, eta[l] * Sg);
           }
-          if (e == 0)
-            tile.add<3>(node, v);
-          else
-            tile.add<6>(node, v);
-#pragma unroll
-          for (int kk = 0; kk < 3; ++kk) {
-            lx[kk] += sgn * eF * dS[kk];
-            if (e == 1) ld[kk] += sgn * eF * dS[kk];
-          }
+          f0 += eF * ax[2].w[c];
+          f1 += eF * ax[2].dw[c];
         }
+        e[0] += dwx * ax[1].w[b] * f0;
+        e[1] += wx * ax[1].dw[b] * f0;
+        e[2] += wxy * f1;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lx[k] += sgn * e[k];
+      ld[k] += end ? sgn * e[k] : 0.0;
+    }
   }
-  if (!ok) P.bad[0] = 1.0;
+  if (!ok) atomic_max_nonneg(P.sc.spread_copy(S_BAD), 1.0);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    P.lx[a * np + i] += lx[a];
-    P.ld[a * np + i] += ld[a];
-    P.lvb[a * np + i] += lvb[a];
+    if constexpr (LANES == 4) {
+      lx[a] = quad_sum(lx[a]);
+      ld[a] = quad_sum(ld[a]);
+      lvb[a] = quad_sum(lvb[a]);
+    }
+    if (LANES == 1 || part == a) {
+      P.lx[a * np + i] = lx[a];
+      P.ld[a * np + i] = ld[a];
+      P.lvb[a * np + i] = lvb[a];
+    }
   }
 }
 
@@ -290,11 +352,18 @@ __device__ __forceinline__ void push_adjoint(const AdjParticleArgs& P, int64_t i
 //   I = sum_q w_q X Y Z,  I_k = sum_q w_q d_k(X Y Z),  I_k^s = sum_q w_q s_q d_k(X Y Z)
 // (derivatives per unit of cell coordinate, scaled by 1/H once per particle)
 // meet the node's mu:  lvbar += mu_g I,  lx += (vbar . mu_g) I_k,
-// ld += (vbar . mu_g) I_k^s.  The same sums as the node-by-node form above,
+// ld += (vbar . mu_g) I_k^s.  The same sums as a node-by-node evaluation,
 // with about a third of its arithmetic.
-__global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= P.np) return;
+// UPDATE false: lx, ld and lvbar are the current's terms.  True: the push's terms
+// (written before) are added, lx is stored, and the next iterate xn = b + (lvbar +
+// dt ld) / 2 is formed here, with max|xn - xi| and max|xn| into the spread slots
+// S_DVMAX and S_VMAX (as separate kernels: 170 us more per iteration at 2,097,152
+// particles, zeroing the three arrays included).
+template <bool UPDATE>
+__device__ __forceinline__ void current_adjoint_one(const AdjParticleArgs& P, int64_t i,
+                                                    const double* __restrict__ bvec,
+                                                    double* __restrict__ xn, double& dm,
+                                                    double& xm) {
   const Grid& G = P.G;
   const int64_t np = P.np, nc = G.ncell;
   double x0[3], vb[3], d[3];
@@ -370,57 +439,116 @@ __global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P) {
       }
     }
   });
-  if (!ok) P.bad[0] = 1.0;
+  if (!ok) atomic_max_nonneg(P.sc.spread_copy(S_BAD), 1.0);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    P.lx[a * np + i] += lx[a] * G.invH[a];
-    P.ld[a * np + i] += ld[a] * G.invH[a];
-    P.lvb[a * np + i] += lvb[a];
+    const int64_t e = a * np + i;
+    lx[a] *= G.invH[a];
+    ld[a] *= G.invH[a];
+    if constexpr (UPDATE) {
+      P.lx[e] += lx[a];
+      const double x = bvec[e] + 0.5 * ((P.lvb[e] + lvb[a]) + P.dt * (P.ld[e] + ld[a]));
+      xn[e] = x;
+      dm = fmax(dm, fabs(x - P.xi[e]));
+      xm = fmax(xm, fabs(x));
+      if (!isfinite(x)) dm = INFINITY;
+    } else {
+      P.lx[e] = lx[a];
+      P.ld[e] = ld[a];
+      P.lvb[e] = lvb[a];
+    }
   }
 }
 
+template <bool UPDATE>
+__global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P,
+                                                            const double* __restrict__ b,
+                                                            double* __restrict__ xn) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  double dm = 0.0, xm = 0.0;
+  if (i < P.np) current_adjoint_one<UPDATE>(P, i, b, xn, dm, xm);
+  if (UPDATE) {
+    dm = block_max(dm);
+    xm = block_max(xm);
+    if (threadIdx.x == 0) {
+      atomic_max_nonneg(P.sc.spread_copy(S_DVMAX), dm);
+      atomic_max_nonneg(P.sc.spread_copy(S_VMAX), xm);
+    }
+  }
+}
 // The push terms over cell-sorted particles, in blocks of P.chunk particles
 // whose lanes are spread over P.span, as in the current scatter: the block finds
 // the node box of its particles' orbits and end points (clipped to the start
 // stencils plus what fits, where the box exceeds the tile), copies the box's
 // fields into LDS, sums the nine mesh adjoints of its particles in a second LDS
-// array over it, and adds that to global memory once.  The kernel runs at one
-// wavefront per SIMD (its registers), so one block per CU loses nothing to the
-// 144 KB.
+// array over it, and adds that to global memory once.  Particles that reach beyond
+// the box go to P.list, and k_push_adjoint_list takes them from global memory (a
+// second path in this kernel cost it registers and scalar spills).
 // Rows are padded where that fits (as TileStrides in particles.hip: the 64-bit
 // additions of 16 neighbouring lanes then rarely share a bank pair).
-constexpr int kAdjTileNodes = 1000;
-
+// Bound by instruction issue and the LDS about equally (2,097,152 particles of a
+// 32^3 mesh: 13,500 vector instructions and 1,490 LDS instructions per wavefront),
+// two wavefronts per SIMD.  Measured per launch, one step of the transposed
+// iteration: 2220 us with the points' weights held in 512 registers (one wavefront
+// per SIMD), 2080 with two lanes per particle, 1720 in this form with a node's nine
+// values side by side, 1675 with one plane per value, 1427 with planes 4 mod 16
+// apart where rows of 16 do not fit; 32,769 particles of 16^3: 125, 91, and 51 with
+// four lanes per particle.
 struct AdjStrides {
   int sy, sx;
   bool fits;
   __device__ __forceinline__ AdjStrides(const int* dim) : sy(1), sx(1), fits(false) {
     // each extent is bounded first so that the products cannot overflow
     if (!(dim[0] > 0 && dim[0] <= kAdjTileNodes && dim[1] <= kAdjTileNodes &&
-          dim[2] <= kAdjTileNodes))
+          dim[2] <= kAdjTileNodes && (int64_t)dim[0] * dim[1] * dim[2] <= kAdjTileNodes))
       return;
+    // rows of 16, then rows as they are with planes 4 mod 16 apart, then no padding
     sy = (dim[2] + 15) & ~15;
     sx = dim[1] * sy + 4;
-    if ((int64_t)dim[0] * sx > kAdjTileNodes) {
+    if (dim[0] * sx > kAdjTileNodes) {
       sy = dim[2];
-      sx = dim[1] * sy;
+      sx = ((dim[1] * sy + 11) & ~15) + 4;
     }
-    fits = (int64_t)dim[0] * sx <= kAdjTileNodes;
+    if (dim[0] * sx > kAdjTileNodes) sx = dim[1] * sy;
+    fits = dim[0] * sx <= kAdjTileNodes;
   }
 };
 
-__global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P) {
+constexpr int kAdjBlock = 512;
+
+// particle k of this thread in block blk, and the block's first: as chunk_base and
+// chunk_particle (reduce.hpp) for groups of LANES lanes
+template <int LANES>
+__device__ __forceinline__ int64_t group_base(int chunk, int span, int blk) {
+  const int per_span = span / chunk;
+  return (int64_t)(blk / per_span) * span + (blk % per_span) * (chunk / (kWave / LANES));
+}
+template <int LANES>
+__device__ __forceinline__ int64_t group_particle(int64_t base, int span, int k) {
+  constexpr int kGroups = kWave / LANES;
+  const int g = (threadIdx.x % kWave) / LANES, seg = 4 * (g % (kGroups / 4)) + g / (kGroups / 4);
+  return base + seg * (span / kGroups) + (int)(threadIdx.x / kWave) + (kAdjBlock / kWave) * k;
+}
+
+template <int LANES>
+__global__ __launch_bounds__(kAdjBlock) __attribute__((
+    amdgpu_waves_per_eu(2))) void k_push_adjoint_tiled(AdjParticleArgs P) {
   __shared__ double field[9 * kAdjTileNodes];
   __shared__ double sum[9 * kAdjTileNodes];
   __shared__ int s_ref[3];
   const Grid& G = P.G;
-  const int per_thread = P.chunk / kBlock;
-  const int64_t base = chunk_base(P.chunk, P.span, blockIdx.x);
+  const int per_thread = P.chunk * LANES / kAdjBlock;
+  const int64_t base = group_base<LANES>(P.chunk, P.span, blockIdx.x);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int a = 0; a < 3; ++a)  // a span's last blocks may be empty
-      s_ref[a] = to_int_clamped(
-          floor(P.x[a * P.np + min(base, P.np - 1)] * G.invH[a] + Spline<2>::base_off));
+    for (int a = 0; a < 3; ++a) {
+      // its z, and the middle of the sort's 4 x 4 column in x and y: a block in two
+      // columns then stays within half a period of it, also where that is 8 cells.
+      // (A span's last blocks may be empty.)
+      const double u = P.x[a * P.np + min(base, P.np - 1)] * G.invH[a];
+      s_ref[a] = to_int_clamped(floor(u + Spline<2>::base_off));
+      if (a < 2) s_ref[a] = (s_ref[a] & ~3) + 1;
+    }
   __syncthreads();
   // node boxes: the orbits from x0 to x0 + d (unwrapped), which also hold both end
   // points' stencils, and the start stencils alone
@@ -428,7 +556,7 @@ __global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P
 #pragma unroll
   for (int k = 0; k < 12; ++k) mv[k] = 0x3fffffff;
   for (int k = 0; k < per_thread; ++k) {
-    const int64_t i = chunk_particle(base, P.span, k);
+    const int64_t i = group_particle<LANES>(base, P.span, k);
     if (i >= P.np) continue;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -441,78 +569,91 @@ __global__ __launch_bounds__(kBlock) void k_push_adjoint_tiled(AdjParticleArgs P
       mv[9 + a] = min(mv[9 + a], -(rel + (b0 - lo) + 3));
     }
   }
-  block_min_ints<12>(mv);
-  AdjTile tile{&P, (lds_double*)field, (lds_double*)sum, {0, 0, 0}, {0, 0, 0}, 1, 1};
-  int tlo[3];
+  block_min_ints<12, kAdjBlock>(mv);
+  int tlo[3], dim[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     tlo[a] = mv[a];
-    tile.dim[a] = -mv[3 + a] - tlo[a] + 1;
+    dim[a] = -mv[3 + a] - tlo[a] + 1;
   }
-  if (!AdjStrides(tile.dim).fits) {
+  if (!AdjStrides(dim).fits) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       tlo[a] = mv[6 + a];
-      tile.dim[a] = -mv[9 + a] - tlo[a] + 1;
+      dim[a] = -mv[9 + a] - tlo[a] + 1;
     }
     for (int e = 0; e < 4; ++e) {  // widened while it fits
-      const int wider[3] = {tile.dim[0] + 2, tile.dim[1] + 2, tile.dim[2] + 2};
+      const int wider[3] = {dim[0] + 2, dim[1] + 2, dim[2] + 2};
       if (!AdjStrides(wider).fits) break;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         tlo[a] -= 1;
-        tile.dim[a] = wider[a];
+        dim[a] = wider[a];
       }
     }
   }
-  const AdjStrides str(tile.dim);
-  tile.sy = str.sy;
-  tile.sx = str.sx;
-  if (!str.fits) tile.dim[0] = tile.dim[1] = tile.dim[2] = 0;  // every node in global memory
-  const int nt = tile.dim[0] * tile.dim[1] * tile.dim[2];
-  const float inv_d1 = 1.0f / (float)max(tile.dim[1], 1), inv_d2 = 1.0f / (float)max(tile.dim[2], 1);
+  const AdjStrides str(dim);
+  if (!str.fits) dim[0] = dim[1] = dim[2] = 0;  // every particle to the list
+  const int nt = dim[0] * dim[1] * dim[2];
+  const float inv_d1 = 1.0f / (float)max(dim[1], 1), inv_d2 = 1.0f / (float)max(dim[2], 1);
   // node t of the box: its slot in the tile and its place in the mesh
   auto box_node = [&](int t, int& slot, int64_t& g) {
     const int q = div_small(t, inv_d2), cx = div_small(q, inv_d1);
-    const int cz = t - q * tile.dim[2], cy = q - cx * tile.dim[1];
-    slot = 9 * (cx * tile.sx + cy * tile.sy + cz);
+    const int cz = t - q * dim[2], cy = q - cx * dim[1];
+    slot = cx * str.sx + cy * str.sy + cz;
     g = node_index(G, s_ref[0] + tlo[0] + cx, s_ref[1] + tlo[1] + cy, s_ref[2] + tlo[2] + cz);
   };
-  for (int t = threadIdx.x; t < nt; t += kBlock) {
+  for (int t = threadIdx.x; t < nt; t += kAdjBlock) {
     int slot;
     int64_t g;
     box_node(t, slot, g);
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      field[slot + k] = tile.global_field(k)[g];
-      sum[slot + k] = 0.0;
+      field[slot + k * kAdjTileNodes] = mesh_field(P, k)[g];
+      sum[slot + k * kAdjTileNodes] = 0.0;
     }
   }
   __syncthreads();
   for (int k = 0; k < per_thread; ++k) {
-    const int64_t i = chunk_particle(base, P.span, k);
+    const int64_t i = group_particle<LANES>(base, P.span, k);
     if (i >= P.np) continue;
+    TileNodes nodes{(lds_double*)field, (lds_double*)sum, {0, 0, 0}, str.sy, str.sx};
+    bool inside = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
+      const double d = P.dt * P.vb[a * P.np + i];
       int lo, n, b0;
-      orbit_nodes<2>(P.x[a * P.np + i], P.dt * P.vb[a * P.np + i], G.invH[a], lo, n, b0);
+      orbit_nodes<2>(P.x[a * P.np + i], d, G.invH[a], lo, n, b0);
       const int raw = lo - s_ref[a];
       // particle frame -> chunk frame -> tile
-      tile.o[a] = min_image(raw, G.n[a]) - raw - s_ref[a] - tlo[a];
+      nodes.o[a] = min_image(raw, G.n[a]) - raw - s_ref[a] - tlo[a];
+      inside = inside && lo + nodes.o[a] >= 0 && lo + n + nodes.o[a] < dim[a] && d == d;
     }
-    push_adjoint(P, i, tile);
+    if (inside)
+      push_adjoint<LANES>(P, i, (int)threadIdx.x % LANES, nodes);
+    else if (threadIdx.x % LANES == 0)
+      P.list[1 + atomicAdd(P.list, 1)] = (int)i;
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < nt; t += kBlock) {
+  for (int t = threadIdx.x; t < nt; t += kAdjBlock) {
     int slot;
     int64_t g;
     box_node(t, slot, g);
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const double val = sum[slot + k];
-      if (val != 0.0) unsafeAtomicAdd(tile.global_sum(k) + g, val);
+      const double val = sum[slot + k * kAdjTileNodes];
+      if (val != 0.0) unsafeAtomicAdd(mesh_sum(P, k) + g, val);
     }
   }
+}
+
+// the particles of P.list, entry j by block j % grid (few lanes per wavefront: every
+// lane reads nodes of its own)
+__global__ __launch_bounds__(kBlock) void k_push_adjoint_list(AdjParticleArgs P) {
+  const int count = P.list[0];
+  for (int64_t j = (int64_t)threadIdx.x * gridDim.x + blockIdx.x; j < count;
+       j += (int64_t)kBlock * gridDim.x)
+    push_adjoint<1>(P, P.list[1 + j], 0, MeshNodes{P});
 }
 
 // vbar = (w + v)/2
@@ -539,27 +680,6 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_rhs(int64_t n3, double dt,
   lxacc[i] = x1 + lx[i];
 }
 
-// xn = b + (lvb + dt ld)/2; max|xn - xi| and max|xn| into red[0], red[1]
-__global__ __launch_bounds__(kBlock) void k_adjoint_update(int64_t n3, double dt,
-                                                          const double* __restrict__ b,
-                                                          const double* __restrict__ lvb,
-                                                          const double* __restrict__ ld,
-                                                          const double* __restrict__ xi,
-                                                          double* __restrict__ xn,
-                                                          double* __restrict__ red) {
-  double dm = 0.0, xm = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n3;
-       i += (int64_t)gridDim.x * kBlock) {
-    const double x = b[i] + 0.5 * (lvb[i] + dt * ld[i]);
-    xn[i] = x;
-    dm = fmax(dm, fabs(x - xi[i]));
-    xm = fmax(xm, fabs(x));
-    if (!isfinite(x)) dm = INFINITY;
-  }
-  block_max_to(dm, red);
-  block_max_to(xm, red + 1);
-}
-
 // lx0 = lxacc + lx, lv0 = 2 xi - lv1
 __global__ __launch_bounds__(kBlock) void k_adjoint_out(int64_t n3, const double* __restrict__ lxacc,
                                                        const double* __restrict__ lx,
@@ -575,11 +695,22 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_out(int64_t n3, const double
 
 }  // namespace
 
-void launch_particle_adjoint(hipStream_t s, const AdjParticleArgs& P, bool eta, bool mu) {
+void launch_push_adjoint(hipStream_t s, const AdjParticleArgs& P) {
   if (P.np <= 0) return;
-  if (eta)
-    k_push_adjoint_tiled<<<(unsigned)scatter_blocks(P.np, P.chunk, P.span), kBlock, 0, s>>>(P);
-  if (mu) k_current_adjoint<<<blocks_for(P.np), kBlock, 0, s>>>(P);
+  const unsigned blocks = (unsigned)scatter_blocks(P.np, P.chunk, P.span);
+  if (P.chunk >= kAdjBlock)
+    k_push_adjoint_tiled<1><<<blocks, kAdjBlock, 0, s>>>(P);
+  else
+    k_push_adjoint_tiled<4><<<blocks, kAdjBlock, 0, s>>>(P);
+  k_push_adjoint_list<<<std::min(blocks_for(P.np), 256u), kBlock, 0, s>>>(P);
+}
+
+void launch_current_adjoint(hipStream_t s, const AdjParticleArgs& P, const double* b, double* xn) {
+  if (P.np <= 0) return;
+  if (b)
+    k_current_adjoint<true><<<blocks_for(P.np), kBlock, 0, s>>>(P, b, xn);
+  else
+    k_current_adjoint<false><<<blocks_for(P.np), kBlock, 0, s>>>(P, nullptr, nullptr);
 }
 
 void launch_vbar(hipStream_t s, int64_t n3, const double* w, const double* v, double* vb) {
@@ -590,16 +721,6 @@ void launch_adjoint_rhs(hipStream_t s, int64_t n3, double dt, const double* lx1,
                         const double* lx, const double* ld, const double* lvb, double* b,
                         double* lxacc) {
   if (n3 > 0) k_adjoint_rhs<<<blocks_for(n3), kBlock, 0, s>>>(n3, dt, lx1, lv1, lx, ld, lvb, b, lxacc);
-}
-
-void launch_adjoint_update(hipStream_t s, int64_t n3, double dt, const double* b,
-                           const double* lvb, const double* ld, const double* xi, double* xn,
-                           double* red) {
-  // a grid of at most 1024 blocks: every block adds its two maxima to the
-  // same two words, so fewer blocks mean fewer contended atomics
-  if (n3 > 0)
-    k_adjoint_update<<<std::min(blocks_for(n3), 1024u), kBlock, 0, s>>>(n3, dt, b, lvb, ld, xi, xn,
-                                                                        red);
 }
 
 void launch_adjoint_out(hipStream_t s, int64_t n3, const double* lxacc, const double* lx,

@@ -330,6 +330,20 @@ int auto_chunk(int64_t np, int span) {
   return chunk;
 }
 
+// Particles per block of the adjoint's push terms.  Up to 98,304 particles blocks of
+// 128 with four lanes per particle (its chain of rows is what such a launch takes),
+// then one lane per particle in blocks of 512 to 2048, at least one per compute
+// unit.  Measured per launch with 128 / 512 / 1024 per block: 32,769 particles
+// 51 / 116 / 204 us, 65,537 95 / 115 / 199, 131,073 172 / 129 / 203, 262,145
+// 299 / 226 / 204; 2,097,152 with 512 / 1024 / 2048 / 4096: 1590 / 1513 / 1432 /
+// 1427 us.
+int adjoint_chunk(int64_t np) {
+  if (np <= 98304) return 128;
+  int chunk = 2048;
+  while (chunk > 512 && np < (int64_t)chunk * 256) chunk /= 2;
+  return chunk;
+}
+
 // most scatter blocks of any chunk and span (blocks of 256 particles, and those
 // of the last span that may be empty)
 int64_t scatter_blocks_max(int64_t np) { return scatter_blocks(np > 0 ? np : 1, 256, kMaxSpan); }
@@ -557,10 +571,10 @@ struct AdjWs {
   // in and lx0, lv0 out; 3 x np each); id: cell order -> caller order
   double *xs, *vs, *ws, *lx1s, *lv1s, *lx0s, *lv0s;
   int *id, *id2;
+  int* list;  // 1 + np: particles beyond their block's tile in the push terms
   SortScratch sb;
   double *J, *gfield, *lg_r, *mu;                     // 3, 6, 9, 3 x ncell (real)
   double2 *Fh, *F1h, *Jh, *inv, *l1, *lg, *lcur, *lJh;  // 9, 9, 3, 6, 9, 9, 9, 3 x ncell
-  double* red;                                        // [max|dxi|, max|xi|, bad]
 };
 
 size_t carve_adjoint(const Grid& G, int64_t np, char* base, AdjWs* A) {
@@ -573,6 +587,7 @@ size_t carve_adjoint(const Grid& G, int64_t np, char* base, AdjWs* A) {
   const size_t n1 = (size_t)(np > 0 ? np : 1);
   A->id = c.take<int>(n1);
   A->id2 = c.take<int>(n1);
+  A->list = c.take<int>(n1 + 1);
   A->sb.key = c.take<int>(n1);
   A->sb.count = c.take<int>(8 * nc);
   A->sb.offset = c.take<int>(8 * nc + 1);
@@ -590,7 +605,6 @@ size_t carve_adjoint(const Grid& G, int64_t np, char* base, AdjWs* A) {
   A->lg = c.take<double2>(9 * nc);
   A->lcur = c.take<double2>(9 * nc);
   A->lJh = c.take<double2>(3 * nc);
-  A->red = c.take<double>(4);
   return c.off + 256;
 }
 
@@ -1468,9 +1482,11 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   const double* A0r = fields + 2 * nc;
 
   const int span = auto_span(np, nc);
-  AdjParticleArgs PA{G, dt, S->q / S->m, np, auto_chunk(np, span), span, x, A.vb, A.xi, A.mu, gphi, A0r, A1r,
-                     A.lx, A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.red + 2};
-  launch_fill(s, 4, A.red, 0.0);
+  const int chunk = adjoint_chunk(np);
+  AdjParticleArgs PA{G, dt, S->q / S->m, np, chunk, std::max(span, chunk), x, A.vb, A.xi, A.mu, gphi, A0r, A1r,
+                     A.lx, A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.list, S->sc};
+  launch_reset_slots(s, S->sc, S_DVMAX, 2);
+  launch_finish(s, S->sc, nullptr, 0, A.list);
 
   // adjoints reaching w straight from the outputs
   launch_fill(s, 2 * 9 * nc, reinterpret_cast<double*>(A.lcur), 0.0);
@@ -1480,8 +1496,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   }
   launch_cn_adjoint(s, FP, lF1 ? A.l1 : nullptr, nullptr, A.lcur, A.lJh);
   current_adjoint(S, A);
-  for (double* p : {A.lx, A.ld, A.lvb}) launch_fill(s, n3, p, 0.0);
-  launch_particle_adjoint(s, PA, false, true);
+  launch_current_adjoint(s, PA, nullptr, nullptr);
   launch_adjoint_rhs(s, n3, dt, lx1, lv1, A.lx, A.ld, A.lvb, A.b, A.lxacc);
   if (n3 > 0)
     HIPCHK(hipMemcpyAsync(A.xi, A.b, sizeof(double) * n3, hipMemcpyDeviceToDevice, s));
@@ -1491,22 +1506,21 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   bool conv = false;
   double err = 0.0;
   for (it = 1; it <= max_iters + 1; ++it) {
-    for (double* p : {A.lx, A.ld, A.lvb}) launch_fill(s, n3, p, 0.0);
     launch_fill(s, 9 * nc, A.lg_r, 0.0);
     PA.xi = A.xi;
-    launch_particle_adjoint(s, PA, true, false);
+    launch_push_adjoint(s, PA);
     RealIO lgin = soa_io(A.lg_r, nc, 9);  // [grad phi, A^{n+1}, A^n]
     fft3_forward(s, G, 9, A.lg, lgin, twp(S), S->sc, 1.0 / (double)nc);
     launch_cn_adjoint(s, FP, nullptr, A.lg, nullptr, A.lJh);
     current_adjoint(S, A);
-    launch_particle_adjoint(s, PA, false, true);
-    launch_fill(s, 2, A.red, 0.0);
-    launch_adjoint_update(s, n3, dt, A.b, A.lvb, A.ld, A.xi, A.xn, A.red);
+    launch_current_adjoint(s, PA, A.b, A.xn);
+    const FinishJob jobs[2] = {{0, 0, 2, S_DVMAX, F_SPREAD_MAX}, {0, 0, 1, S_BAD, F_SPREAD_MAX}};
+    launch_finish(s, S->sc, jobs, 2, A.list);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(S->host, A.red, sizeof(double) * 3, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    const ecpic_status st = sync_read(S, S_DVMAX, S_BAD - S_DVMAX + 1);
+    if (st != ECPIC_OK) return st;
     const double dm = S->host[0], xm = S->host[1];
-    if (S->host[2] != 0.0)
+    if (S->host[S_BAD - S_DVMAX] != 0.0)
       return fail(ECPIC_EINVAL, "adjoint: an orbit crossed more than %d knots", kMaxPieces - 1);
     if (!std::isfinite(dm) || !std::isfinite(xm))
       return fail(ECPIC_ENONFINITE, "adjoint: non-finite iterate at iteration %d", it);

@@ -331,18 +331,19 @@ struct AdjParticleArgs {
   double* lgphi;       // push-side mesh adjoints (3 x ncell each), atomics
   double* lA0;
   double* lA1;
-  double* bad;         // set to 1 if an orbit had too many pieces
+  int* list;           // 1 + np: count (0 on entry) and particles beyond their block's LDS tile
+  Scratch sc;          // spread slots: S_BAD 1 if an orbit had too many pieces, and below
 };
-// eta: push terms with xi (fast for cell-ordered particles: local chunks fit
-// an LDS tile); mu: current terms
-void launch_particle_adjoint(hipStream_t s, const AdjParticleArgs& P, bool eta, bool mu);
+// push terms with xi into lx, ld, lvb and the mesh adjoints (added)
+void launch_push_adjoint(hipStream_t s, const AdjParticleArgs& P);
+// current terms with mu: b null, into lx, ld, lvb; else added to the push's lx, ld,
+// lvb (lx stored), the next iterate xn = b + (lvb + dt ld) / 2, max|xn - xi| and
+// max|xn| into the spread slots S_DVMAX and S_VMAX
+void launch_current_adjoint(hipStream_t s, const AdjParticleArgs& P, const double* b, double* xn);
 void launch_vbar(hipStream_t s, int64_t n3, const double* w, const double* v, double* vb);
 void launch_adjoint_rhs(hipStream_t s, int64_t n3, double dt, const double* lx1, const double* lv1,
                         const double* lx, const double* ld, const double* lvb, double* b,
                         double* lxacc);
-void launch_adjoint_update(hipStream_t s, int64_t n3, double dt, const double* b,
-                           const double* lvb, const double* ld, const double* xi, double* xn,
-                           double* red);
 void launch_adjoint_out(hipStream_t s, int64_t n3, const double* lxacc, const double* lx,
                         const double* xi, const double* lv1, double* lx0, double* lv0);
 // adjoint of k_cn; l1: next level's adjoint spectra (9, nullable); lg: gather

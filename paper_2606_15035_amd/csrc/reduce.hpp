@@ -160,9 +160,9 @@ __device__ __forceinline__ int64_t chunk_particle(int64_t base, int span, int k)
 }
 
 // block-wide minimum of M ints at once (one barrier pair for all of them)
-template <int M>
+template <int M, int BLOCK = kBlock>
 __device__ __forceinline__ void block_min_ints(int (&v)[M]) {
-  __shared__ int lds_i[M][kBlock / kWave];
+  __shared__ int lds_i[M][BLOCK / kWave];
   const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
 #pragma unroll
   for (int m = 0; m < M; ++m) {
@@ -175,7 +175,7 @@ __device__ __forceinline__ void block_min_ints(int (&v)[M]) {
   for (int m = 0; m < M; ++m) {
     int r = lds_i[m][0];
 #pragma unroll
-    for (int w = 1; w < kBlock / kWave; ++w) r = min(r, lds_i[m][w]);
+    for (int w = 1; w < BLOCK / kWave; ++w) r = min(r, lds_i[m][w]);
     v[m] = r;
   }
   __syncthreads();
