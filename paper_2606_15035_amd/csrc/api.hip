@@ -239,6 +239,7 @@ struct ecpic_sim {
   int* gwork;  // gather work list: [count, particles whose orbits left their block's LDS tile]
   int* sboxes;  // node boxes of the scatter's chunks, found in a step's first pass
   int* gboxes;  // node boxes of the gather's blocks, likewise
+  uint16_t* gorder;  // the order in which they take their particles
   double2* tw[3];
   Scratch sc;
   double* host = nullptr;  // pinned read-back
@@ -411,6 +412,8 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->gwork = w.take<int>((np > 0 ? np : 1) + 1);
   S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
   S->gboxes = w.take<int>((size_t)kBoxInts * std::max<int64_t>(particle_blocks(np), 1));
+  const int64_t gslots = gather_slots(np, nc);
+  S->gorder = gslots > 0 ? w.take<uint16_t>((size_t)gslots) : nullptr;
   // the plain iteration's next iterate is the gather's output, so the gather
   // (and the step's set-up) can hand the scatter vbar^p directly
   S->vbar = S->cfg.anderson_depth == 0 ? w.take<double>(n3) : nullptr;
@@ -925,7 +928,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     if (prof_g) HIPCHK(hipEventRecord(S->ev[2], s));
     on_store(S, [&](auto& st, auto&) {  // v^{n+1,p+1}
       launch_gather_push(s, r, P, st, S->vit, S->vnew, S->vbar, S->gbuf, S->gwork, S->sc, prev,
-                         ChunkBoxes{S->gboxes, p >= 1});
+                         ChunkBoxes{S->gboxes, p >= 1, S->gorder});
     });
     if (prof_g) HIPCHK(hipEventRecord(S->ev[3], s));
     AndersonVecs av{};

@@ -168,6 +168,10 @@ constexpr int kBoxInts = 12;
 struct ChunkBoxes {
   int* box = nullptr;
   int reuse = 0;
+  // gather only: the order in which a block takes its particles (offsets from
+  // its first one, one per particle slot), found and kept with the box; null:
+  // as they are stored
+  uint16_t* order = nullptr;
 };
 // Orbit current of iterate vit; with vbar non-null, vbar^p (3 x np) is read
 // from there instead of being formed from v^n and vit
@@ -190,6 +194,7 @@ struct GatherGrid {
   bool whole_mesh;
 };
 GatherGrid gather_grid(int64_t np, int64_t ncell);
+int64_t gather_slots(int64_t np, int64_t ncell);  // entries of ChunkBoxes::order, 0: none
 // work: 1 + np ints, work[0] = 0 on entry; the tiled kernel lists the particles
 // whose orbits leave their block's node box, the second kernel runs them from
 // global memory; the per-pass finishing kernel resets work[0].  vbar_out

@@ -323,6 +323,14 @@ __device__ __forceinline__ void orbit_nodes(double x0, double d, double invH, in
   lo += Spline<R>::first_off;
 }
 
+// Knots strictly inside one axis of an orbit (by more than kKnotEps), which the
+// kernels order particles by; nothing but the order rests on it.
+__device__ __forceinline__ int knots_crossed(double x0, double d, double invH, double knot_off) {
+  const double u0 = x0 * invH + knot_off, u1 = (x0 + d) * invH + knot_off;
+  const int hi = to_int_clamped(ceil(fmax(u0, u1) - kKnotEps));
+  return max(hi - to_int_clamped(floor(fmin(u0, u1) + kKnotEps)) - 1, 0);
+}
+
 // Base node of the stencil of the point at s (the rule over the whole orbit
 // without splitting, where every point takes the stencil of its own cell).
 template <int R>

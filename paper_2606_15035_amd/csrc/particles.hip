@@ -1267,10 +1267,11 @@ struct MeshGather {  // the whole mesh in LDS, nodes in flat order
 // as they finish (no block barrier after the orbit loops: a wavefront with fewer
 // pieces does not wait for the block's slowest one), so that they hold no
 // registers through the orbit loops.
+constexpr int kMaxGatherBatches = 4;
 struct GatherTotals {
   unsigned long long dvm, vm, bad;  // bit patterns of non-negative doubles
   int pieces;
-  double aa[kBlock / kWave][2];  // one row per wavefront
+  double aa[kMaxGatherBatches * kBlock / kWave][2];  // one row per 64 particles (or wavefront)
   unsigned int done;
 };
 
@@ -1282,7 +1283,7 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
                                              double* __restrict__ vnew,
                                              double* __restrict__ vbar_out, Acc&& make_acc,
                                              Inside&& inside, const AndersonPrev& prev,
-                                             GatherTotals& tot) {
+                                             GatherTotals& tot, int aa_sum) {
   double dvm = 0.0, vm = 0.0, bad = 0.0, npieces = 0.0;
   double aa[2] = {0.0, 0.0};
   if (active) {
@@ -1342,7 +1343,7 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
     aa[0] = wave_sum(aa[0]);
     aa[1] = wave_sum(aa[1]);
     if (threadIdx.x % kWave == 0)
-      for (int k = 0; k < 2; ++k) tot.aa[threadIdx.x / kWave][k] += aa[k];
+      for (int k = 0; k < 2; ++k) tot.aa[aa_sum][k] += aa[k];
   }
 }
 
@@ -1351,7 +1352,7 @@ __device__ __forceinline__ void totals_init(GatherTotals& tot) {
     tot.dvm = tot.vm = tot.bad = 0ull;
     tot.pieces = 0;
     tot.done = 0u;
-    for (int w = 0; w < kBlock / kWave; ++w) tot.aa[w][0] = tot.aa[w][1] = 0.0;
+    for (auto& a : tot.aa) a[0] = a[1] = 0.0;
   }
 }
 
@@ -1372,9 +1373,70 @@ __device__ __forceinline__ void totals_finish(GatherTotals& tot, const Scratch& 
   if (anderson)
     for (int k = 0; k < 2; ++k) {
       double a = tot.aa[0][k];
-      for (int w = 1; w < kBlock / kWave; ++w) a += tot.aa[w][k];
+      for (int w = 1; w < kMaxGatherBatches * kBlock / kWave; ++w) a += tot.aa[w][k];
       sc.region(P_AA)[k * aa_rows + aa_row] = a;
     }
+}
+
+// The order in which a gather block takes its particles: by the knots that
+// their orbits cross, the most first, as stored where these are equal.  A
+// wavefront runs its 64 orbits in lockstep, as long as its longest one: with
+// the particles as stored it ran 1.9 pieces for 1.3 per orbit on average (cold
+// beams, 64 per cell).  Per pass, as stored / ordered: quadratic, 2,097,152
+// 280 / 249 us; mixed, 33,554,432 with orbits of several cells 6565 / 5571 us;
+// cubic, 524,288 in two batches of 256 257 / 209 us.  Blocks of one batch keep the
+// stored order: one wavefront would get all the long orbits and the others
+// would be done early (300,007 at 9 per cell: 112 / 126 us).  cls:
+// the thread's counts (batch k in bits 4k .. 4k+3); hist: 256 ints of LDS;
+// order: one entry per particle slot of the block.  Called by the whole block.
+__device__ __forceinline__ void block_order(unsigned cls, int batches, int* hist,
+                                            uint16_t* __restrict__ order) {
+  constexpr int kSets = kMaxGatherBatches * kBlock / kWave;  // 64 particles each
+  static_assert(kBlock == 16 * kSets, "one thread per count and set");
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+  hist[threadIdx.x] = 0;
+  __syncthreads();
+  // hist[(15 - count) * kSets + set]; rank: the lane's place among those of its count
+  int rank[kMaxGatherBatches];
+#pragma unroll
+  for (int k = 0; k < kMaxGatherBatches; ++k) {
+    rank[k] = 0;
+    if (k >= batches) continue;
+    const int c = 15 - (int)((cls >> (4 * k)) & 15u);
+    unsigned long long todo = __ballot(true);
+    while (todo) {
+      const int leader = __ffsll((long long)todo) - 1;
+      const int lc = __builtin_amdgcn_readlane(c, leader);
+      const unsigned long long group = __ballot(c == lc);
+      if (c == lc) rank[k] = __popcll(group & ((1ull << lane) - 1ull));
+      if (lane == leader) hist[lc * kSets + k * (kBlock / kWave) + wid] = __popcll(group);
+      todo &= ~group;
+    }
+  }
+  __syncthreads();
+  const int n = hist[threadIdx.x];
+  int incl = n;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int t = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += t;
+  }
+  __syncthreads();
+  hist[threadIdx.x] = incl;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < wid; ++w) before += hist[w * kWave + kWave - 1];
+  __syncthreads();
+  hist[threadIdx.x] = before + incl - n;  // slots before this count and set
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMaxGatherBatches; ++k) {
+    if (k >= batches) continue;
+    const int c = 15 - (int)((cls >> (4 * k)) & 15u);
+    order[hist[c * kSets + k * (kBlock / kWave) + wid] + rank[k]] =
+        (uint16_t)(k * kBlock + threadIdx.x);
+  }
+  __syncthreads();
 }
 
 // Two waves per SIMD for the quadratic gather: its orbit loop fits 256
@@ -1419,7 +1481,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
           [&](const int*) {
             return GlobalGather{F.g, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
           },
-          [](int, const double*, const double*, int*) { return true; }, prev, tot);
+          [](int, const double*, const double*, int*) { return true; }, prev, tot,
+          threadIdx.x / kWave);
     }
     totals_finish(tot, sc, prev.w != nullptr, aa_row0 + bid, aa_rows);
   } else {
@@ -1438,7 +1501,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
             [&](const int*) {
               return MeshGather{tile, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
             },
-            [](int, const double*, const double*, int*) { return true; }, prev, tot);
+            [](int, const double*, const double*, int*) { return true; }, prev, tot,
+            threadIdx.x / kWave);
       }
     } else {
       // the block's node box: reference node sref, origin tlo relative to it and
@@ -1467,9 +1531,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         for (int k = 0; k < 12; ++k) mv[k] = 0x3fffffff;
 #pragma unroll
         for (int a = 0; a < 3; ++a) sref[a] = s_ref[a];
+        unsigned cls = 0u;  // per batch: knots that the thread's orbit crosses, in 4 bits
         for (int k = 0; k < P.gper; ++k) {
           const int64_t i = first + k * kBlock + threadIdx.x;
           if (i >= P.np) break;
+          int crossed = 0;
           double x0[3], va[3], vi[3];
           st.x_of(P.G, P.np, i, x0);
           st.v_of(P.np, i, va);
@@ -1484,8 +1550,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
             mv[3 + a] = min(mv[3 + a], -(rel + n));
             mv[6 + a] = min(mv[6 + a], rel + (b0 - lo));
             mv[9 + a] = min(mv[9 + a], -(rel + (b0 - lo) + W));
+            crossed += min(knots_crossed(x0[a], d, P.G.invH[a], Spline<R>::base_off), 15);
           }
+          cls |= (unsigned)min(crossed, 15) << (4 * k);
         }
+        if (SPLIT && bx.order)
+          block_order(cls, P.gper, reinterpret_cast<int*>(tile2),
+                      bx.order + first);
         block_min_ints<12>(mv);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -1537,8 +1608,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         }
       }
       __syncthreads();
+      // Sets of 64 particles, the longest orbits first, go to the wavefronts there and
+      // back (0 1 2 3, 3 2 1 0, ..); which wavefront is the first changes from block to
+      // block, since wavefront w of every block sits on the same SIMD.
+      constexpr int kWaves = kBlock / kWave;
+      const int wid = __builtin_amdgcn_readfirstlane(((int)threadIdx.x / kWave + bid / 8) % kWaves);
       for (int k = 0; k < P.gper; ++k) {
-        const int64_t i = first + k * kBlock + threadIdx.x;
+        const int set = k * kWaves + (k & 1 ? kWaves - 1 - wid : wid);
+        const int64_t slot = first + set * kWave + threadIdx.x % kWave;
+        const int64_t i = SPLIT && bx.order ? first + bx.order[slot] : slot;
         gather_batch<R, SPLIT>(
             P, st, (int)i, i < P.np, vit, vnew, vbar_out,
             [&](const int* shift) {
@@ -1558,7 +1636,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
               if (!in) work[1 + atomicAdd(work, 1)] = ip;
               return in;
             },
-            prev, tot);
+            prev, tot, set);
       }
     }
     totals_finish(tot, sc, prev.w != nullptr, aa_row0 + bid, aa_rows);
@@ -1903,11 +1981,11 @@ void launch_scatter(hipStream_t s, int r, const StepParams& P, const PS& st, con
 }
 
 // Batches of 256 particles per gather block: as many as leave four blocks per
-// compute unit, at most 4, and no more than the particles of 16 cells, whose box
-// fits the tile.
+// compute unit, at most 4, and no more than the particles of 32 cells, whose box
+// fits the tile (4x4x2 cells with cubic stencils and orbits of a cell: 9x9x7 nodes).
 int gather_batches(int64_t np, int64_t ncell) {
-  int g = 4;
-  while (g > 1 && (np < (int64_t)g * kBlock * 1024 || g * kBlock * ncell > 16 * np)) g /= 2;
+  int g = kMaxGatherBatches;
+  while (g > 1 && (np < (int64_t)g * kBlock * 1024 || g * kBlock * ncell > 32 * np)) g /= 2;
   return g;
 }
 
@@ -1918,6 +1996,11 @@ GatherGrid gather_grid(int64_t np, int64_t ncell) {
   g.whole_mesh = ncell <= kGatherTileNodes;
   g.list_blocks = g.whole_mesh ? 0 : std::min((int)blocks_for(np), 512);
   return g;
+}
+
+int64_t gather_slots(int64_t np, int64_t ncell) {
+  const GatherGrid g = gather_grid(np, ncell);
+  return g.batches > 1 ? (int64_t)g.blocks * g.batches * kBlock : 0;
 }
 
 template <class PS>
