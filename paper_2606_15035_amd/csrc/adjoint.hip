@@ -115,19 +115,6 @@ __device__ __forceinline__ void weight_at(int k, double t, double& w, double& dw
   dw = m + c2 * t;
 }
 
-// sum over the four lanes of a quad, to each of them
-__device__ __forceinline__ double quad_sum(double v) {
-  auto swap = [](double u, auto perm) {
-    constexpr int kPerm = decltype(perm)::value;
-    return __hiloint2double(
-        __builtin_amdgcn_mov_dpp(__double2hiint(u), kPerm, 0xf, 0xf, true),
-        __builtin_amdgcn_mov_dpp(__double2loint(u), kPerm, 0xf, 0xf, true));
-  };
-  v += swap(v, std::integral_constant<int, 0xB1>{});  // lanes 1 0 3 2
-  v += swap(v, std::integral_constant<int, 0x4E>{});  // lanes 2 3 0 1
-  return v;
-}
-
 // The push terms of one particle (eta = (q/m) xi) in tensor-product form.  With
 // eta'_j = eta_j / H_j and derivatives per unit of cell coordinate (S_g = X_a Y_b
 // Z_c; the degree-2 second derivatives are 1, -2, 1), w_q the weights of the

@@ -411,7 +411,8 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   for (int a = 0; a < 3; ++a) S->tw[a] = w.take<double2>(S->G.n[a] / 2);
   S->gwork = w.take<int>((np > 0 ? np : 1) + 1);
   S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
-  S->gboxes = w.take<int>((size_t)kBoxInts * std::max<int64_t>(particle_blocks(np), 1));
+  const GatherGrid gg = gather_grid(np, nc);
+  S->gboxes = w.take<int>((size_t)kBoxInts * std::max(gg.blocks, 1));
   const int64_t gslots = gather_slots(np, nc);
   S->gorder = gslots > 0 ? w.take<uint16_t>((size_t)gslots) : nullptr;
   // the plain iteration's next iterate is the gather's output, so the gather
@@ -425,6 +426,7 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
       std::max<int64_t>(mesh_blocks(nc), cn_pencil_blocks(S->G)));
   S->sc.part_stride = std::max<int64_t>((int64_t)kMaxSumValues * (maxblk > 0 ? maxblk : 1),
                                         (int64_t)kAndersonSums * anderson_dot_blocks(3 * np));
+  S->sc.part_stride = std::max<int64_t>(S->sc.part_stride, 2 * (gg.blocks + gg.list_blocks));
   S->sc.part = w.take<double>((size_t)P_NSITES * S->sc.part_stride);
   if (state_bytes) *state_bytes = st.off + 256;
   if (ws_bytes) *ws_bytes = w.off + 256;

@@ -185,12 +185,12 @@ struct AndersonPrev {
   const double* w = nullptr;
   const double* g = nullptr;
 };
-// Launch shape of the gather (particles.hip): batches of 256 particles per
+// Launch shape of the gather (particles.hip): lanes per particle, batches of 256 / lanes particles per
 // block, blocks, whether the whole mesh sits in LDS, and the blocks of the
 // kernel that runs the listed particles; Anderson partial sums have
 // blocks + list_blocks rows
 struct GatherGrid {
-  int batches, blocks, list_blocks;
+  int lanes, batches, blocks, list_blocks;
   bool whole_mesh;
 };
 GatherGrid gather_grid(int64_t np, int64_t ncell);

@@ -293,6 +293,21 @@ __device__ __forceinline__ void gather_piece(const Grid& G, const double* x0, co
   gather_points<R, NQ, WITH_U>(G, x0, d, base, sq, wq, acc, Uh, gp, D, Ub, pou);
 }
 
+// weight and derivative (per unit of cell coordinate) of stencil node k at t, for
+// a k that differs from lane to lane
+template <int R>
+__device__ __forceinline__ void lane_weight(int k, double t, double& w, double& dw) {
+  double ws[R + 1], ds[R + 1];
+  Spline<R>::wd(t, ws, ds);
+  w = ws[0];
+  dw = ds[0];
+#pragma unroll
+  for (int j = 1; j <= R; ++j) {
+    w = k == j ? ws[j] : w;
+    dw = k == j ? ds[j] : dw;
+  }
+}
+
 // ---- one orbit piece: gather for the push ----------------------------------
 // The push needs grad phi-bar and (D A)^T vbar only.  With b_g(s) = vbar . A_g(s),
 //   ((D A)^T vbar)_j = sum_g int b_g(s) d_j S_g(x(s)) ds,
@@ -304,11 +319,14 @@ __device__ __forceinline__ void gather_piece(const Grid& G, const double* x0, co
 // multiply those column sums, not every node.  Derivatives are taken per unit
 // of cell coordinate: dtv accumulates H_j ((D A)^T vbar)_j, and the caller
 // multiplies by 1/H_j once per particle.
-template <int R, int NQ, class Acc>
+// LANES = 1: the whole stencil.  4: lane `part` of a quad takes the rows of its
+// plane a = part (degree 1: the one row a = part / 2, b = part % 2), and the sums
+// of the quad are the particle's.
+template <int R, int LANES, int NQ, class Acc>
 __device__ __forceinline__ void push_points(const Grid& G, const double* x0, const double* d,
                                             const double* base, const double* sq,
                                             const double* wq, const double* vb, const Acc& acc,
-                                            double* gp, double* dtv) {
+                                            int part, double* gp, double* dtv) {
   constexpr int W = R + 1;
   double tx[NQ], ty[NQ], Z[NQ][W], dZ[NQ][W];
 #pragma unroll
@@ -321,76 +339,106 @@ __device__ __forceinline__ void push_points(const Grid& G, const double* x0, con
   const int fx = to_int_clamped(base[0]) + Spline<R>::first_off;
   const int fy = to_int_clamped(base[1]) + Spline<R>::first_off;
   const int fz = to_int_clamped(base[2]) + Spline<R>::first_off;
-#pragma unroll
-  for (int a = 0; a < W; ++a) {
-    double Xw[NQ], dXw[NQ];  // quadrature weight x X_a, x dX_a/dx
+  // one row (a, b): Xw, dXw = quadrature weight x X_a, x dX_a/dx; ybd gives Y_b, dY_b
+  auto stencil_row = [&](int a, int b, const double (&Xw)[NQ], const double (&dXw)[NQ],
+                         auto&& ybd) {
+    double xyw[NQ], dxyw[NQ], xdyw[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      double Xq, dXq;
-      Spline<R>::wk(a, tx[q], Xq, dXq);
-      Xw[q] = wq[q] * Xq;
-      dXw[q] = wq[q] * dXq;
+      double Yq, dYq;
+      ybd(ty[q], Yq, dYq);
+      xyw[q] = Xw[q] * Yq;
+      dxyw[q] = dXw[q] * Yq;
+      xdyw[q] = Xw[q] * dYq;
+    }
+    const int row = acc.row(fx + a, fy + b);
+    double B[NQ], dB[NQ];
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      const auto p = acc.node(row, fz + c);
+      double f[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) f[k] = p[k];
+      const double a0 = vb[0] * f[3] + vb[1] * f[4] + vb[2] * f[5];  // vbar . A^n_g
+      const double da = vb[0] * f[6] + vb[1] * f[7] + vb[2] * f[8] - a0;
+      double I = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        I += xyw[q] * Z[q][c];
+        const double bq = a0 + sq[q] * da;  // vbar . A_g(s_q)
+        B[q] = c == 0 ? bq * Z[q][c] : B[q] + bq * Z[q][c];
+        dB[q] = c == 0 ? bq * dZ[q][c] : dB[q] + bq * dZ[q][c];
+      }
+      gp[0] += f[0] * I;
+      gp[1] += f[1] * I;
+      gp[2] += f[2] * I;
     }
 #pragma unroll
-    for (int b = 0; b < W; ++b) {
-      double xyw[NQ], dxyw[NQ], xdyw[NQ];
+    for (int q = 0; q < NQ; ++q) {
+      dtv[0] += dxyw[q] * B[q];
+      dtv[1] += xdyw[q] * B[q];
+      dtv[2] += xyw[q] * dB[q];
+    }
+  };
+  if constexpr (LANES == 1) {
+#pragma unroll
+    for (int a = 0; a < W; ++a) {
+      double Xw[NQ], dXw[NQ];
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        double Yq, dYq;
-        Spline<R>::wk(b, ty[q], Yq, dYq);
-        xyw[q] = Xw[q] * Yq;
-        dxyw[q] = dXw[q] * Yq;
-        xdyw[q] = Xw[q] * dYq;
+        double Xq, dXq;
+        Spline<R>::wk(a, tx[q], Xq, dXq);
+        Xw[q] = wq[q] * Xq;
+        dXw[q] = wq[q] * dXq;
       }
-      const int row = acc.row(fx + a, fy + b);
-      double B[NQ], dB[NQ];
 #pragma unroll
-      for (int c = 0; c < W; ++c) {
-        const auto p = acc.node(row, fz + c);
-        double f[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) f[k] = p[k];
-        const double a0 = vb[0] * f[3] + vb[1] * f[4] + vb[2] * f[5];  // vbar . A^n_g
-        const double da = vb[0] * f[6] + vb[1] * f[7] + vb[2] * f[8] - a0;
-        double I = 0.0;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          I += xyw[q] * Z[q][c];
-          const double bq = a0 + sq[q] * da;  // vbar . A_g(s_q)
-          B[q] = c == 0 ? bq * Z[q][c] : B[q] + bq * Z[q][c];
-          dB[q] = c == 0 ? bq * dZ[q][c] : dB[q] + bq * dZ[q][c];
-        }
-        gp[0] += f[0] * I;
-        gp[1] += f[1] * I;
-        gp[2] += f[2] * I;
-      }
+      for (int b = 0; b < W; ++b)
+        stencil_row(a, b, Xw, dXw,
+                    [&](double t, double& y, double& dy) { Spline<R>::wk(b, t, y, dy); });
+    }
+  } else {
+    const int a = R == 1 ? part / 2 : part;
+    if (a < W) {
+      double Xw[NQ], dXw[NQ];
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        dtv[0] += dxyw[q] * B[q];
-        dtv[1] += xdyw[q] * B[q];
-        dtv[2] += xyw[q] * dB[q];
+        double Xq, dXq;
+        lane_weight<R>(a, tx[q], Xq, dXq);
+        Xw[q] = wq[q] * Xq;
+        dXw[q] = wq[q] * dXq;
+      }
+      if constexpr (R == 1) {
+        const int b = part % 2;
+        stencil_row(a, b, Xw, dXw,
+                    [&](double t, double& y, double& dy) { lane_weight<R>(b, t, y, dy); });
+      } else {
+#pragma unroll
+        for (int b = 0; b < W; ++b)
+          stencil_row(a, b, Xw, dXw,
+                      [&](double t, double& y, double& dy) { Spline<R>::wk(b, t, y, dy); });
       }
     }
   }
 }
 
-template <int R, class Acc>
+template <int R, int LANES, class Acc>
 __device__ __forceinline__ void push_piece(const Grid& G, const double* x0, const double* d,
                                            double s0, double s1, const double* base,
-                                           const double* vb, const Acc& acc, double* gp,
+                                           const double* vb, const Acc& acc, int part, double* gp,
                                            double* dtv) {
   constexpr int NQ = Quad<R>::NQ;
   double sq[NQ], wq[NQ];
   piece_rule<R>(s0, s1, sq, wq);
-  push_points<R, NQ>(G, x0, d, base, sq, wq, vb, acc, gp, dtv);
+  push_points<R, LANES, NQ>(G, x0, d, base, sq, wq, vb, acc, part, gp, dtv);
 }
 
 // point interpolant of A^n (which = 0) or A^{n+1} (which = 1) at x, whose
 // stencil nodes are moved into the particle frame by +shift[a] (a multiple
 // of n[a]; zero unless x is a wrapped end point)
-template <int R, class Acc>
+// LANES, part: as in push_points
+template <int R, int LANES, class Acc>
 __device__ __forceinline__ void point_A_acc(const Grid& G, const double* x, const int* shift,
-                                            const Acc& acc, int which, double* out) {
+                                            const Acc& acc, int which, int part, double* out) {
   constexpr int W = R + 1;
   double w[3][W];
   int f[3];
@@ -403,18 +451,32 @@ __device__ __forceinline__ void point_A_acc(const Grid& G, const double* x, cons
   }
   out[0] = out[1] = out[2] = 0.0;
   const int off = which ? 6 : 3;
+  auto stencil_row = [&](int a, int b, double wxy) {
+    const int row = acc.row(f[0] + a, f[1] + b);
 #pragma unroll
-  for (int a = 0; a < W; ++a) {
+    for (int c = 0; c < W; ++c) {
+      const auto p = acc.node(row, f[2] + c);
+      const double wt = wxy * w[2][c];
 #pragma unroll
-    for (int b = 0; b < W; ++b) {
-      const int row = acc.row(f[0] + a, f[1] + b);
-      const double wxy = w[0][a] * w[1][b];
+      for (int l = 0; l < 3; ++l) out[l] += p[off + l] * wt;
+    }
+  };
+  if constexpr (LANES == 1) {
 #pragma unroll
-      for (int c = 0; c < W; ++c) {
-        const auto p = acc.node(row, f[2] + c);
-        const double wt = wxy * w[2][c];
+    for (int a = 0; a < W; ++a)
 #pragma unroll
-        for (int l = 0; l < 3; ++l) out[l] += p[off + l] * wt;
+      for (int b = 0; b < W; ++b) stencil_row(a, b, w[0][a] * w[1][b]);
+  } else {
+    const int a = R == 1 ? part / 2 : part;
+    double wa = w[0][0];
+#pragma unroll
+    for (int k = 1; k < W; ++k) wa = a == k ? w[0][k] : wa;
+    if (a < W) {
+      if constexpr (R == 1) {
+        stencil_row(a, part % 2, wa * (part % 2 ? w[1][1] : w[1][0]));
+      } else {
+#pragma unroll
+        for (int b = 0; b < W; ++b) stencil_row(a, b, wa * w[1][b]);
       }
     }
   }
@@ -1193,16 +1255,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 // and x0, d and i are hidden from the compiler there, which would otherwise
 // carry cell coordinates and addresses formed before the loop to their uses
 // behind it (28 spilled registers, 0.35 against 0.28 ms per pass at 32^3).
-template <int R, bool SPLIT, class Acc, class PS>
+// With LANES = 4 the quad's lanes all end with the particle's v^{n+1,p+1}.
+template <int R, bool SPLIT, int LANES, class Acc, class PS>
 __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& acc, const PS& st,
-                                                int& i, double (&x0)[3], double (&d)[3],
-                                                const double (&vb)[3], double* vn, double& npieces,
-                                                double& bad) {
+                                                int part, int& i, double (&x0)[3],
+                                                double (&d)[3], const double (&vb)[3], double* vn,
+                                                double& npieces, double& bad) {
   double gp[3] = {0.0, 0.0, 0.0};
   double dtv[3] = {0.0, 0.0, 0.0};  // H_j ((D A)^T vbar)_j until the pieces are summed
   if constexpr (SPLIT) {
     const bool ok = for_each_piece<R>(x0, d, P.G, [&](double s0, double s1, const double* base) {
-      push_piece<R>(P.G, x0, d, s0, s1, base, vb, acc, gp, dtv);
+      push_piece<R, LANES>(P.G, x0, d, s0, s1, base, vb, acc, part, gp, dtv);
       npieces += 1.0;
     });
     if (!ok) bad = 1.0;
@@ -1210,7 +1273,7 @@ __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& 
     for (int q = 0; q < P.rule.n; ++q) {
       double base[3], sq, wq;
       unsplit_point<R>(P.G, P.rule, q, x0, d, base, sq, wq);
-      push_points<R, 1>(P.G, x0, d, base, &sq, &wq, vb, acc, gp, dtv);
+      push_points<R, LANES, 1>(P.G, x0, d, base, &sq, &wq, vb, acc, part, gp, dtv);
     }
     npieces += 1.0;
   }
@@ -1231,10 +1294,16 @@ __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& 
     x1[a] = wrap_pos(x0[a] + d[a], P.G.L[a], P.G.invL[a]);
     sh1[a] = (int)rint((x0[a] + d[a] - x1[a]) * P.G.invL[a]) * P.G.n[a];
   }
-  point_A_acc<R>(P.G, x0, zero, acc, 0, A0s);
-  point_A_acc<R>(P.G, x1, sh1, acc, 1, A1e);
+  point_A_acc<R, LANES>(P.G, x0, zero, acc, 0, part, A0s);
+  point_A_acc<R, LANES>(P.G, x1, sh1, acc, 1, part, A1e);
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
+    if constexpr (LANES == 4) {
+      gp[j] = quad_sum(gp[j]);
+      dtv[j] = quad_sum(dtv[j]);
+      A0s[j] = quad_sum(A0s[j]);
+      A1e[j] = quad_sum(A1e[j]);
+    }
     const double Pn = mi * va[j] + qi * A0s[j];
     const double DAv = dtv[j] * P.G.invH[j];                  // ((D A)^T vbar)_j
     const double P1 = Pn + P.dt * (-qi * gp[j] + qi * DAv);   // eq. orbit-P-update
@@ -1275,9 +1344,9 @@ struct GatherTotals {
   unsigned int done;
 };
 
-// The gather and push of one batch of 256 particles; i = particle, or active
-// false.  With inside(x0, d) false the lane's particle is left to the list.
-template <int R, bool SPLIT, class PS, class Acc, class Inside>
+// The gather and push of one batch of 256 / LANES particles; i = particle (of the
+// lane's quad, with four lanes each), or active false.  With inside(x0, d) false the lane's particle is left to the list.
+template <int R, bool SPLIT, int LANES, class PS, class Acc, class Inside>
 __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, int i,
                                              bool active, const double* __restrict__ vit,
                                              double* __restrict__ vnew,
@@ -1286,6 +1355,7 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
                                              GatherTotals& tot, int aa_sum) {
   double dvm = 0.0, vm = 0.0, bad = 0.0, npieces = 0.0;
   double aa[2] = {0.0, 0.0};
+  const int part = LANES == 1 ? 0 : (int)threadIdx.x % LANES;
   if (active) {
     double x0[3], vb[3], d[3];
     {
@@ -1302,7 +1372,8 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
     int shift[3];
     if (inside(i, x0, d, shift)) {
       double vn[3];
-      gather_push_one<R, SPLIT>(P, make_acc(shift), st, i, x0, d, vb, vn, npieces, bad);
+      gather_push_one<R, SPLIT, LANES>(P, make_acc(shift), st, part, i, x0, d, vb, vn, npieces,
+                                       bad);
       // vn is complete here: otherwise its y and z sums sink behind the branches
       // below and every field value they use stays in registers until then
       // (more than 200 spilled)
@@ -1312,13 +1383,16 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
       load3(vit, P.np, i, vi);
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        vnew[j * P.np + i] = vn[j];
-        if (vbar_out) vbar_out[j * P.np + i] = 0.5 * (vn[j] + va[j]);  // the next pass's vbar
+        if (LANES == 1 || part == j) {
+          vnew[j * P.np + i] = vn[j];
+          if (vbar_out) vbar_out[j * P.np + i] = 0.5 * (vn[j] + va[j]);  // the next pass's vbar
+        }
         dvm = fmax(dvm, fabs(vn[j] - vi[j]));
         vm = fmax(vm, fabs(vn[j]));
         if (!isfinite(vn[j])) bad = 2.0;  // max-reductions drop NaN: flag it explicitly
       }
-      if (prev.w) {  // Anderson mixing over one difference: dF . dF and dF . f_p
+      if (part != 0) npieces = 0.0;
+      if (prev.w && part == 0) {  // Anderson mixing over one difference: dF . dF and dF . f_p
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
           const int64_t e = j * P.np + i;
@@ -1454,7 +1528,7 @@ constexpr int kGatherWavesPerSimd = R == 2 ? 2 : 1;
 // list is a second kernel (GATHER_LIST), so each keeps its own register budget.
 // After the first Picard pass of a step the block takes the box it stored in
 // that pass.
-template <int R, int FROM, class PS, bool SPLIT>
+template <int R, int FROM, class PS, bool SPLIT, int LANES>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     kGatherWavesPerSimd<R>))) void k_gather_push(StepParams P, PS st,
                                                  const double* __restrict__ vit,
@@ -1470,13 +1544,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   if constexpr (FROM == GATHER_LIST) {
     __syncthreads();
     const int count = work[0];  // written by the tiled kernel (previous launch)
-    // entry j to block j % grid: few lanes per wavefront.  Every lane reads nodes
-    // of its own, 5 cache lines each, and one CU's line rate bounds a wavefront
-    // (300,007 particles at 9 per cell: 70 us per pass with 64 lanes at a time)
-    for (int t = 0; t * gridDim.x + bid < count; t += kBlock) {
-      const int j = (t + (int)threadIdx.x) * (int)gridDim.x + bid;
+    // entry j to block j % grid: the entries are the longest orbits, and every lane
+    // reads nodes of its own, 5 cache lines each, so that a particle's chain of rows
+    // and one CU's line rate bound the kernel.  With four lanes per particle, per
+    // pass: 300,007 particles at 9 per cell 56 -> 25 us, 100,002 at 12 16 -> 9 us.
+    constexpr int kEntries = kBlock / LANES;
+    for (int t = 0; t * gridDim.x + bid < count; t += kEntries) {
+      const int j = (t + (int)threadIdx.x / LANES) * (int)gridDim.x + bid;
       const bool active = j < count;
-      gather_batch<R, SPLIT>(
+      gather_batch<R, SPLIT, LANES>(
           P, st, active ? work[1 + j] : 0, active, vit, vnew, vbar_out,
           [&](const int*) {
             return GlobalGather{F.g, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
@@ -1489,14 +1565,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     __shared__ double2 tile2[kGatherTileNodes * kGbufStride / 2];
     lds_cdouble* tile = (lds_cdouble*)(reinterpret_cast<double*>(tile2));
     const double2* g2 = reinterpret_cast<const double2*>(F.g);
-    const int64_t first = (int64_t)bid * P.gper * kBlock;
+    constexpr int kBatch = kBlock / LANES;  // particles
+    const int64_t first = (int64_t)bid * P.gper * kBatch;
     if constexpr (FROM == GATHER_MESH) {
       const int n2 = (int)P.G.ncell * (kGbufStride / 2);
       for (int t = threadIdx.x; t < n2; t += kBlock) tile2[t] = g2[t];
       __syncthreads();
       for (int k = 0; k < P.gper; ++k) {
-        const int64_t i = first + k * kBlock + threadIdx.x;
-        gather_batch<R, SPLIT>(
+        const int64_t i = first + k * kBatch + threadIdx.x / LANES;
+        gather_batch<R, SPLIT, LANES>(
             P, st, (int)i, i < P.np, vit, vnew, vbar_out,
             [&](const int*) {
               return MeshGather{tile, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
@@ -1533,7 +1610,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         for (int a = 0; a < 3; ++a) sref[a] = s_ref[a];
         unsigned cls = 0u;  // per batch: knots that the thread's orbit crosses, in 4 bits
         for (int k = 0; k < P.gper; ++k) {
-          const int64_t i = first + k * kBlock + threadIdx.x;
+          const int64_t i = first + k * kBatch + threadIdx.x / LANES;
           if (i >= P.np) break;
           int crossed = 0;
           double x0[3], va[3], vi[3];
@@ -1554,7 +1631,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
           }
           cls |= (unsigned)min(crossed, 15) << (4 * k);
         }
-        if (SPLIT && bx.order)
+        if (SPLIT && LANES == 1 && bx.order)
           block_order(cls, P.gper, reinterpret_cast<int*>(tile2),
                       bx.order + first);
         block_min_ints<12>(mv);
@@ -1615,9 +1692,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       const int wid = __builtin_amdgcn_readfirstlane(((int)threadIdx.x / kWave + bid / 8) % kWaves);
       for (int k = 0; k < P.gper; ++k) {
         const int set = k * kWaves + (k & 1 ? kWaves - 1 - wid : wid);
-        const int64_t slot = first + set * kWave + threadIdx.x % kWave;
-        const int64_t i = SPLIT && bx.order ? first + bx.order[slot] : slot;
-        gather_batch<R, SPLIT>(
+        const int64_t slot = first + set * (kWave / LANES) + threadIdx.x % kWave / LANES;
+        const int64_t i = SPLIT && LANES == 1 && bx.order ? first + bx.order[slot] : slot;
+        gather_batch<R, SPLIT, LANES>(
             P, st, (int)i, i < P.np, vit, vnew, vbar_out,
             [&](const int* shift) {
               return TileGather{tile, shift[0] - sref[0] - tlo[0], shift[1] - sref[1] - tlo[1],
@@ -1633,7 +1710,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                 shift[a] = rel - (lo - sref[a]);
                 in = in && d[a] == d[a] && rel >= tlo[a] && rel + n < tlo[a] + dim[a];
               }
-              if (!in) work[1 + atomicAdd(work, 1)] = ip;
+              if (!in && threadIdx.x % LANES == 0) work[1 + atomicAdd(work, 1)] = ip;
               return in;
             },
             prev, tot, set);
@@ -1989,10 +2066,19 @@ int gather_batches(int64_t np, int64_t ncell) {
   return g;
 }
 
+// Up to this count a gather's particles take four lanes each: such a launch takes
+// what one particle's chain of pieces and rows takes.  Beyond it the blocks, of 64
+// particles with a node box each, are too many.  Per pass with one / four lanes:
+// linear, 4,096 particles in a mesh of 256 nodes 9.9 / 8.6 us; quadratic, 32,769
+// 26.1 / 21.6 us, 100,002 36 / 56 us; linear, 131,072 15 / 36 us.
+constexpr int64_t kQuadGather = 40960;
+
 GatherGrid gather_grid(int64_t np, int64_t ncell) {
   GatherGrid g;
+  g.lanes = np <= kQuadGather ? 4 : 1;
   g.batches = gather_batches(np, ncell);
-  g.blocks = (int)((np + (int64_t)g.batches * kBlock - 1) / ((int64_t)g.batches * kBlock));
+  const int64_t per = (int64_t)g.batches * (kBlock / g.lanes);
+  g.blocks = (int)((np + per - 1) / per);
   g.whole_mesh = ncell <= kGatherTileNodes;
   g.list_blocks = g.whole_mesh ? 0 : std::min((int)blocks_for(np), 512);
   return g;
@@ -2013,15 +2099,21 @@ void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const 
   P.gper = g.batches;
   const int rows = g.blocks + g.list_blocks;
   auto go = [&](auto R, auto SPLIT) {
-    if (g.whole_mesh) {
-      k_gather_push<R.value, GATHER_MESH, PS, SPLIT.value><<<g.blocks, kBlock, 0, s>>>(
-          P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
-      return;
-    }
-    k_gather_push<R.value, GATHER_TILE, PS, SPLIT.value><<<g.blocks, kBlock, 0, s>>>(
-        P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
-    k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value><<<g.list_blocks, kBlock, 0, s>>>(
-        P, st, vit, vnew, vbar_out, F, work, sc, prev, ChunkBoxes{}, g.blocks, rows);
+    auto run = [&](auto LANES) {
+      if (g.whole_mesh)
+        k_gather_push<R.value, GATHER_MESH, PS, SPLIT.value, LANES.value>
+            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+      else
+        k_gather_push<R.value, GATHER_TILE, PS, SPLIT.value, LANES.value>
+            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+    };
+    if (g.lanes == 4)
+      run(std::integral_constant<int, 4>{});
+    else
+      run(std::integral_constant<int, 1>{});
+    if (!g.whole_mesh)
+      k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value, 4><<<g.list_blocks, kBlock, 0, s>>>(
+          P, st, vit, vnew, vbar_out, F, work, sc, prev, ChunkBoxes{}, g.blocks, rows);
   };
   if constexpr (!PS::kMixed) {
     if (!P.split) {

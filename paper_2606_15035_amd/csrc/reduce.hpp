@@ -26,6 +26,19 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// sum over the four lanes of a quad, to each of them
+__device__ __forceinline__ double quad_sum(double v) {
+  auto swap = [](double u, auto perm) {
+    constexpr int kPerm = decltype(perm)::value;
+    return __hiloint2double(
+        __builtin_amdgcn_mov_dpp(__double2hiint(u), kPerm, 0xf, 0xf, true),
+        __builtin_amdgcn_mov_dpp(__double2loint(u), kPerm, 0xf, 0xf, true));
+  };
+  v += swap(v, std::integral_constant<int, 0xB1>{});  // lanes 1 0 3 2
+  v += swap(v, std::integral_constant<int, 0x4E>{});  // lanes 2 3 0 1
+  return v;
+}
+
 // Sum of M values over the block; the totals are valid in every thread of
 // wave 0 (thread 0 uses them).  Must be called by all threads of the block.
 template <int M>
