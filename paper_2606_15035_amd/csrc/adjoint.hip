@@ -447,11 +447,18 @@ __device__ __forceinline__ void current_adjoint_one(const AdjParticleArgs& P, in
   }
 }
 
+// A wavefront takes eight particles each of eight neighbouring segments, at the same
+// place in each: by the segments' order its orbits cross about the same number of
+// knots.
 template <bool UPDATE>
-__global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P,
+__global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P, int segment,
                                                             const double* __restrict__ b,
                                                             double* __restrict__ xn) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  // segments are powers of two, at least 8
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t first = j & ~(int64_t)(8 * segment - 1);  // of the eight segments
+  const int lane = (int)j % kWave, row = (int)(j - first) / kWave;
+  const int64_t i = first + (lane / 8) * segment + row * 8 + lane % 8;
   double dm = 0.0, xm = 0.0;
   if (i < P.np) current_adjoint_one<UPDATE>(P, i, b, xn, dm, xm);
   if (UPDATE) {
@@ -479,8 +486,9 @@ __global__ __launch_bounds__(kBlock) void k_current_adjoint(AdjParticleArgs P,
 // iteration: 2220 us with the points' weights held in 512 registers (one wavefront
 // per SIMD), 2080 with two lanes per particle, 1720 in this form with a node's nine
 // values side by side, 1675 with one plane per value, 1427 with planes 4 mod 16
-// apart where rows of 16 do not fit; 32,769 particles of 16^3: 125, 91, and 51 with
-// four lanes per particle.
+// apart where rows of 16 do not fit, 1267 with the particles of a lane by the knots that
+// they cross (k_segment_order); 32,769 particles of 16^3: 125, 91, and 51 with
+// four lanes per particle, 48 in that order.
 struct AdjStrides {
   int sy, sx;
   bool fits;
@@ -643,6 +651,69 @@ __global__ __launch_bounds__(kBlock) void k_push_adjoint_list(AdjParticleArgs P)
     push_adjoint<1>(P, P.list[1 + j], 0, MeshNodes{P});
 }
 
+// Particles of every segment of `segment` consecutive ones by the knots that their
+// orbits cross, the most first, as they come where these are equal.  The lanes of the
+// push terms sit in different segments at the same place of each
+// (group_particle), and a wavefront runs its orbits in lockstep, as long as its
+// longest one: 1.9 pieces for 1.3 per orbit on average (cold beams, 64 per cell).
+// 2,097,152 particles, as sorted / in this order: push terms 1454 / 1267 us per launch,
+// current terms 450 / 380 us; the order itself takes 80 us once per transposed step.
+// One wavefront per segment; it counts first, then moves x, v, w and the ids.
+constexpr int kSegCounts = 16;  // 15: fifteen or more
+__device__ __forceinline__ int knots_of(const Grid& G, double dt, const Fp64Store& p, int64_t np,
+                                        int64_t i) {
+  int c = 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int64_t e = a * np + i;
+    c += min(knots_crossed(p.x[e], dt * (0.5 * (p.vp[e] + p.v[e])), G.invH[a],
+                           Spline<2>::base_off),
+             kSegCounts);
+  }
+  return min(c, kSegCounts - 1);
+}
+__global__ __launch_bounds__(kWave) void k_segment_order(Grid G, double dt, int64_t np, int segment,
+                                                        Fp64Store src, Fp64Store dst,
+                                                        const int* __restrict__ id,
+                                                        int* __restrict__ id2) {
+  const int64_t first = (int64_t)blockIdx.x * segment;
+  const int n = (int)min((int64_t)segment, np - first);
+  const int lane = threadIdx.x;
+  int at = 0;  // lane c: particles that cross c knots, then the next place for one
+  for (int t = 0; t < n; t += kWave) {
+    const bool active = t + lane < n;
+    const int c = active ? knots_of(G, dt, src, np, first + t + lane) : -1;
+#pragma unroll
+    for (int k = 0; k < kSegCounts; ++k) {
+      const int m = __popcll(__ballot(c == k));
+      at += lane == k ? m : 0;
+    }
+  }
+  int before = 0;
+#pragma unroll
+  for (int k = 1; k < kSegCounts; ++k) {
+    const int m = __builtin_amdgcn_readlane(at, k);
+    before += lane < k ? m : 0;
+  }
+  at = before;
+  for (int t = 0; t < n; t += kWave) {
+    const bool active = t + lane < n;
+    const int c = active ? knots_of(G, dt, src, np, first + t + lane) : -1;
+    int place = 0;
+#pragma unroll
+    for (int k = 0; k < kSegCounts; ++k) {
+      const unsigned long long group = __ballot(c == k);
+      const int start = __builtin_amdgcn_readlane(at, k);
+      place = c == k ? start + __popcll(group & ((1ull << lane) - 1ull)) : place;
+      at += lane == k ? __popcll(group) : 0;
+    }
+    if (active) {
+      src.move_to(dst, np, first + t + lane, first + place);
+      id2[first + place] = id[first + t + lane];
+    }
+  }
+}
+
 // vbar = (w + v)/2
 __global__ __launch_bounds__(kBlock) void k_vbar(int64_t n3, const double* __restrict__ w,
                                                 const double* __restrict__ v,
@@ -692,12 +763,24 @@ void launch_push_adjoint(hipStream_t s, const AdjParticleArgs& P) {
   k_push_adjoint_list<<<std::min(blocks_for(P.np), 256u), kBlock, 0, s>>>(P);
 }
 
+int adjoint_segment(int chunk, int span) { return span / (chunk >= kAdjBlock ? kWave : kWave / 4); }
+
+void launch_segment_order(hipStream_t s, const Grid& G, double dt, int64_t np, int segment,
+                          const Fp64Store& src, const Fp64Store& dst, const int* id, int* id2) {
+  if (np > 0)
+    k_segment_order<<<(unsigned)((np + segment - 1) / segment), kWave, 0, s>>>(G, dt, np, segment,
+                                                                              src, dst, id, id2);
+}
+
 void launch_current_adjoint(hipStream_t s, const AdjParticleArgs& P, const double* b, double* xn) {
   if (P.np <= 0) return;
+  const int segment = adjoint_segment(P.chunk, P.span);
+  const int64_t per = std::max(8 * segment, kBlock);  // whole groups of eight segments
+  const unsigned blocks = (unsigned)((P.np + per - 1) / per * (per / kBlock));
   if (b)
-    k_current_adjoint<true><<<blocks_for(P.np), kBlock, 0, s>>>(P, b, xn);
+    k_current_adjoint<true><<<blocks, kBlock, 0, s>>>(P, segment, b, xn);
   else
-    k_current_adjoint<false><<<blocks_for(P.np), kBlock, 0, s>>>(P, nullptr, nullptr);
+    k_current_adjoint<false><<<blocks, kBlock, 0, s>>>(P, segment, nullptr, nullptr);
 }
 
 void launch_vbar(hipStream_t s, int64_t n3, const double* w, const double* v, double* vb) {

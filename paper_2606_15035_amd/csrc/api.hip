@@ -1446,17 +1446,20 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   // The step's particles in cell order for the whole adjoint (x, v and w move
   // together; the particle kernels then work on local chunks), the caller's
   // order restored for lx0 and lv0 at the end.
+  const int chunk = adjoint_chunk(np), span = std::max(auto_span(np, nc), chunk);
   if (np > 0) {
     launch_iota(s, np, A.id);
     int* id = A.id;
     int* id2 = A.id2;
     Fp64Store cur{const_cast<double*>(x), const_cast<double*>(v), const_cast<double*>(w)};
-    Fp64Store alt{A.xs, A.vs, A.ws};
+    Fp64Store alt{A.lx, A.ld, A.lvb};  // not in use yet; cur views them after the sort
     launch_sort(s, G, 2, np, cur, alt, id, id2, A.sb);
-    A.id = id;  // the ids of the sorted copies (cur now views A.xs, A.vs, A.ws)
-    x = cur.x;
-    v = cur.v;
-    w = cur.vp;
+    launch_segment_order(s, G, dt, np, adjoint_segment(chunk, span), cur,
+                         Fp64Store{A.xs, A.vs, A.ws}, id, id2);
+    A.id = id2;
+    x = A.xs;
+    v = A.vs;
+    w = A.ws;
     if (lx1) {
       launch_from_caller(s, np, A.id, lx1, A.lx1s);
       lx1 = A.lx1s;
@@ -1486,10 +1489,8 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   const double* A1r = A.gfield + 3 * nc;
   const double* A0r = fields + 2 * nc;
 
-  const int span = auto_span(np, nc);
-  const int chunk = adjoint_chunk(np);
-  AdjParticleArgs PA{G, dt, S->q / S->m, np, chunk, std::max(span, chunk), x, A.vb, A.xi, A.mu, gphi, A0r, A1r,
-                     A.lx, A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.list, S->sc};
+  AdjParticleArgs PA{G, dt, S->q / S->m, np, chunk, span, x, A.vb, A.xi, A.mu, gphi, A0r, A1r, A.lx,
+                     A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.list, S->sc};
   launch_reset_slots(s, S->sc, S_DVMAX, 2);
   launch_finish(s, S->sc, nullptr, 0, A.list);
 

@@ -339,6 +339,12 @@ struct AdjParticleArgs {
   int* list;           // 1 + np: count (0 on entry) and particles beyond their block's LDS tile
   Scratch sc;          // spread slots: S_BAD 1 if an orbit had too many pieces, and below
 };
+// Consecutive particles per lane (or quad of lanes) of the push terms' blocks, and
+// the order of the particles inside such segments: x, v and w (src.vp) from src to dst,
+// their ids from id to id2
+int adjoint_segment(int chunk, int span);
+void launch_segment_order(hipStream_t s, const Grid& G, double dt, int64_t np, int segment,
+                          const Fp64Store& src, const Fp64Store& dst, const int* id, int* id2);
 // push terms with xi into lx, ld, lvb and the mesh adjoints (added)
 void launch_push_adjoint(hipStream_t s, const AdjParticleArgs& P);
 // current terms with mu: b null, into lx, ld, lvb; else added to the push's lx, ld,
