@@ -240,6 +240,7 @@ struct ecpic_sim {
   int* sboxes;  // node boxes of the scatter's chunks, found in a step's first pass
   int* gboxes;  // node boxes of the gather's blocks, likewise
   uint16_t* gorder;  // the order in which they take their particles
+  uint8_t* sorder;  // the order of the particles of the scatter's lanes
   double2* tw[3];
   Scratch sc;
   double* host = nullptr;  // pinned read-back
@@ -413,6 +414,7 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
   const GatherGrid gg = gather_grid(np, nc);
   S->gboxes = w.take<int>((size_t)kBoxInts * std::max(gg.blocks, 1));
+  S->sorder = w.take<uint8_t>((size_t)256 * scatter_blocks_max(np));  // spans included
   const int64_t gslots = gather_slots(np, nc);
   S->gorder = gslots > 0 ? w.take<uint16_t>((size_t)gslots) : nullptr;
   // the plain iteration's next iterate is the gather's output, so the gather
@@ -885,7 +887,8 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     on_store(S, [&](auto& st, auto&) {
       CurrentOut o = cout;
       o.J = Jq;
-      launch_scatter(s, r, P, st, vit_q, S->vbar, o, S->sc, ChunkBoxes{S->sboxes, q >= 1});
+      launch_scatter(s, r, P, st, vit_q, S->vbar, o, S->sc, 
+                     ChunkBoxes{S->sboxes, q >= 1, nullptr, S->sorder});
     });
     if (S->mixed()) launch_fixed_current(s, 3 * nc, S->Jfix, Jq, fix_unit);
   };

@@ -172,6 +172,12 @@ struct ChunkBoxes {
   // its first one, one per particle slot), found and kept with the box; null:
   // as they are stored
   uint16_t* order = nullptr;
+  // scatter only: the order of the particles of every lane of a block, by the knots that
+  // their orbits cross, the most first (one byte per particle slot), found and kept
+  // with the box.  A wavefront runs its orbits in lockstep, as long as its longest
+  // one, and its lanes sit in different cells: in this order they cross about the
+  // same number at a time.  Null: as they are stored
+  uint8_t* lane_order = nullptr;
 };
 // Orbit current of iterate vit; with vbar non-null, vbar^p (3 x np) is read
 // from there instead of being formed from v^n and vit

@@ -644,13 +644,14 @@ __device__ __forceinline__ unsigned long long quantize(double w, double scale) {
 // stored it.  index(k), k < per_thread, are the thread's particles; slack(dim)
 // is the number of nodes by which a box can grow on every side and still fit
 // the kernel's tile, negative if it does not fit.
-template <int R, class PS, class Index, class Slack>
+// crossed(k, n): called there for each of them with the knots that its orbit crosses.
+template <int R, class PS, class Index, class Slack, class Crossed>
 __device__ __forceinline__ void scatter_box(const StepParams& P, const PS& st,
                                             const double* __restrict__ vit,
                                             const double* __restrict__ vbar, const ChunkBoxes& bx,
                                             int64_t base, int per_thread,
-                                            Index&& index, Slack&& slack, int (&sref)[3],
-                                            int (&tlo)[3], int (&dim)[3]) {
+                                            Index&& index, Slack&& slack, Crossed&& crossed,
+                                            int (&sref)[3], int (&tlo)[3], int (&dim)[3]) {
   constexpr int W = R + 1;
   __shared__ int s_ref[3];
   if (bx.reuse) {  // found by this chunk in the step's first pass
@@ -680,9 +681,13 @@ __device__ __forceinline__ void scatter_box(const StepParams& P, const PS& st,
     int cmax[3] = {-0x3fffffff, -0x3fffffff, -0x3fffffff};
     for (int k = 0; k < per_thread; ++k) {
       const int64_t i = index(k);
-      if (i >= P.np) continue;
+      if (i >= P.np) {
+        crossed(k, 0);
+        continue;
+      }
       double x0[3], d[3], vb[3];
       orbit_of(P, st, vit, vbar, i, x0, d, vb);
+      int knots = 0;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         int lo, n, b0;
@@ -692,7 +697,9 @@ __device__ __forceinline__ void scatter_box(const StepParams& P, const PS& st,
         rmax[a] = max(rmax[a], rel + n);
         cmin[a] = min(cmin[a], rel + (b0 - lo));
         cmax[a] = max(cmax[a], rel + (b0 - lo) + W);
+        knots += min(knots_crossed(x0[a], d[a], P.G.invH[a], Spline<R>::base_off), kMaxPieces);
       }
+      crossed(k, knots);
     }
     int mv[12] = {rmin[0], rmin[1], rmin[2], -rmax[0], -rmax[1], -rmax[2],
                   cmin[0], cmin[1], cmin[2], -cmax[0], -cmax[1], -cmax[2]};
@@ -748,13 +755,42 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   unsigned long long* tile_q = reinterpret_cast<unsigned long long*>(tile);
   const int per_thread = P.chunk / kBlock;  // at most 16
   const int64_t base = chunk_base(P.chunk, P.span, blockIdx.x);
+  // The order of the particles of a lane (see ChunkBoxes): candidates r = 0 ..
+  // per_lane - 1 of its segment, the one of place p to slot p / kWaves of wavefront
+  // p % kWaves.  The counts lie in the tile, not in use yet, in rows padded against
+  // bank conflicts.
+  constexpr int kWaves = kBlock / kWave;
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+  const int per_lane = P.chunk / kWave, lane_row = lane * (per_lane + 4);
+  uint8_t* lane_knots = reinterpret_cast<uint8_t*>(tile);
+  uint8_t* lane_order = bx.lane_order + (int64_t)blockIdx.x * P.chunk;
   double js[1] = {0.0};
   double bad = 0.0;
   late_reduce_init<2>();
   int sref[3], tlo[3], dim[3];
   scatter_box<R>(P, st, vit, vbar, bx, base, per_thread,
                  [&](int k) { return chunk_particle(base, P.span, k); },
-                 [](const int* d) { return box_slack(d); }, sref, tlo, dim);
+                 [](const int* d) { return box_slack(d); },
+                 [&](int k, int n) {
+                   if (SPLIT && bx.lane_order) lane_knots[lane_row + wid + kWaves * k] = (uint8_t)n;
+                 },
+                 sref, tlo, dim);
+  if (SPLIT && bx.lane_order && !bx.reuse) {
+    for (int k = 0; k < per_thread; ++k) {
+      const int own = wid + kWaves * k, n = lane_knots[lane_row + own];
+      int place = 0;
+      for (int r = 0; r < per_lane; ++r) {
+        const int m = lane_knots[lane_row + r];
+        place += m > n || (m == n && r < own) ? 1 : 0;
+      }
+      lane_order[((place % kWaves) * kWave + lane) * per_thread + place / kWaves] = (uint8_t)own;
+    }
+    __syncthreads();
+  }
+  auto particle = [&](int k) {
+    if (!(SPLIT && bx.lane_order)) return chunk_particle(base, P.span, k);
+    return chunk_particle(base, P.span, 0) - wid + lane_order[(int)threadIdx.x * per_thread + k];
+  };
   const bool use_tile = box_slack(dim) >= 0;  // block-uniform
   const TileStrides ts(dim[1], dim[2]);
   const int nt = use_tile ? dim[0] * ts.sx : 0;
@@ -769,7 +805,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   auto process = [&](int k, auto global_phase) -> bool {
     constexpr bool GLOBAL = decltype(global_phase)::value;
     bool outside = false;
-    const int64_t i = chunk_particle(base, P.span, k);
+    const int64_t i = particle(k);
     if (i >= P.np) return false;
     double x0[3], d[3], vb[3], c3[3];
     orbit_of(P, st, vit, vbar, i, x0, d, vb);
@@ -1059,7 +1095,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
   int sref[3], tlo[3], dim[3];
   scatter_box<R>(P, st, vit, vbar, bx, base, P.chunk / kBlock,
                  [&](int k) { return base + wid * run + k * kWave + lane; },
-                 [](const int* d) { return plain_slack(d, kMmNodes); }, sref, tlo, dim);
+                 [](const int* d) { return plain_slack(d, kMmNodes); }, [](int, int) {}, sref,
+                 tlo, dim);
   const bool use_tile = plain_slack(dim, kMmNodes) >= 0;  // block-uniform
   const int sy = dim[2], sx = dim[1] * dim[2], nt = use_tile ? dim[0] * sx : 0;
   for (int t = threadIdx.x; t < 3 * nt; t += kBlock) tile[t] = 0.0;
@@ -2024,11 +2061,18 @@ void launch_extrapolate(hipStream_t s, int64_t np, const PS& st, double* vit, do
   k_extrapolate<<<blocks_for(3 * np), kBlock, 0, s>>>(3 * np, st.v, st.vp, vit, vbar);
 }
 
+// Blocks of at least two batches of 256 order their lanes' particles.  Per pass, as
+// stored / ordered: mixed, 33,554,432 at 128 per cell with orbits of several cells,
+// 2048 per block 3383 / 2877 us; mixed, 2,097,152 cold beams, 2048 per block 144 /
+// 137 us; cubic, 524,288, 512 per block 76.6 / 73.6 us.
+constexpr int kLaneOrderChunk = 512;
+
 template <class PS>
 void launch_scatter(hipStream_t s, int r, const StepParams& P, const PS& st, const double* vit,
                     const double* vbar, CurrentOut out, Scratch sc, ChunkBoxes bx) {
   if (P.np <= 0) return;
   const bool multi = P.nsp > 1;
+  if (P.chunk < kLaneOrderChunk) bx.lane_order = nullptr;
   // degree x (split) x species
   const unsigned nblk = (unsigned)scatter_blocks(P.np, P.chunk, P.span);
   auto go = [&](auto R, auto SPLIT) {
