@@ -452,13 +452,17 @@ RealIO soa_io(double* base, int64_t nc, int nb) {
 
 const double2* const* twp(ecpic_sim* S) { return S->tw; }
 
-// the read-back of red[first .. first + count) into the pinned host buffer,
-// queued with an event after it; wait_read() waits for that event only, so
-// work queued behind it keeps the GPU busy while the host looks at the values
-ecpic_status queue_read(ecpic_sim* S, int first, int count) {
+// all slots, or some of them, into the pinned host buffer by the finishing kernel
+HostRead read_all(const ecpic_sim* S) { return HostRead{S->host, 0, S_NSLOTS}; }
+HostRead read_slots(const ecpic_sim* S, int first, int count) {
+  return HostRead{S->host, first, count};
+}
+
+// an event behind a finishing kernel that hands its slots to the host; wait_read()
+// waits for that event only, so work queued behind it keeps the GPU busy while the
+// host looks at the values
+ecpic_status queue_read(ecpic_sim* S) {
   if (!S->ev_read) HIPCHK(hipEventCreateWithFlags(&S->ev_read, hipEventDisableTiming));
-  HIPCHK(hipMemcpyAsync(S->host, S->sc.red + first, sizeof(double) * count, hipMemcpyDeviceToHost,
-                        S->stream));
   HIPCHK(hipEventRecord(S->ev_read, S->stream));
   return ECPIC_OK;
 }
@@ -524,9 +528,7 @@ int sure_passes(const ecpic_sim* S) {
   return std::max(m, 2);
 }
 
-ecpic_status sync_read(ecpic_sim* S, int first, int count) {
-  HIPCHK(hipMemcpyAsync(S->host, S->sc.red + first, sizeof(double) * count, hipMemcpyDeviceToHost,
-                        S->stream));
+ecpic_status sync_read(ecpic_sim* S) {
   HIPCHK(hipStreamSynchronize(S->stream));
   return ECPIC_OK;
 }
@@ -557,10 +559,11 @@ ecpic_status update_level_energies(ecpic_sim* S) {
   launch_field_energy(S->stream, S->fp(), S->spec[S->cur], S->sc);
   const FinishJob jobs[2] = {{P_K, (int)particle_blocks(S->np), 2, S_K},
                              {P_W, (int)mesh_blocks(S->G.ncell), 1, S_WCUR}};
-  launch_finish(S->stream, S->sc, S->np > 0 ? jobs : jobs + 1, S->np > 0 ? 2 : 1);
-  HIPCHK(hipGetLastError());
   if (S->np <= 0) launch_fill(S->stream, 2, S->sc.red + S_K, 0.0);
-  ecpic_status st = sync_read(S, 0, S_NSLOTS);
+  launch_finish(S->stream, S->sc, S->np > 0 ? jobs : jobs + 1, S->np > 0 ? 2 : 1, nullptr,
+                read_all(S));
+  HIPCHK(hipGetLastError());
+  ecpic_status st = sync_read(S);
   if (st != ECPIC_OK) return st;
   S->K = S->host[S_K];
   S->W = S->host[S_WCUR];
@@ -681,7 +684,7 @@ ecpic_status ecpic_create(const ecpic_config* cfg, int64_t n_particles, void* st
   S->state_base = static_cast<char*>(state_dev);
   S->state_size = need_s;
   if (hipHostMalloc(reinterpret_cast<void**>(&S->host), sizeof(double) * S_NSLOTS,
-                    hipHostMallocDefault) != hipSuccess) {
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     delete S;
     return fail(ECPIC_ENOMEM, "pinned host allocation failed");
   }
@@ -952,10 +955,11 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
                                  {P_AA,
                                   mk == 1 ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
                                   anderson_sums(mk), S_AA}};
-      launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gwork);
+      launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gwork,
+                    read_slots(S, S_DVMAX, (S_AA - S_DVMAX) + anderson_sums(mk)));
     }
     HIPCHK(hipGetLastError());
-    ecpic_status st = queue_read(S, S_DVMAX, (S_AA - S_DVMAX) + anderson_sums(mk));
+    ecpic_status st = queue_read(S);
     if (st != ECPIC_OK) return st;
     if (am == 0 && !prof && p + 1 <= S->cfg.picard_max && p + 1 < sure) {
       // w_{p+1} = g_p; Jprev, read by this pass's transform, is the next
@@ -1036,16 +1040,17 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     launch_reset_slots(s, S->sc, S_WORK, 4);
   }
   launch_accept_A(s, nc, S->gbuf);
-  if (S->np > 0) {
+  {
     const FinishJob jobs[3] = {{P_K, (int)particle_blocks(S->np), 2, S_K},
                                {P_SWEEP, (int)particle_blocks(S->np), 2, S_WORK},
                                {0, 0, 2, S_RAMAX, F_SPREAD_MAX}};
-    launch_finish(s, S->sc, jobs, S->cfg.diagnostics ? 3 : 1);
+    launch_finish(s, S->sc, jobs, S->np <= 0 ? 0 : (S->cfg.diagnostics ? 3 : 1), nullptr,
+                  read_all(S));
   }
   if (prof) HIPCHK(hipEventRecord(S->ev[2], s));
   S->cur = 1 - S->cur;
   HIPCHK(hipGetLastError());
-  ecpic_status st = sync_read(S, 0, S_NSLOTS);
+  ecpic_status st = sync_read(S);
   if (st != ECPIC_OK) return st;
   const double* h = S->host;
   if (prof) {
@@ -1104,11 +1109,11 @@ ecpic_status ecpic_field_solve(ecpic_sim* S, const double* J_dev) {
               S->spec[1 - S->cur], S->Jh, S->batch, gather_fields_out(S, true), twp(S), S->sc);
   {
     const FinishJob job = {P_CN, cn_pencil_blocks(S->G), 3, S_JE};
-    launch_finish(s, S->sc, &job, 1);
+    launch_finish(s, S->sc, &job, 1, nullptr, read_all(S));
   }
   S->cur = 1 - S->cur;
   HIPCHK(hipGetLastError());
-  ecpic_status st = sync_read(S, 0, S_NSLOTS);
+  ecpic_status st = sync_read(S);
   if (st != ECPIC_OK) return st;
   S->en.R_field = S->host[S_DW] + S->cfg.dt * S->host[S_JE];
   S->en.JE_mesh = S->host[S_JE];
@@ -1129,10 +1134,10 @@ ecpic_status ecpic_energy_diagnostics(ecpic_sim* S, ecpic_energy* out) {
     const FinishJob jobs[3] = {{P_W, (int)mesh_blocks(nc), 1, S_WCUR},
                                {P_NORM, (int)mesh_blocks(nc), 2, S_GL2},
                                {0, 0, 2, S_GMAX, F_SPREAD_MAX}};
-    launch_finish(s, S->sc, jobs, 3);
+    launch_finish(s, S->sc, jobs, 3, nullptr, read_all(S));
   }
   HIPCHK(hipGetLastError());
-  ecpic_status st = sync_read(S, 0, S_NSLOTS);
+  ecpic_status st = sync_read(S);
   if (st != ECPIC_OK) return st;
   const double* h = S->host;
   S->en.K = S->K;
@@ -1524,9 +1529,9 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
     current_adjoint(S, A);
     launch_current_adjoint(s, PA, A.b, A.xn);
     const FinishJob jobs[2] = {{0, 0, 2, S_DVMAX, F_SPREAD_MAX}, {0, 0, 1, S_BAD, F_SPREAD_MAX}};
-    launch_finish(s, S->sc, jobs, 2, A.list);
+    launch_finish(s, S->sc, jobs, 2, A.list, read_slots(S, S_DVMAX, S_BAD - S_DVMAX + 1));
     HIPCHK(hipGetLastError());
-    const ecpic_status st = sync_read(S, S_DVMAX, S_BAD - S_DVMAX + 1);
+    const ecpic_status st = sync_read(S);
     if (st != ECPIC_OK) return st;
     const double dm = S->host[0], xm = S->host[1];
     if (S->host[S_BAD - S_DVMAX] != 0.0)

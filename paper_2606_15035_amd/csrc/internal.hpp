@@ -114,9 +114,15 @@ struct FinishJob {
   int row0 = 0;
 };
 constexpr int kMaxFinishJobs = 8;
-// clear_int (optional): an int set to zero after the jobs (the gather's work-list count)
+// slots first .. first + count - 1 into the host's pinned buffer dst
+struct HostRead {
+  double* dst = nullptr;
+  int first = 0, count = 0;
+};
+// clear_int (optional): an int set to zero after the jobs (the gather's work-list
+// count); read: slots that the kernel hands to the host, after the jobs
 void launch_finish(hipStream_t s, Scratch sc, const FinishJob* jobs, int njobs,
-                   int* clear_int = nullptr);
+                   int* clear_int = nullptr, HostRead read = HostRead{});
 
 // Anderson mixing (anderson.hip): iterates w[j] and images g[j] of passes
 // p - j, j = 0..mk, each 3 x np doubles.

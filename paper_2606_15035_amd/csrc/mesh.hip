@@ -440,6 +440,7 @@ struct FinishArgs {
   FinishJob job[kMaxFinishJobs];
   int njobs;
   int* clear_int;  // optional: set to zero once every job is done (a work-list count)
+  HostRead read;
 };
 
 constexpr int kFinishThreads = 1024;  // one wavefront per row, 16 rows at a time
@@ -480,6 +481,12 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(FinishArgs F) {
     }
   }
   if (F.clear_int && threadIdx.x == 0) *F.clear_int = 0;
+  // Straight into the host's memory: a copy queued behind this kernel is a launch of
+  // its own (4,096 particles: 3.4 us of the GPU's time in every pass).
+  if (F.read.count > 0) {  // uniform
+    __syncthreads();
+    if ((int)threadIdx.x < F.read.count) F.read.dst[threadIdx.x] = F.sc.red[F.read.first + threadIdx.x];
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_reset_slots(Scratch sc, int first, int count) {
@@ -1034,13 +1041,15 @@ void launch_set_A0(hipStream_t s, int64_t ncell, const double* A, double* gbuf) 
   k_set_A0<<<blocks_for(ncell), kBlock, 0, s>>>(ncell, A, gbuf);
 }
 
-void launch_finish(hipStream_t s, Scratch sc, const FinishJob* jobs, int njobs, int* clear_int) {
+void launch_finish(hipStream_t s, Scratch sc, const FinishJob* jobs, int njobs, int* clear_int,
+                   HostRead read) {
   FinishArgs F;
   F.sc = sc;
   F.njobs = njobs < kMaxFinishJobs ? njobs : kMaxFinishJobs;
   for (int j = 0; j < F.njobs; ++j) F.job[j] = jobs[j];
   F.clear_int = clear_int;
-  if (F.njobs > 0 || clear_int) k_finish<<<1, kFinishThreads, 0, s>>>(F);
+  F.read = read;
+  if (F.njobs > 0 || clear_int || read.count > 0) k_finish<<<1, kFinishThreads, 0, s>>>(F);
 }
 
 int64_t mesh_blocks(int64_t ncell) { return (ncell + kBlock - 1) / kBlock; }
