@@ -1296,7 +1296,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 template <int R, bool SPLIT, int LANES, class Acc, class PS>
 __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& acc, const PS& st,
                                                 int part, int& i, double (&x0)[3],
-                                                double (&d)[3], const double (&vb)[3], double* vn,
+                                                double (&d)[3], const double (&vb)[3],
+                                                const double* __restrict__ vit, double* vn,
+                                                double (&va)[3], double (&vi)[3],
                                                 double& npieces, double& bad) {
   double gp[3] = {0.0, 0.0, 0.0};
   double dtv[3] = {0.0, 0.0, 0.0};  // H_j ((D A)^T vbar)_j until the pieces are summed
@@ -1322,8 +1324,10 @@ __device__ __forceinline__ void gather_push_one(const StepParams& P, const Acc& 
   // A_h^{n+1}(x^{n+1}) at the wrapped end point closes the velocity (eq. orbit-v-update).
   const int spc = st.species(i);
   const double qi = species_value(P.qs, spc), mi = species_value(P.ms, spc);
-  double va[3];
   st.v_of(P.np, i, va);
+  // for the caller too, on its way while the interpolants are formed (read again
+  // behind them: 0.5% more time per step at 2,097,152 and 33,554,432 particles)
+  load3(vit, P.np, i, vi);
   double x1[3], A0s[3], A1e[3];
   int zero[3] = {0, 0, 0}, sh1[3];
 #pragma unroll
@@ -1408,16 +1412,13 @@ __device__ __forceinline__ void gather_batch(const StepParams& P, const PS& st, 
     }
     int shift[3];
     if (inside(i, x0, d, shift)) {
-      double vn[3];
-      gather_push_one<R, SPLIT, LANES>(P, make_acc(shift), st, part, i, x0, d, vb, vn, npieces,
-                                       bad);
+      double vn[3], va[3], vi[3];
+      gather_push_one<R, SPLIT, LANES>(P, make_acc(shift), st, part, i, x0, d, vb, vit, vn, va, vi,
+                                       npieces, bad);
       // vn is complete here: otherwise its y and z sums sink behind the branches
       // below and every field value they use stays in registers until then
       // (more than 200 spilled)
       asm volatile("" : "+v"(vn[0]), "+v"(vn[1]), "+v"(vn[2]), "+v"(i) : : "memory");
-      double va[3], vi[3];
-      st.v_of(P.np, i, va);
-      load3(vit, P.np, i, vi);
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         if (LANES == 1 || part == j) {
