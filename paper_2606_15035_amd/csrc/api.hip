@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -250,9 +251,10 @@ struct ecpic_sim {
   hipEvent_t ev_read = nullptr;  // after each pass's read-back of its errors
   // the step's cell sort as a graph, one per arrangement of the two particle
   // stores and id arrays (they swap at every sort): pointers it was captured
-  // with (cur, alt, id, id2, first guess, its vbar) and the executable
+  // with (cur, its species, alt, its species, id, id2, first guess, its vbar) and the
+  // executable
   struct SortGraph {
-    const void* key[6] = {};
+    const void* key[8] = {};
     hipGraphExec_t exec = nullptr;
   } sort_graph[2];
   int next_sort_graph = 0;
@@ -478,15 +480,18 @@ const void* store_key(const MixedStore& s) { return s.cell; }
 // The step's cell sort (six small kernels, which would otherwise each wait
 // for the host's launch on an idle GPU) as one graph launch.  A graph keeps
 // the pointers it was captured with, so it is captured once per arrangement
-// of the stores, id arrays and first-guess buffers (two alternate), on a
+// of the stores, species bytes, id arrays and first-guess buffers (two alternate), on a
 // private stream, and replayed on the simulation's stream; the host then
-// swaps the stores and ids as the sort itself does.
+// swaps the stores and ids as the sort itself does.  The species bytes come and go, and
+// meet either store, when particles are given anew (a graph captured without them
+// would leave every byte behind).
 template <class PS>
 ecpic_status sort_by_graph(ecpic_sim* S, PS& cur, PS& alt) {
-  const void* key[6] = {store_key(cur), store_key(alt), S->id, S->id2, S->vit, S->vbar};
+  const void* key[] = {store_key(cur), cur.sp, store_key(alt), alt.sp,
+                       S->id,          S->id2, S->vit,         S->vbar};
   ecpic_sim::SortGraph* g = nullptr;
   for (auto& c : S->sort_graph)
-    if (c.exec && std::equal(key, key + 6, c.key)) g = &c;
+    if (c.exec && std::equal(std::begin(key), std::end(key), c.key)) g = &c;
   if (!g) {
     g = &S->sort_graph[S->next_sort_graph];
     S->next_sort_graph ^= 1;
@@ -509,7 +514,7 @@ ecpic_status sort_by_graph(ecpic_sim* S, PS& cur, PS& alt) {
       g->exec = nullptr;
       return fail(ECPIC_EDEVICE, "capturing the cell sort as a graph: %s", hipGetErrorString(e));
     }
-    std::copy(key, key + 6, g->key);
+    std::copy(std::begin(key), std::end(key), g->key);
   }
   HIPCHK(hipGraphLaunch(g->exec, S->stream));
   std::swap(cur, alt);
