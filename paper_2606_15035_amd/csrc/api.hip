@@ -883,7 +883,9 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     on_store(S, [&](auto& st, auto&) { launch_extrapolate(s, S->np, st, S->vit, S->vbar); });
   const CurrentOut cout{nullptr, S->Jfix, S->fix_scale};
   const double fix_unit = S->q / S->G.dV / S->fix_scale;
-  launch_reset_slots(s, S->sc, S_PIECES, 1);
+  // the slots of the passes.  A failed step leaves the flag of the pass that was
+  // queued ahead when it failed
+  launch_reset_slots(s, S->sc, S_DVMAX, S_PIECES - S_DVMAX + 1);
   int p = 0, jcur = 1 - S->jlast;
   if (!S->jclean && !S->mixed()) launch_fill(s, 3 * nc, S->Jb[jcur], 0.0);  // after a failed step
   S->jclean = false;

@@ -23,6 +23,7 @@ enum Slot : int {
   S_JS,         // J_s = sum_i |q| |vbar_i|_inf / |Omega| (sum)
   S_BAD,        // 1: an orbit had too many pieces, 1.5: a current contribution beyond the
                 // fixed-point range, 2: a non-finite velocity (max)
+  S_PIECES,     // orbit pieces summed over particles    (sum of integers)
   S_AA,         // Anderson sums dF_i . dF_j (i <= j), then dF_i . f_p   (sums)
   S_AA_END = S_AA + kAndersonSums - 1,
   S_JE,         // sum_g J . E^{n+1/2} dV               (sum)
@@ -39,7 +40,6 @@ enum Slot : int {
   S_GL2,        // sum G_h^2                            (sum)
   S_RL2,        // sum R_h^2                            (sum)
   S_WCUR,       // W of the current field level         (sum)
-  S_PIECES,     // orbit pieces summed over particles    (sum of integers)
   S_NSLOTS
 };
 // Producer sites of block partial sums (each has its own region).
