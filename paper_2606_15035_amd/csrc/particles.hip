@@ -1584,8 +1584,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     const int count = work[0];  // written by the tiled kernel (previous launch)
     // entry j to block j % grid: the entries are the longest orbits, and every lane
     // reads nodes of its own, 5 cache lines each, so that a particle's chain of rows
-    // and one CU's line rate bound the kernel.  With four lanes per particle, per
-    // pass: 300,007 particles at 9 per cell 56 -> 25 us, 100,002 at 12 16 -> 9 us.
+    // and one CU's line rate bound the kernel.  With four lanes per particle (FP64
+    // only, see launch_gather_push), per pass: 300,007 particles at 9 per cell 56 -> 25
+    // us, 100,002 at 12 16 -> 9 us.
     constexpr int kEntries = kBlock / LANES;
     for (int t = 0; t * gridDim.x + bid < count; t += kEntries) {
       const int j = (t + (int)threadIdx.x / LANES) * (int)gridDim.x + bid;
@@ -2152,13 +2153,23 @@ void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const 
         k_gather_push<R.value, GATHER_TILE, PS, SPLIT.value, LANES.value>
             <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
     };
-    if (g.lanes == 4)
+    auto list = [&](auto LANES) {
+      if (!g.whole_mesh)
+        k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value, LANES.value>
+            <<<g.list_blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev,
+                                              ChunkBoxes{}, g.blocks, rows);
+    };
+    if (g.lanes == 4) {
       run(std::integral_constant<int, 4>{});
-    else
+      list(std::integral_constant<int, 4>{});
+    } else {
       run(std::integral_constant<int, 1>{});
-    if (!g.whole_mesh)
-      k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value, 4><<<g.list_blocks, kBlock, 0, s>>>(
-          P, st, vit, vnew, vbar_out, F, work, sc, prev, ChunkBoxes{}, g.blocks, rows);
+      // Four lanes per listed particle add a particle's terms in another order than one.
+      // Which particles are listed goes by the particles of a block, hence by the
+      // order of the particles, and the mixed form's results do not: there all
+      // of a launch's particles are summed alike.
+      list(std::integral_constant<int, PS::kMixed ? 1 : 4>{});
+    }
   };
   if constexpr (!PS::kMixed) {
     if (!P.split) {
