@@ -918,10 +918,13 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     if (!S->vnew) return fail(ECPIC_EDEVICE, "internal: no free iterate buffer");
     push_front(gl, ng, am + 1, S->vnew);
     // Anderson: differences over mk = min(m, p) passes; one difference is
-    // summed by the gather itself, more by a streaming kernel after it
+    // summed by the gather itself, more by a streaming kernel after it.  So is one where
+    // nothing else leaves a run to chance, in the mixed form without sorting: the
+    // gather's listed particles come in no fixed order
     const int mk = am > 0 && S->np > 0 ? std::min(am, p) : 0;
+    const bool aa_gather = mk == 1 && !(S->mixed() && S->cfg.sort_interval < 0);
     AndersonPrev prev{};
-    if (mk == 1) {
+    if (aa_gather) {
       prev.w = wl[1];
       prev.g = gl[1];
     }
@@ -951,7 +954,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
       av.w[j] = wl[j];
       av.g[j] = gl[j];
     }
-    if (mk >= 2) launch_anderson_dots(s, mk, n3, av, S->sc);
+    if (mk > 0 && !aa_gather) launch_anderson_dots(s, mk, n3, av, S->sc);
     {
       const FinishJob jobs[7] = {{P_CN, cn_pencil_blocks(S->G), 3, S_JE},
                                  {0, 0, 1, S_DJMAX, F_SPREAD_MAX},
@@ -960,7 +963,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
                                  {0, 0, 1, S_BAD, F_SPREAD_MAX},
                                  {0, 0, 1, S_PIECES, F_SPREAD_SUM},
                                  {P_AA,
-                                  mk == 1 ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
+                                  aa_gather ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
                                   anderson_sums(mk), S_AA}};
       launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gwork,
                     read_slots(S, S_DVMAX, (S_AA - S_DVMAX) + anderson_sums(mk)));

@@ -48,3 +48,14 @@ def test_mixed_step_does_not_depend_on_the_order(np_, r, vth):
         out = run(wl, x, v, order, pmax=2, sort_interval=sort)
         for name, a, b in zip(("x", "v", "vprev", "fields", "J"), ref, out):
             assert np.array_equal(a, b), (name, sort, np.count_nonzero(a != b), a.size)
+
+
+def test_unsorted_mixed_run_with_anderson_mixing_repeats_itself():
+    """Never sorted, the mixed form with mixing over one difference takes its sums over
+    the particles in the order in which they are given: two runs are the same bits."""
+    wl = plasma((16, 16, 16), 41001, 2, 1.5, seed=3)
+    x, v = to_storage(wl, wl.x, wl.v)
+    given = np.arange(wl.np)
+    a, b, c = (run(wl, x, v, given, pmax=4, sort_interval=-1, anderson=1) for _ in range(3))
+    for name, u, w, t in zip(("x", "v", "vprev", "fields", "J"), a, b, c):
+        assert np.array_equal(u, w) and np.array_equal(u, t), name
