@@ -627,7 +627,7 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((
     if (inside)
       push_adjoint<LANES>(P, i, (int)threadIdx.x % LANES, nodes);
     else if (threadIdx.x % LANES == 0)
-      P.list[1 + atomicAdd(P.list, 1)] = (int)i;
+      P.list[atomicAdd(P.nlist, 1)] = (int)i;
   }
   __syncthreads();
   for (int t = threadIdx.x; t < nt; t += kAdjBlock) {
@@ -645,10 +645,10 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((
 // the particles of P.list, entry j by block j % grid (few lanes per wavefront: every
 // lane reads nodes of its own)
 __global__ __launch_bounds__(kBlock) void k_push_adjoint_list(AdjParticleArgs P) {
-  const int count = P.list[0];
+  const int count = *P.nlist;
   for (int64_t j = (int64_t)threadIdx.x * gridDim.x + blockIdx.x; j < count;
        j += (int64_t)kBlock * gridDim.x)
-    push_adjoint<1>(P, P.list[1 + j], 0, MeshNodes{P});
+    push_adjoint<1>(P, P.list[j], 0, MeshNodes{P});
 }
 
 // Particles of every segment of `segment` consecutive ones by the knots that their

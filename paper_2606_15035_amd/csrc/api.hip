@@ -586,7 +586,9 @@ struct AdjWs {
   // in and lx0, lv0 out; 3 x np each); id: cell order -> caller order
   double *xs, *vs, *ws, *lx1s, *lv1s, *lx0s, *lv0s;
   int *id, *id2;
-  int* list;  // 1 + np: particles beyond their block's tile in the push terms
+  // particles beyond their block's tile in the push terms and their number, in the
+  // sort's arrays (free from the sort on)
+  int *list, *nlist;
   SortScratch sb;
   double *J, *gfield, *lg_r, *mu;                     // 3, 6, 9, 3 x ncell (real)
   double2 *Fh, *F1h, *Jh, *inv, *l1, *lg, *lcur, *lJh;  // 9, 9, 3, 6, 9, 9, 9, 3 x ncell
@@ -602,9 +604,8 @@ size_t carve_adjoint(const Grid& G, int64_t np, char* base, AdjWs* A) {
   const size_t n1 = (size_t)(np > 0 ? np : 1);
   A->id = c.take<int>(n1);
   A->id2 = c.take<int>(n1);
-  A->list = c.take<int>(n1 + 1);
-  A->sb.key = c.take<int>(n1);
-  A->sb.count = c.take<int>(8 * nc);
+  A->list = A->sb.key = c.take<int>(n1);
+  A->nlist = A->sb.count = c.take<int>(8 * nc);
   A->sb.offset = c.take<int>(8 * nc + 1);
   A->sb.cursor = c.take<int>(8 * nc);
   A->sb.scan_totals = c.take<int>(sort_scan_blocks(nc));
@@ -1508,9 +1509,10 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   const double* A0r = fields + 2 * nc;
 
   AdjParticleArgs PA{G, dt, S->q / S->m, np, chunk, span, x, A.vb, A.xi, A.mu, gphi, A0r, A1r, A.lx,
-                     A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.list, S->sc};
+                     A.ld, A.lvb, A.lg_r, A.lg_r + 6 * nc, A.lg_r + 3 * nc, A.list,
+                     A.nlist, S->sc};
   launch_reset_slots(s, S->sc, S_DVMAX, 2);
-  launch_finish(s, S->sc, nullptr, 0, A.list);
+  launch_finish(s, S->sc, nullptr, 0, A.nlist);
 
   // adjoints reaching w straight from the outputs
   launch_fill(s, 2 * 9 * nc, reinterpret_cast<double*>(A.lcur), 0.0);
@@ -1539,7 +1541,7 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
     current_adjoint(S, A);
     launch_current_adjoint(s, PA, A.b, A.xn);
     const FinishJob jobs[2] = {{0, 0, 2, S_DVMAX, F_SPREAD_MAX}, {0, 0, 1, S_BAD, F_SPREAD_MAX}};
-    launch_finish(s, S->sc, jobs, 2, A.list, read_slots(S, S_DVMAX, S_BAD - S_DVMAX + 1));
+    launch_finish(s, S->sc, jobs, 2, A.nlist, read_slots(S, S_DVMAX, S_BAD - S_DVMAX + 1));
     HIPCHK(hipGetLastError());
     const ecpic_status st = sync_read(S);
     if (st != ECPIC_OK) return st;

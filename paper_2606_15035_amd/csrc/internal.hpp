@@ -348,7 +348,8 @@ struct AdjParticleArgs {
   double* lgphi;       // push-side mesh adjoints (3 x ncell each), atomics
   double* lA0;
   double* lA1;
-  int* list;           // 1 + np: count (0 on entry) and particles beyond their block's LDS tile
+  int* list;           // np: particles beyond their block's LDS tile
+  int* nlist;          // their number (0 on entry)
   Scratch sc;          // spread slots: S_BAD 1 if an orbit had too many pieces, and below
 };
 // Consecutive particles per lane (or quad of lanes) of the push terms' blocks, and
