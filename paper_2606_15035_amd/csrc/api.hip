@@ -237,7 +237,7 @@ struct ecpic_sim {
   double2* batch;
   double* realbuf;
   double* Uhalf;
-  int* gwork;  // gather work list: [count, particles whose orbits left their block's LDS tile]
+  int* gcount;  // length of the gather's list, whose particles lie in sb.key: free between sorts
   int* sboxes;  // node boxes of the scatter's chunks, found in a step's first pass
   int* gboxes;  // node boxes of the gather's blocks, likewise
   uint16_t* gorder;  // the order in which they take their particles
@@ -412,7 +412,7 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->realbuf = w.take<double>(9 * nc);
   S->Uhalf = w.take<double>(3 * nc);
   for (int a = 0; a < 3; ++a) S->tw[a] = w.take<double2>(S->G.n[a] / 2);
-  S->gwork = w.take<int>((np > 0 ? np : 1) + 1);
+  S->gcount = w.take<int>(1);
   S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
   const GatherGrid gg = gather_grid(np, nc);
   S->gboxes = w.take<int>((size_t)kBoxInts * std::max(gg.blocks, 1));
@@ -713,7 +713,7 @@ ecpic_status ecpic_create(const ecpic_config* cfg, int64_t n_particles, void* st
   if (hipMemsetAsync(S->sc.red, 0, sizeof(double) * S_NSLOTS, S->stream) != hipSuccess ||
       hipMemsetAsync(S->sc.spread, 0, sizeof(double) * S_NSLOTS * kSpread * kSpreadStride,
                      S->stream) != hipSuccess ||
-      hipMemsetAsync(S->gwork, 0, sizeof(int), S->stream) != hipSuccess ||
+      hipMemsetAsync(S->gcount, 0, sizeof(int), S->stream) != hipSuccess ||
       (S->Jfix && hipMemsetAsync(S->Jfix, 0, sizeof(unsigned long long) * 3 * S->G.ncell,
                                  S->stream) != hipSuccess) ||
       hipStreamSynchronize(S->stream) != hipSuccess) {
@@ -946,7 +946,8 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
                 gout, twp(S), S->sc);
     if (prof_g) HIPCHK(hipEventRecord(S->ev[2], s));
     on_store(S, [&](auto& st, auto&) {  // v^{n+1,p+1}
-      launch_gather_push(s, r, P, st, S->vit, S->vnew, S->vbar, S->gbuf, S->gwork, S->sc, prev,
+      launch_gather_push(s, r, P, st, S->vit, S->vnew, S->vbar, S->gbuf,
+                         GatherList{S->gcount, S->sb.key}, S->sc, prev,
                          ChunkBoxes{S->gboxes, p >= 1, S->gorder});
     });
     if (prof_g) HIPCHK(hipEventRecord(S->ev[3], s));
@@ -966,7 +967,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
                                  {P_AA,
                                   aa_gather ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
                                   anderson_sums(mk), S_AA}};
-      launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gwork,
+      launch_finish(s, S->sc, jobs, S->np > 0 ? (mk > 0 ? 7 : 6) : 2, S->gcount,
                     read_slots(S, S_DVMAX, (S_AA - S_DVMAX) + anderson_sums(mk)));
     }
     HIPCHK(hipGetLastError());

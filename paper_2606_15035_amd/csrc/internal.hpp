@@ -119,8 +119,8 @@ struct HostRead {
   double* dst = nullptr;
   int first = 0, count = 0;
 };
-// clear_int (optional): an int set to zero after the jobs (the gather's work-list
-// count); read: slots that the kernel hands to the host, after the jobs
+// clear_int (optional): an int set to zero after the jobs (the length of the gather's
+// list); read: slots that the kernel hands to the host, after the jobs
 void launch_finish(hipStream_t s, Scratch sc, const FinishJob* jobs, int njobs,
                    int* clear_int = nullptr, HostRead read = HostRead{});
 
@@ -207,15 +207,19 @@ struct GatherGrid {
 };
 GatherGrid gather_grid(int64_t np, int64_t ncell);
 int64_t gather_slots(int64_t np, int64_t ncell);  // entries of ChunkBoxes::order, 0: none
-// work: 1 + np ints, work[0] = 0 on entry; the tiled kernel lists the particles
-// whose orbits leave their block's node box, the second kernel runs them from
-// global memory; the per-pass finishing kernel resets work[0].  vbar_out
-// (nullable): (vnew + v^n) / 2, the vbar of a next pass whose iterate is vnew.
+// The particles (np at most) whose orbits leave their block's node box, listed by the
+// tiled kernel and run from global memory by the second one; count = 0 on entry (the
+// per-pass finishing kernel resets it)
+struct GatherList {
+  int* count;
+  int* particle;
+};
+// vbar_out (nullable): (vnew + v^n) / 2, the vbar of a next pass whose iterate is vnew.
 // bx: node boxes of the blocks, as for the scatter's chunks.
 template <class PS>
 void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const double* vit,
-                        double* vnew, double* vbar_out, const double* gbuf, int* work, Scratch sc,
-                        AndersonPrev prev = AndersonPrev{}, ChunkBoxes bx = {});
+                        double* vnew, double* vbar_out, const double* gbuf, GatherList list,
+                        Scratch sc, AndersonPrev prev = AndersonPrev{}, ChunkBoxes bx = {});
 template <class PS>
 void launch_sweep(hipStream_t s, int r, const StepParams& P, const PS& st, const double* vit,
                   const double* gbuf, const double* Uhalf, Scratch sc);

@@ -1561,9 +1561,8 @@ constexpr int kGatherWavesPerSimd = R == 2 ? 2 : 1;
 // GATHER_TILE: the block finds the box of nodes its orbits touch; where that box exceeds the tile it takes the box of its start stencils,
 // widened by as many nodes as fit.  It copies the gather fields of the box into
 // LDS, and every stencil read of the orbit loop then comes from LDS; particles
-// whose orbit leaves the box go to a list (work[0] = count,
-// work[1..] = particles), all of them if not even the start stencils fit.  The
-// list is a second kernel (GATHER_LIST), so each keeps its own register budget.
+// whose orbit leaves the box go to the list, all of them if not even the start
+// stencils fit.  The list is a second kernel (GATHER_LIST), so each keeps its own register budget.
 // After the first Picard pass of a step the block takes the box it stored in
 // that pass.
 template <int R, int FROM, class PS, bool SPLIT, int LANES>
@@ -1572,7 +1571,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                                                  const double* __restrict__ vit,
                                                  double* __restrict__ vnew,
                                                  double* __restrict__ vbar_out, AosFields F,
-                                                 int* __restrict__ work, Scratch sc,
+                                                 GatherList list, Scratch sc,
                                                  AndersonPrev prev, ChunkBoxes bx, int aa_row0,
                                                  int aa_rows) {
   constexpr int W = R + 1;
@@ -1581,7 +1580,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   const int bid = blockIdx.x;
   if constexpr (FROM == GATHER_LIST) {
     __syncthreads();
-    const int count = work[0];  // written by the tiled kernel (previous launch)
+    const int count = *list.count;  // written by the tiled kernel (previous launch)
     // entry j to block j % grid: the entries are the longest orbits, and every lane
     // reads nodes of its own, 5 cache lines each, so that a particle's chain of rows
     // and one CU's line rate bound the kernel.  With four lanes per particle (FP64
@@ -1592,7 +1591,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       const int j = (t + (int)threadIdx.x / LANES) * (int)gridDim.x + bid;
       const bool active = j < count;
       gather_batch<R, SPLIT, LANES>(
-          P, st, active ? work[1 + j] : 0, active, vit, vnew, vbar_out,
+          P, st, active ? list.particle[j] : 0, active, vit, vnew, vbar_out,
           [&](const int*) {
             return GlobalGather{F.g, P.G.mask[0], P.G.mask[1], P.G.mask[2], P.G.shx, P.G.shy};
           },
@@ -1749,7 +1748,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                 shift[a] = rel - (lo - sref[a]);
                 in = in && d[a] == d[a] && rel >= tlo[a] && rel + n < tlo[a] + dim[a];
               }
-              if (!in && threadIdx.x % LANES == 0) work[1 + atomicAdd(work, 1)] = ip;
+              if (!in && threadIdx.x % LANES == 0) list.particle[atomicAdd(list.count, 1)] = ip;
               return in;
             },
             prev, tot, set);
@@ -2137,8 +2136,8 @@ int64_t gather_slots(int64_t np, int64_t ncell) {
 
 template <class PS>
 void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const double* vit,
-                        double* vnew, double* vbar_out, const double* gbuf, int* work, Scratch sc,
-                        AndersonPrev prev, ChunkBoxes bx) {
+                        double* vnew, double* vbar_out, const double* gbuf, GatherList list,
+                        Scratch sc, AndersonPrev prev, ChunkBoxes bx) {
   if (P.np <= 0) return;
   AosFields F{gbuf};
   const GatherGrid g = gather_grid(P.np, P.G.ncell);
@@ -2148,27 +2147,27 @@ void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const 
     auto run = [&](auto LANES) {
       if (g.whole_mesh)
         k_gather_push<R.value, GATHER_MESH, PS, SPLIT.value, LANES.value>
-            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, list, sc, prev, bx, 0, rows);
       else
         k_gather_push<R.value, GATHER_TILE, PS, SPLIT.value, LANES.value>
-            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev, bx, 0, rows);
+            <<<g.blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, list, sc, prev, bx, 0, rows);
     };
-    auto list = [&](auto LANES) {
+    auto far = [&](auto LANES) {
       if (!g.whole_mesh)
         k_gather_push<R.value, GATHER_LIST, PS, SPLIT.value, LANES.value>
-            <<<g.list_blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, work, sc, prev,
+            <<<g.list_blocks, kBlock, 0, s>>>(P, st, vit, vnew, vbar_out, F, list, sc, prev,
                                               ChunkBoxes{}, g.blocks, rows);
     };
     if (g.lanes == 4) {
       run(std::integral_constant<int, 4>{});
-      list(std::integral_constant<int, 4>{});
+      far(std::integral_constant<int, 4>{});
     } else {
       run(std::integral_constant<int, 1>{});
       // Four lanes per listed particle add a particle's terms in another order than one.
       // Which particles are listed goes by the particles of a block, hence by the
       // order of the particles, and the mixed form's results do not: there all
       // of a launch's particles are summed alike.
-      list(std::integral_constant<int, PS::kMixed ? 1 : 4>{});
+      far(std::integral_constant<int, PS::kMixed ? 1 : 4>{});
     }
   };
   if constexpr (!PS::kMixed) {
@@ -2244,7 +2243,7 @@ void launch_fixed_current(hipStream_t s, int64_t n, unsigned long long* Jfix, do
   template void launch_scatter<PS>(hipStream_t, int, const StepParams&, const PS&, const double*, \
                                    const double*, CurrentOut, Scratch, ChunkBoxes);              \
   template void launch_gather_push<PS>(hipStream_t, int, StepParams, const PS&, const double*,  \
-                                       double*, double*, const double*, int*,     \
+                                       double*, double*, const double*, GatherList,             \
                                        Scratch, AndersonPrev, ChunkBoxes);                       \
   template void launch_sweep<PS>(hipStream_t, int, const StepParams&, const PS&, const double*,  \
                                  const double*, const double*, Scratch);                         \
