@@ -1553,9 +1553,13 @@ __device__ __forceinline__ void block_order(unsigned cls, int batches, int* hist
 
 // Two waves per SIMD for the quadratic gather: its orbit loop fits 256
 // registers, and asking for the occupancy makes the compiler keep it (it would
-// otherwise go to one wave and twice the registers for a few more values).
-template <int R>
-constexpr int kGatherWavesPerSimd = R == 2 ? 2 : 1;
+// otherwise go to one wave and twice the registers for a few more values).  Not from
+// global memory, where the compiler's own choice (the same two waves, the loads in another
+// order) was the faster one: 524,288 unsorted, per pass mixed 890 -> 708 us, FP64 810 -> 752.
+template <int R, int FROM>
+constexpr int kGatherWavesPerSimd = R == 2 && FROM != GATHER_LIST ? 2 : 1;
+
+constexpr int kShortList = 32768;  // half of the chip's lanes at one wave per SIMD
 
 // One block = P.gper batches of 256 consecutive cell-sorted particles.
 // GATHER_TILE: the block finds the box of nodes its orbits touch; where that box exceeds the tile it takes the box of its start stencils,
@@ -1567,7 +1571,7 @@ constexpr int kGatherWavesPerSimd = R == 2 ? 2 : 1;
 // that pass.
 template <int R, int FROM, class PS, bool SPLIT, int LANES>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    kGatherWavesPerSimd<R>))) void k_gather_push(StepParams P, PS st,
+    kGatherWavesPerSimd<R, FROM>))) void k_gather_push(StepParams P, PS st,
                                                  const double* __restrict__ vit,
                                                  double* __restrict__ vnew,
                                                  double* __restrict__ vbar_out, AosFields F,
@@ -1581,14 +1585,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
   if constexpr (FROM == GATHER_LIST) {
     __syncthreads();
     const int count = *list.count;  // written by the tiled kernel (previous launch)
-    // entry j to block j % grid: the entries are the longest orbits, and every lane
-    // reads nodes of its own, 5 cache lines each, so that a particle's chain of rows
-    // and one CU's line rate bound the kernel.  With four lanes per particle (FP64
+    // Every lane reads nodes of its own, 5 cache lines each, so that a particle's chain of
+    // rows and one CU's line rate bound the kernel.  With four lanes per particle (FP64
     // only, see launch_gather_push), per pass: 300,007 particles at 9 per cell 56 -> 25
     // us, 100,002 at 12 16 -> 9 us.
+    // A short list's entry j goes to block j % grid: all CUs share it.  Of a long one
+    // neighbouring entries go to a wavefront, since particles listed together lie together
+    // (both gather kernels, short / long rule: 524,288 unsorted 598 / 455 us, 2,097,152
+    // with orbits of 5 cells 9395 / 8477; 41,000 with orbits of one cell 130 / 134).
     constexpr int kEntries = kBlock / LANES;
-    for (int t = 0; t * gridDim.x + bid < count; t += kEntries) {
-      const int j = (t + (int)threadIdx.x / LANES) * (int)gridDim.x + bid;
+    const bool spread = count < kShortList;
+    const int64_t grid = gridDim.x;
+    for (int64_t t = spread ? bid : bid * kEntries; t < count; t += kEntries * grid) {
+      const int64_t j = t + threadIdx.x / LANES * (spread ? grid : 1);
       const bool active = j < count;
       gather_batch<R, SPLIT, LANES>(
           P, st, active ? list.particle[j] : 0, active, vit, vnew, vbar_out,
@@ -1728,7 +1737,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       // block, since wavefront w of every block sits on the same SIMD.
       constexpr int kWaves = kBlock / kWave;
       const int wid = __builtin_amdgcn_readfirstlane(((int)threadIdx.x / kWave + bid / 8) % kWaves);
-      for (int k = 0; k < P.gper; ++k) {
+      // the block's particles to the list at once: one by one their counter's atomics
+      // took 75 of 100 us (524,288 unsorted)
+      if (!use_tile) {
+        __shared__ int s_place;
+        const int n = (int)min((int64_t)P.gper * kBatch, P.np - first);
+        if (threadIdx.x == 0) s_place = atomicAdd(list.count, n);
+        __syncthreads();
+        for (int t = threadIdx.x; t < n; t += kBlock) list.particle[s_place + t] = (int)first + t;
+      }
+      for (int k = 0; k < P.gper && use_tile; ++k) {
         const int set = k * kWaves + (k & 1 ? kWaves - 1 - wid : wid);
         const int64_t slot = first + set * (kWave / LANES) + threadIdx.x % kWave / LANES;
         const int64_t i = SPLIT && LANES == 1 && bx.order ? first + bx.order[slot] : slot;
@@ -1739,7 +1757,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                                 shift[2] - sref[2] - tlo[2], dim[1], dim[2]};
             },
             [&](int ip, const double* x0, const double* d, int* shift) {
-              bool in = use_tile;
+              bool in = true;
 #pragma unroll
               for (int a = 0; a < 3; ++a) {
                 int lo, n, b0;
