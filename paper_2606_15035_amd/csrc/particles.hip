@@ -1718,18 +1718,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         tlo[a] = __builtin_amdgcn_readfirstlane(tlo[a]);
         dim[a] = __builtin_amdgcn_readfirstlane(dim[a]);
       }
-      const bool use_tile = dim[0] > 0;
-      if (use_tile) {
-        const int nt2 = dim[0] * dim[1] * dim[2] * (kGbufStride / 2);
-        const float inv_d1 = 1.0f / (float)dim[1], inv_d2 = 1.0f / (float)dim[2];
-        for (int t = threadIdx.x; t < nt2; t += kBlock) {
-          const int nd = t / (kGbufStride / 2), part = t % (kGbufStride / 2);
-          const int q = div_small(nd, inv_d2), cx = div_small(q, inv_d1);
-          const int cz = nd - q * dim[2], cy = q - cx * dim[1];
-          const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
-                                       sref[2] + tlo[2] + cz);
-          tile2[t] = g2[g * (kGbufStride / 2) + part];
-        }
+      // Not even the start stencils fit: the block's particles to the list at once (one by
+      // one their counter's atomics took 75 of 100 us, 524,288 unsorted)
+      if (dim[0] <= 0) {
+        __shared__ int s_place;
+        const int n = (int)min((int64_t)P.gper * kBatch, P.np - first);
+        __syncthreads();  // totals_init
+        if (threadIdx.x == 0) s_place = atomicAdd(list.count, n);
+        __syncthreads();
+        for (int t = threadIdx.x; t < n; t += kBlock) list.particle[s_place + t] = (int)first + t;
+        totals_finish(tot, sc, prev.w != nullptr, aa_row0 + bid, aa_rows);
+        return;
+      }
+      const int nt2 = dim[0] * dim[1] * dim[2] * (kGbufStride / 2);
+      const float inv_d1 = 1.0f / (float)dim[1], inv_d2 = 1.0f / (float)dim[2];
+      for (int t = threadIdx.x; t < nt2; t += kBlock) {
+        const int nd = t / (kGbufStride / 2), part = t % (kGbufStride / 2);
+        const int q = div_small(nd, inv_d2), cx = div_small(q, inv_d1);
+        const int cz = nd - q * dim[2], cy = q - cx * dim[1];
+        const int64_t g = node_index(P.G, sref[0] + tlo[0] + cx, sref[1] + tlo[1] + cy,
+                                     sref[2] + tlo[2] + cz);
+        tile2[t] = g2[g * (kGbufStride / 2) + part];
       }
       __syncthreads();
       // Sets of 64 particles, the longest orbits first, go to the wavefronts there and
@@ -1737,16 +1746,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
       // block, since wavefront w of every block sits on the same SIMD.
       constexpr int kWaves = kBlock / kWave;
       const int wid = __builtin_amdgcn_readfirstlane(((int)threadIdx.x / kWave + bid / 8) % kWaves);
-      // the block's particles to the list at once: one by one their counter's atomics
-      // took 75 of 100 us (524,288 unsorted)
-      if (!use_tile) {
-        __shared__ int s_place;
-        const int n = (int)min((int64_t)P.gper * kBatch, P.np - first);
-        if (threadIdx.x == 0) s_place = atomicAdd(list.count, n);
-        __syncthreads();
-        for (int t = threadIdx.x; t < n; t += kBlock) list.particle[s_place + t] = (int)first + t;
-      }
-      for (int k = 0; k < P.gper && use_tile; ++k) {
+      for (int k = 0; k < P.gper; ++k) {
         const int set = k * kWaves + (k & 1 ? kWaves - 1 - wid : wid);
         const int64_t slot = first + set * (kWave / LANES) + threadIdx.x % kWave / LANES;
         const int64_t i = SPLIT && LANES == 1 && bx.order ? first + bx.order[slot] : slot;
