@@ -231,7 +231,7 @@ struct ecpic_sim {
   int jlast = 0;     // index of the current of the last accepted pass
   bool jclean = true;  // Jb[1 - jlast] is zero (each pass's transform clears the other buffer)
   int chunk = 256, span = 256;  // automatic scatter chunk, span of its lanes
-  bool scatter_mm = false;  // see use_scatter_mm
+  bool scatter_mm = false;  // see use_scatter_mm and mm_turns_limit
   // workspace
   double2* Jh;
   double2* batch;
@@ -355,14 +355,26 @@ int64_t scatter_blocks_max(int64_t np) { return scatter_blocks(np > 0 ? np : 1, 
 // The FP64 current by matrix instructions (k_scatter_mm): quadratic shape,
 // sorted in every step, and at least 48 particles per cell, so that the
 // particles of one stencil fill its products (K = 4).  Measured per pass
-// against the kernel with one LDS addition per lane, node and component: 64
-// particles per cell (2,097,152) 150 against 180 us, 12 per cell (100,002) 36
-// against 27 us.  The linear shape (8 nodes) has too few additions to gain, the
+// against the kernel with one LDS addition per lane, node and component: 12 per cell
+// (100,002) 36 against 27 us.  The linear shape (8 nodes) has too few additions to gain, the
 // cubic one runs out of registers (524,288: 140 against 82 us).
 bool use_scatter_mm(const ecpic_config* c, int64_t np, int64_t ncell) {
   return c->precision == ECPIC_FP64 && c->split_orbit_at_knots == 1 && c->spline_degree == 2 &&
          c->sort_interval >= 0 && c->sort_interval <= 1 && np >= 48 * ncell;
 }
+// Its cost goes with the turns of a wavefront, one per group of particles with one stencil
+// and one per piece outside its tile, which it counts: a simulation leaves it for good after a
+// step that took more than this many per particle and pass.  Below 512 per cell it gains where
+// neighbours cross their knots together and loses where a plasma is thermal (per pass, this
+// kernel / the other; 64 per cell: cold beams 0.04 to 0.09 turns, 140 to 165 / 156 to 358 us;
+// orbits of 0.01, 0.3 and 1 cell at random, 0.102, 0.29 and 1.0 turns, 186 / 150, 319 / 217 and
+// 1091 / 423; 48 per cell 0.113 and more, 151 / 125; 128 per cell 0.084 and 0.127, 61 / 64
+// and 71 / 70; 256 per cell 0.075 and 0.109, 99 / 84 and 118 / 93, the one thermal case that
+// it keeps and loses).  From 512 on the other kernel's lanes share cells, and this one
+// wins until its pieces leave the tile (512 per cell 0.53, 1.09 and 4.2 turns, 601 / 982,
+// 6121 / 8408 and 64588 / 35052 us; 1024 per cell 0.91 and 3.9, 9321 / 23385 and 121178 /
+// 102929; 4096 per cell 0.12 and 2.5, 231 / 980 and 83185 / 1535).
+double mm_turns_limit(int64_t np, int64_t ncell) { return np < 512 * ncell ? 0.1 : 1.5; }
 constexpr int kMmChunk = 1024;  // its chunk at most: a 1024-node tile holds the box of 16 cells
 
 // fn(live store, sort alternate) for the store the configuration selects
@@ -886,7 +898,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   const double fix_unit = S->q / S->G.dV / S->fix_scale;
   // the slots of the passes.  A failed step leaves the flag of the pass that was
   // queued ahead when it failed
-  launch_reset_slots(s, S->sc, S_DVMAX, S_PIECES - S_DVMAX + 1);
+  launch_reset_slots(s, S->sc, S_DVMAX, S_GROUPS - S_DVMAX + 1);
   int p = 0, jcur = 1 - S->jlast;
   if (!S->jclean && !S->mixed()) launch_fill(s, 3 * nc, S->Jb[jcur], 0.0);  // after a failed step
   S->jclean = false;
@@ -963,7 +975,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
                                  {P_JS, (int)scatter_blocks(S->np, P.chunk, P.span), 1, S_JS},
                                  {0, 0, 2, S_DVMAX, F_SPREAD_MAX},
                                  {0, 0, 1, S_BAD, F_SPREAD_MAX},
-                                 {0, 0, 1, S_PIECES, F_SPREAD_SUM},
+                                 {0, 0, 2, S_PIECES, F_SPREAD_SUM},  // and S_GROUPS
                                  {P_AA,
                                   aa_gather ? gg.blocks + gg.list_blocks : anderson_dot_blocks(n3),
                                   anderson_sums(mk), S_AA}};
@@ -1065,6 +1077,11 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
   ecpic_status st = sync_read(S);
   if (st != ECPIC_OK) return st;
   const double* h = S->host;
+  if (S->scatter_mm &&
+      h[S_GROUPS] > mm_turns_limit(S->np, S->G.ncell) * (double)S->np * (p + 1)) {
+    S->scatter_mm = false;
+    S->chunk = auto_chunk(S->np, S->span);
+  }
   if (prof) {
     float ta = 0.f, tb = 0.f;
     HIPCHK(hipEventElapsedTime(&ta, S->ev[0], S->ev[1]));

@@ -24,6 +24,7 @@ enum Slot : int {
   S_BAD,        // 1: an orbit had too many pieces, 1.5: a current contribution beyond the
                 // fixed-point range, 2: a non-finite velocity (max)
   S_PIECES,     // orbit pieces summed over particles    (sum of integers)
+  S_GROUPS,     // turns of the matrix-instruction scatter's wavefronts (sum of integers)
   S_AA,         // Anderson sums dF_i . dF_j (i <= j), then dF_i . f_p   (sums)
   S_AA_END = S_AA + kAndersonSums - 1,
   S_JE,         // sum_g J . E^{n+1/2} dV               (sum)

@@ -1091,6 +1091,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
   const int64_t base = (int64_t)blockIdx.x * P.chunk;
   double js[1] = {0.0};
   double bad = 0.0;
+  int turns = 0;  // of this wavefront: groups, and pieces outside the tile
   late_reduce_init<2>();
   int sref[3], tlo[3], dim[3];
   scatter_box<R>(P, st, vit, vbar, bx, base, P.chunk / kBlock,
@@ -1170,6 +1171,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
         filled += n;
         todo &= ~grp;
       }
+      turns += ngroups + __popcll(__ballot(has && !inside));
       if (ngroups > 0) {
         double sq[NQ], wq[NQ], tx[NQ], Y[NQ][W], Z[NQ][W];
         piece_rule<R>(s0, s1, sq, wq);
@@ -1276,6 +1278,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
       if (val != 0.0) unsafeAtomicAdd(J + l * nc + g, val);
     }
   }
+  if (lane == 0) unsafeAtomicAdd(sc.spread_copy(S_GROUPS), (double)turns);
   const double part[2] = {js[0], bad};
   const bool ismax[2] = {false, true};
   double blk[2];
