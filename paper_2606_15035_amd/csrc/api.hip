@@ -280,6 +280,13 @@ struct ecpic_sim {
     P.chunk = cfg.scatter_chunk > 0 ? cfg.scatter_chunk : chunk;
     P.span = scatter_mm ? P.chunk : std::max(P.chunk, span);
     P.scatter_mm = scatter_mm ? 1 : 0;
+    // Scatter blocks that run at once on one XCD sit together in meshes of up to 4096
+    // cells, where all XCDs would add to all of the current (its lines go from one L2 to
+    // the other; per pass: 262,144 at 16^3 57 -> 45 us, with orbits of 3 cells 9834 ->
+    // 7645, linear 38 -> 29, cubic 82 -> 73).  In larger ones an XCD's blocks then meet on
+    // the same lines (2,097,152 at 32^3 with orbits of 5 cells 79.8 -> 101 ms); fewer
+    // blocks run all at once (65,536 at 16x8x8 3006 -> 3176 us).
+    P.by_xcd = G.ncell <= 4096 && np >= 131072;
     P.nsp = nsp;
     for (int k = 0; k < kMaxSpecies; ++k) {
       P.qs[k] = qs[k];

@@ -68,6 +68,7 @@ struct StepParams {
   int chunk;  // particles per scatter block: a power of two in [256, 4096]
   int span;   // particles over which the lanes of a scatter block are spread: a power of two >= chunk
   int gper;   // batches of 256 particles per gather block (set by its launcher)
+  int by_xcd;  // scatter blocks in contiguous runs per XCD
   int scatter_mm;  // FP64, split, degree 2: the current by matrix instructions
   int nsp;
   double qs[kMaxSpecies];

@@ -659,7 +659,6 @@ struct PencilArgs {
 };
 
 // slots of a field: npl runs of nx + nx / 8 + 1 points, npl nx <= 2 kBlock, npl <= 4
-constexpr int kXcds = 8;
 constexpr int kPencilLds = 2 * kBlock + kBlock / 4 + 4;
 
 __global__ __launch_bounds__(kBlock) void k_cn_pencils(PencilArgs A) {

@@ -754,7 +754,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((
   __shared__ double tile[3 * kScatterNodes];  // FIX: int64 quanta in the same bytes
   unsigned long long* tile_q = reinterpret_cast<unsigned long long*>(tile);
   const int per_thread = P.chunk / kBlock;  // at most 16
-  const int64_t base = chunk_base(P.chunk, P.span, blockIdx.x);
+  const int block = P.by_xcd ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int64_t base = chunk_base(P.chunk, P.span, block);
   // The order of the particles of a lane (see ChunkBoxes): candidates r = 0 ..
   // per_lane - 1 of its segment, the one of place p to slot p / kWaves of wavefront
   // p % kWaves.  The counts lie in the tile, not in use yet, in rows padded against

@@ -160,6 +160,14 @@ __device__ __forceinline__ int div_small(int t, float inv_d) {
   return (int)(((float)t + 0.5f) * inv_d);
 }
 
+// The block of a grid that block blk stands for, so that every XCD (blocks go round robin
+// to the 8 of them) takes a contiguous eighth
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_block(int blk, int blocks) {
+  const int x = blk % kXcds;
+  return x * (blocks / kXcds) + min(x, blocks % kXcds) + blk / kXcds;
+}
+
 // first particle of scatter block blk, and particle k of this thread in it: the
 // block's lanes sit span / 64 particles apart, chunk / 64 consecutive particles
 // each; span / chunk blocks share a span

@@ -1,6 +1,8 @@
 """The current scatter where its rules change: steps on both sides of leaving the
 matrix-instruction kernel (thermal plasmas that leave it after a step, by the turns of its
-groups or by pieces outside its tile; dense ones that keep it).  Whole steps against the oracle in fixed-iteration mode, at
+groups or by pieces outside its tile; dense ones that keep it), and blocks in contiguous
+runs per XCD (131,072 particles and more on up to 4096 cells), with numbers of blocks that
+are and are not a multiple of 8.  Whole steps against the oracle in fixed-iteration mode, at
 1e-12 of the velocity, displacement, current and field scales (the bar of the whole-step
 parity tests)."""
 import pytest
@@ -23,3 +25,17 @@ def test_scatter_kernel_change(n, np_, vth, steps):
         g.picard_step()
         o.step()
         compare_states(wl, g, o, f"scatter rule {n} {np_} vth={vth} step {step}")
+
+
+@pytest.mark.parametrize("np_,r,chunk", [
+    (131071, 1, 0), (131072, 1, 0),
+    (135169, 1, 2048),   # 67 blocks
+    (131073, 2, 0), (131073, 3, 0),
+    (200001, 2, 0),      # 48 per cell and more: the matrix-instruction kernel
+])
+def test_scatter_blocks_by_xcd(np_, r, chunk):
+    wl = plasma((16, 16, 16), np_, r, 0.2, seed=np_ + r)
+    g, o = both(wl, tol=0.0, pmax=1, scatter_chunk=chunk)
+    g.picard_step()
+    o.step()
+    compare_states(wl, g, o, f"scatter by XCD {np_} r={r}")
