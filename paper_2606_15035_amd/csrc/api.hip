@@ -311,7 +311,7 @@ struct ecpic_sim {
 
 namespace {
 
-constexpr int kMaxSpan = 16384;
+constexpr int kMaxSpan = 1 << 20;
 
 // Span of the scatter's lanes: the power of two nearest to the particles of 64
 // cells, so that the 64 lanes of a wavefront sit in about as many cells and
@@ -323,9 +323,16 @@ constexpr int kMaxSpan = 16384;
 // (the fourth); quadratic, 100,002 at 12 per cell, 256 per block 33 / 28 / 27 /
 // 120 us (the third); 300,007 at 9 per cell and orbits of several cells, 256 per
 // block 90 / 90 / 323 / 1205 us (the second).
+// At most 16384, or an eighth of all particles: every block adds its whole node box to the
+// current, and few blocks over most of a small mesh do little else.  Measured with at most
+// 16384 / an eighth / a sixteenth: mixed at 4096 per cell, 2,097,152 562 / 163 / 156 us,
+// 8,388,608 at 2048 per cell 1178 / 556 / 554; cubic 2,097,152 at 4096 2014 / 259 /
+// 338, unsplit 2717 / 300 / 415; mixed 262,144 at 4096 per cell 155 / 152 / 153 (a span of
+// all of them 184).
 int auto_span(int64_t np, int64_t ncell) {
   int64_t span = 256;
-  while (span < kMaxSpan && span * span * 2 < 64 * np / ncell * (64 * np / ncell)) span *= 2;
+  const int64_t most = std::min<int64_t>(kMaxSpan, std::max<int64_t>(16384, np / 8));
+  while (span * 2 <= most && span * span * 2 < 64 * np / ncell * (64 * np / ncell)) span *= 2;
   return (int)span;
 }
 
@@ -355,9 +362,14 @@ int adjoint_chunk(int64_t np) {
   return chunk;
 }
 
+// one wavefront orders a segment of a span (launch_segment_order)
+constexpr int kMaxAdjSpan = 16384;
+
 // most scatter blocks of any chunk and span (blocks of 256 particles, and those
 // of the last span that may be empty)
-int64_t scatter_blocks_max(int64_t np) { return scatter_blocks(np > 0 ? np : 1, 256, kMaxSpan); }
+int64_t scatter_blocks_max(int64_t np, int64_t ncell) {
+  return scatter_blocks(np > 0 ? np : 1, 256, std::max(auto_span(np, ncell), 4096));
+}
 
 // The FP64 current by matrix instructions (k_scatter_mm): quadratic shape,
 // sorted in every step, and at least 48 particles per cell, so that the
@@ -374,13 +386,14 @@ bool use_scatter_mm(const ecpic_config* c, int64_t np, int64_t ncell) {
 // step that took more than this many per particle and pass.  Below 512 per cell it gains where
 // neighbours cross their knots together and loses where a plasma is thermal (per pass, this
 // kernel / the other; 64 per cell: cold beams 0.04 to 0.09 turns, 140 to 165 / 156 to 358 us;
-// orbits of 0.01, 0.3 and 1 cell at random, 0.102, 0.29 and 1.0 turns, 186 / 150, 319 / 217 and
-// 1091 / 423; 48 per cell 0.113 and more, 151 / 125; 128 per cell 0.084 and 0.127, 61 / 64
-// and 71 / 70; 256 per cell 0.075 and 0.109, 99 / 84 and 118 / 93, the one thermal case that
-// it keeps and loses).  From 512 on the other kernel's lanes share cells, and this one
-// wins until its pieces leave the tile (512 per cell 0.53, 1.09 and 4.2 turns, 601 / 982,
-// 6121 / 8408 and 64588 / 35052 us; 1024 per cell 0.91 and 3.9, 9321 / 23385 and 121178 /
-// 102929; 4096 per cell 0.12 and 2.5, 231 / 980 and 83185 / 1535).
+// orbits of 0.01, 0.3 and 1 cell at random, 0.102, 0.29 and 1.0 turns, 189 / 153, 319 / 225 and
+// 1084 / 423; 48 per cell 0.113 and more, 152 / 125; 128 per cell 0.084 and 0.127, 62 / 55
+// and 71 / 59; 256 per cell 0.075 and 0.109, 101 / 81 and 117 / 92: quiet plasmas of 100 and
+// more per cell keep it and lose up to a fifth).  From 512 on orbits of about a cell make
+// the other's node boxes overflow, and this kernel wins until its own pieces leave the tile
+// (512 per cell 0.16, 0.53, 1.09 and 4.2 turns, 256 / 212, 601 / 1209, 5925 / 7080 and 64356
+// / 22633 us; 1024 per cell 0.14, 0.46 and 3.9, 452 / 398, 1038 / 2042 and 133642 / 39592;
+// 4096 per cell 0.12 and 2.5, 231 / 203 and 81838 / 618).
 double mm_turns_limit(int64_t np, int64_t ncell) { return np < 512 * ncell ? 0.1 : 1.5; }
 constexpr int kMmChunk = 1024;  // its chunk at most: a 1024-node tile holds the box of 16 cells
 
@@ -432,10 +445,10 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->Uhalf = w.take<double>(3 * nc);
   for (int a = 0; a < 3; ++a) S->tw[a] = w.take<double2>(S->G.n[a] / 2);
   S->gcount = w.take<int>(1);
-  S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np));
+  S->sboxes = w.take<int>((size_t)kBoxInts * scatter_blocks_max(np, nc));
   const GatherGrid gg = gather_grid(np, nc);
   S->gboxes = w.take<int>((size_t)kBoxInts * std::max(gg.blocks, 1));
-  S->sorder = w.take<uint8_t>((size_t)256 * scatter_blocks_max(np));  // spans included
+  S->sorder = w.take<uint8_t>((size_t)256 * scatter_blocks_max(np, nc));  // spans included
   const int64_t gslots = gather_slots(np, nc);
   S->gorder = gslots > 0 ? w.take<uint16_t>((size_t)gslots) : nullptr;
   // the plain iteration's next iterate is the gather's output, so the gather
@@ -445,7 +458,7 @@ void carve(ecpic_sim* S, char* state, char* ws, size_t* state_bytes, size_t* ws_
   S->sc.red = w.take<double>(S_NSLOTS);
   S->sc.spread = w.take<double>((size_t)S_NSLOTS * kSpread * kSpreadStride);
   const int64_t maxblk = std::max<int64_t>(
-      scatter_blocks_max(np),  // at least particle_blocks(np)
+      scatter_blocks_max(np, nc),  // at least particle_blocks(np)
       std::max<int64_t>(mesh_blocks(nc), cn_pencil_blocks(S->G)));
   S->sc.part_stride = std::max<int64_t>((int64_t)kMaxSumValues * (maxblk > 0 ? maxblk : 1),
                                         (int64_t)kAndersonSums * anderson_dot_blocks(3 * np));
@@ -1490,7 +1503,8 @@ ecpic_status adjoint_step_impl(ecpic_sim* S, char* workspace, const double* x, c
   // The step's particles in cell order for the whole adjoint (x, v and w move
   // together; the particle kernels then work on local chunks), the caller's
   // order restored for lx0 and lv0 at the end.
-  const int chunk = adjoint_chunk(np), span = std::max(auto_span(np, nc), chunk);
+  const int chunk = adjoint_chunk(np);
+  const int span = std::max(std::min(auto_span(np, nc), kMaxAdjSpan), chunk);
   if (np > 0) {
     launch_iota(s, np, A.id);
     int* id = A.id;
