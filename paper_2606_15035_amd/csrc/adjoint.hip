@@ -505,7 +505,7 @@ struct AdjStrides {
       sx = ((dim[1] * sy + 11) & ~15) + 4;
     }
     if (dim[0] * sx > kAdjTileNodes) sx = dim[1] * sy;
-    fits = dim[0] * sx <= kAdjTileNodes;
+    fits = true;
   }
 };
 

@@ -95,11 +95,10 @@ __device__ __forceinline__ void fft_pencils(int N, int logN, int count, const do
     fft_stages<INV, ACROSS, 3>(N, logN, count, done, tw, at);
     done += 3;
   }
-  while (logN - done >= 2) {  // 2 or 4 stages left
+  while (logN > done) {  // 2 or 4 stages left, N being 4 to 256
     fft_stages<INV, ACROSS, 2>(N, logN, count, done, tw, at);
     done += 2;
   }
-  if (logN - done == 1) fft_stages<INV, ACROSS, 1>(N, logN, count, done, tw, at);
 }
 
 struct FftPass {
@@ -208,10 +207,6 @@ __device__ __forceinline__ void mode_k(const Grid& G, int64_t g, double* k) {
 
 // field order in a spectral level: phi, psi, Ax, Ay, Az, Ux, Uy, Uz, rho
 enum { F_PHI = 0, F_PSI = 1, F_A = 2, F_U = 5, F_RHO = 8 };
-
-__device__ __forceinline__ double2 ld(const double2* p, int f, int64_t nc, int64_t g) {
-  return p[f * nc + g];
-}
 
 // |E|^2 / (2 sigma1) + |B|^2 / (2 sigma2) of one mode (E = -i k phi - U, B = i k x A)
 __device__ __forceinline__ double mode_energy(const double* k, double2 phi, const double2* A,

@@ -2,7 +2,8 @@
 // the orbit-discrete gradient and canonical-momentum push, the consistency
 // sweep, and the end-of-step update.
 //
-// One lane per particle; particle arrays are structure-of-arrays doubles
+// One lane per particle, or four in the gather of small counts and of FP64 particles
+// beyond their block's node box; particle arrays are structure-of-arrays doubles
 // (component a of particle i at a*np + i).  The mesh fields a particle reads
 // during the gather are interleaved per node (kGbufStride doubles per node:
 // grad_h phi^{n+1/2}, A^n, A^{n+1}) so that one stencil node costs one short

@@ -125,14 +125,6 @@ __device__ __forceinline__ void atomic_max_nonneg(double* slot, double v) {
     atomicMax(reinterpret_cast<unsigned long long*>(slot), (unsigned long long)__double_as_longlong(v));
 }
 
-// Block max of a non-negative value, folded into *slot (bit-pattern atomicMax).
-// fmax drops NaN operands, so callers flag non-finite values separately.
-__device__ __forceinline__ void block_max_to(double v, double* slot) {
-  const double r = block_max(v);
-  if (threadIdx.x == 0 && r > 0.0)
-    atomicMax(reinterpret_cast<unsigned long long*>(slot), (unsigned long long)__double_as_longlong(r));
-}
-
 // Grid-wide sums, deterministic: every block writes its M block sums to
 // region[m * gridDim.x + blockIdx.x]; a one-block finishing kernel (launched
 // by the host after the producing kernels) adds each row in a fixed order.

@@ -67,8 +67,9 @@ __global__ __launch_bounds__(kBlock) void k_iota(int64_t n, int* p) {
 // Position of a node in the sorted order: columns of 4x4 nodes along z, one
 // after the other, each walked layer by layer, so that consecutive nodes are
 // neighbours (the columns, the layers and the rows inside a layer alternate
-// direction).  Any run of 64 nodes is then a 4x4x5 box wherever it starts, and
-// a shorter run a part of one.  In plain z-fastest order 64 nodes are two rows
+// direction).  Any run of 64 nodes inside a column is then in a 4x4x5 box wherever it
+// starts, one over the end of a column in 8x4 nodes and at most 4 layers, and a shorter run
+// in a part of that.  In plain z-fastest order 64 nodes are two rows
 // of 32 (a node box with orbits and stencils of 6x7x40, here 9x9x10), and the
 // particles of one block at 10 per cell lie in two or three separate rows.
 // Morton order is as compact inside its blocks, but a run that straddles two
