@@ -570,15 +570,16 @@ ecpic_status sync_read(ecpic_sim* S) {
   return ECPIC_OK;
 }
 
-// whether p is device memory that kernels on the current device can use in place
-bool on_device(const void* p) {
+// whether p is memory of the simulation's own device that its kernels can use in place:
+// another device's, whichever is current, and doubles off their alignment are copied
+bool on_device(const ecpic_sim* S, const void* p) {
+  if (reinterpret_cast<uintptr_t>(p) % alignof(double)) return false;
   hipPointerAttribute_t at;
   if (hipPointerGetAttributes(&at, p) != hipSuccess) {
     (void)hipGetLastError();  // ordinary host memory
     return false;
   }
-  int dev = -1;
-  return at.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && at.device == dev;
+  return at.type == hipMemoryTypeDevice && at.device == S->device;
 }
 
 // forward transform of 9 real device fields into spec[cur]; A^n into gbuf
@@ -1208,7 +1209,7 @@ ecpic_status ecpic_get_state(ecpic_sim* S, double* x, double* v, double* vprev, 
     double* dst[3] = {x, v, vprev};
     for (int k = 0; k < 3; ++k) {
       if (!dst[k]) continue;
-      double* to = on_device(dst[k]) ? dst[k] : S->vit;
+      double* to = on_device(S, dst[k]) ? dst[k] : S->vit;
       on_store(S, [&](auto& st, auto&) { launch_export(s, S->pp(), st, k, S->id, to); });
       HIPCHK(hipGetLastError());
       if (to == dst[k]) continue;
@@ -1217,7 +1218,7 @@ ecpic_status ecpic_get_state(ecpic_sim* S, double* x, double* v, double* vprev, 
     }
   }
   if (fields) {
-    double* to = on_device(fields) ? fields : S->realbuf;
+    double* to = on_device(S, fields) ? fields : S->realbuf;
     const RealIO o = soa_io(to, nc, 9);
     fft3_inverse(s, S->G, 9, S->spec[S->cur], S->batch, o, twp(S), 1.0 / (double)nc);
     HIPCHK(hipGetLastError());
@@ -1243,7 +1244,7 @@ ecpic_status ecpic_set_state(ecpic_sim* S, const double* x, const double* v, con
     for (int k = 0; k < 3; ++k) {
       if (!src[k]) continue;
       const double* from = src[k];
-      if (!on_device(from)) {
+      if (!on_device(S, from)) {
         HIPCHK(hipMemcpyAsync(S->vit, from, sizeof(double) * 3 * np, hipMemcpyDefault, s));
         from = S->vit;
       }
@@ -1253,7 +1254,7 @@ ecpic_status ecpic_set_state(ecpic_sim* S, const double* x, const double* v, con
   }
   if (fields) {
     const double* from = fields;
-    if (!on_device(from)) {
+    if (!on_device(S, from)) {
       HIPCHK(hipMemcpyAsync(S->realbuf, from, sizeof(double) * 9 * nc, hipMemcpyDefault, s));
       from = S->realbuf;
     }
