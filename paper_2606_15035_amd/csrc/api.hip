@@ -237,6 +237,7 @@ struct ecpic_sim {
   double2* batch;
   double* realbuf;
   double* Uhalf;
+  bool gfar = false;  // the last pass listed most particles
   int* gcount;  // length of the gather's list, whose particles lie in sb.key: free between sorts
   int* sboxes;  // node boxes of the scatter's chunks, found in a step's first pass
   int* gboxes;  // node boxes of the gather's blocks, likewise
@@ -980,7 +981,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
     if (prof_g) HIPCHK(hipEventRecord(S->ev[2], s));
     on_store(S, [&](auto& st, auto&) {  // v^{n+1,p+1}
       launch_gather_push(s, r, P, st, S->vit, S->vnew, S->vbar, S->gbuf,
-                         GatherList{S->gcount, S->sb.key}, S->sc, prev,
+                         GatherList{S->gcount, S->sb.key, S->gfar}, S->sc, prev,
                          ChunkBoxes{S->gboxes, p >= 1, S->gorder});
     });
     if (prof_g) HIPCHK(hipEventRecord(S->ev[3], s));
@@ -1029,6 +1030,7 @@ ecpic_status ecpic_picard_step(ecpic_sim* S, ecpic_step_info* info) {
       S->prof.ms[2] += t23;
       S->prof.launches[2] += 1;
     }
+    S->gfar = 2.0 * S->host[S_FAR - S_DVMAX] > (double)S->np;
     const double dv = S->host[0], vm = S->host[1], dj = S->host[2], js = S->host[3];
     if (S->host[4] >= 2.0 || S->host[4] != S->host[4])
       return fail(ECPIC_ENONFINITE, "non-finite velocity in Picard pass %d", p);

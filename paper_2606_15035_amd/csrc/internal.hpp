@@ -25,6 +25,7 @@ enum Slot : int {
                 // fixed-point range, 2: a non-finite velocity (max)
   S_PIECES,     // orbit pieces summed over particles    (sum of integers)
   S_GROUPS,     // turns of the matrix-instruction scatter's wavefronts (sum of integers)
+  S_FAR,        // particles on the gather's list         (integer)
   S_AA,         // Anderson sums dF_i . dF_j (i <= j), then dF_i . f_p   (sums)
   S_AA_END = S_AA + kAndersonSums - 1,
   S_JE,         // sum_g J . E^{n+1/2} dV               (sum)
@@ -121,8 +122,8 @@ struct HostRead {
   double* dst = nullptr;
   int first = 0, count = 0;
 };
-// clear_int (optional): an int set to zero after the jobs (the length of the gather's
-// list); read: slots that the kernel hands to the host, after the jobs
+// clear_int (optional): an int that goes to S_FAR and is set to zero (the length of the
+// gather's list); read: slots that the kernel hands to the host, after the jobs
 void launch_finish(hipStream_t s, Scratch sc, const FinishJob* jobs, int njobs,
                    int* clear_int = nullptr, HostRead read = HostRead{});
 
@@ -215,6 +216,7 @@ int64_t gather_slots(int64_t np, int64_t ncell);  // entries of ChunkBoxes::orde
 struct GatherList {
   int* count;
   int* particle;
+  bool most;  // most particles are expected on it (FP64: sets the lanes of a particle)
 };
 // vbar_out (nullable): (vnew + v^n) / 2, the vbar of a next pass whose iterate is vnew.
 // bx: node boxes of the blocks, as for the scatter's chunks.

@@ -434,7 +434,7 @@ struct FinishArgs {
   Scratch sc;
   FinishJob job[kMaxFinishJobs];
   int njobs;
-  int* clear_int;  // optional: set to zero once every job is done (a work-list count)
+  int* clear_int;  // optional: its value to S_FAR, then zero (a work-list count)
   HostRead read;
 };
 
@@ -448,6 +448,10 @@ static_assert(kSpread == kWave, "the finishing kernel folds one copy per lane");
 __global__ __launch_bounds__(kFinishThreads) void k_finish(FinishArgs F) {
   constexpr int NW = kFinishThreads / kWave;
   const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+  if (F.clear_int && threadIdx.x == kFinishThreads - 1) {  // of a wavefront without a row, mostly
+    F.sc.red[S_FAR] = (double)*F.clear_int;
+    *F.clear_int = 0;
+  }
   int row = 0;
   for (int j = 0; j < F.njobs; ++j) {
     const FinishJob jb = F.job[j];
@@ -475,7 +479,6 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(FinishArgs F) {
       }
     }
   }
-  if (F.clear_int && threadIdx.x == 0) *F.clear_int = 0;
   // Straight into the host's memory: a copy queued behind this kernel is a launch of
   // its own (4,096 particles: 3.4 us of the GPU's time in every pass).
   if (F.read.count > 0) {  // uniform

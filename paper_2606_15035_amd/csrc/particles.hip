@@ -1591,8 +1591,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     __syncthreads();
     const int count = *list.count;  // written by the tiled kernel (previous launch)
     // Every lane reads nodes of its own, 5 cache lines each, so that a particle's chain of
-    // rows and one CU's line rate bound the kernel.  With four lanes per particle (FP64
-    // only, see launch_gather_push), per pass: 300,007 particles at 9 per cell 56 -> 25
+    // rows and one CU's line rate bound the kernel.  With four lanes per particle (when:
+    // launch_gather_push), per pass: 300,007 particles at 9 per cell 56 -> 25
     // us, 100,002 at 12 16 -> 9 us.
     // A short list's entry j goes to block j % grid: all CUs share it.  Of a long one
     // neighbouring entries go to a wavefront, since particles listed together lie together
@@ -2190,7 +2190,14 @@ void launch_gather_push(hipStream_t s, int r, StepParams P, const PS& st, const 
       // Which particles are listed goes by the particles of a block, hence by the
       // order of the particles, and the mixed form's results do not: there all
       // of a launch's particles are summed alike.
-      far(std::integral_constant<int, PS::kMixed ? 1 : 4>{});
+      // In the FP64 form one lane is the faster one, but for cubic stencils, where most
+      // particles are listed (one / four lanes per pass: 524,288 at 128 per cell, orbits of 3
+      // cells 975 / 1549 us, never sorted 355 / 403; cubic 262,144 941 / 879; a tenth
+      // of 262,144 listed 213 / 171).
+      if (PS::kMixed || (list.most && R.value < 3))
+        far(std::integral_constant<int, 1>{});
+      else
+        far(std::integral_constant<int, 4>{});
     }
   };
   if constexpr (!PS::kMixed) {
