@@ -225,7 +225,7 @@ ecpic_status ecpic_set_state(ecpic_sim* sim, const double* x, const double* v,
    with the same configuration and particle count (and this library version)
    and restored from it continues exactly as the saved one would: bitwise in
    the mixed form, whose current is an exact integer sum, and up to the order
-   of the FP64 atomic additions in the FP64 form.  Restore: ECPIC_EINVAL for a
+   of the FP64 additions in the FP64 form.  Restore: ECPIC_EINVAL for a
    buffer that is not a checkpoint of this configuration and version. */
 ecpic_status ecpic_checkpoint_bytes(ecpic_sim* sim, size_t* bytes);
 ecpic_status ecpic_checkpoint_save(ecpic_sim* sim, void* host_dst);
